@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256) void batch_prep(const SceneDesc *__restrict__ 
 }
 
 // Offsets of each scene's share in a concatenation of per-scene counts
-// (candidates or allocated blocks), computed once per workgroup into LDS.
+// (candidates, or chunks of allocated blocks), computed once per workgroup
+// into LDS.
 template <bool kBlocks>
 __device__ __forceinline__ void scene_prefix(const SceneDesc *__restrict__ sd, int n, uint32_t *pre)
 {
@@ -74,7 +75,7 @@ __device__ __forceinline__ void scene_prefix(const SceneDesc *__restrict__ sd, i
         for (int k = 0; k < n; ++k) {
             const VolumeView &v = sd[k].v;
             const uint32_t c = !sd[k].active ? 0u
-                               : kBlocks    ? min(v.state->pool_count, v.capacity)
+                               : kBlocks    ? (min(v.state->pool_count, v.capacity) + kRangeChunk - 1) / kRangeChunk
                                             : min(v.state->cand_count, v.max_candidates);
             acc += c;
             pre[k + 1] = acc;
@@ -130,40 +131,40 @@ __global__ void batch_range_clear(const SceneDesc *__restrict__ sd, int n, uint3
     range_clear_body(d.v, d.tiles_x8, d.tiles_y8, d.cam.width, d.cam.height, gt - (long long)d.ray_base * 64);
 }
 
-// Persistent range pass over the concatenation of every active scene's blocks.
+// Range pass of one workgroup of `stride` over the concatenation of every
+// active scene's blocks, a chunk at a time (`pre`: chunk offsets).
+template <bool kDense>
+__device__ __forceinline__ void batch_range_body(const SceneDesc *__restrict__ sd, int n, const uint32_t *pre,
+                                                 RangeLds &L, uint32_t wg, uint32_t stride)
+{
+    auto widen = [&](const SceneDesc &d, uint32_t c, uint32_t zl, uint32_t zh) {
+        uint32_t *cmin = d.v.pix_range;
+        uint32_t *cmax = cmin + (size_t)((d.cam.width + kCell - 1) / kCell) * ((d.cam.height + kCell - 1) / kCell);
+        atomicMin(&cmin[c], zl);
+        atomicMax(&cmax[c], zh);
+    };
+    for (uint32_t g = wg; g < pre[n]; g += stride) {
+        const int s = scene_at(pre, n, g);
+        const SceneDesc &d = sd[s];
+        range_chunk<kDense>(d.v, d.cam, d.stamp, d.tiles_x8, d.tiles_y8, (g - pre[s]) * (uint32_t)kRangeChunk,
+                            min(d.v.state->pool_count, d.v.capacity), L, [&](uint32_t c, uint32_t zl, uint32_t zh) {
+                                if (!span_lds_add(L, ((uint32_t)s << 26) | c, zl, zh)) widen(d, c, zl, zh);
+                            });
+    }
+    for (int e = threadIdx.x; e < kSpanLds; e += 256) {
+        const uint32_t key = L.key[e];
+        if (key != kSpanEmpty) widen(sd[key >> 26], key & ((1u << 26) - 1u), L.lo[e], L.hi[e]);
+    }
+}
+
+template <bool kDense>
 __global__ __launch_bounds__(256) void batch_range(const SceneDesc *__restrict__ sd, int n)
 {
     __shared__ uint32_t pre[kMaxScenes + 1];
-    __shared__ SpanLds L;
+    __shared__ RangeLds L;
     span_lds_init(L);
     scene_prefix<true>(sd, n, pre);   // (synchronises the workgroup)
-    for (uint32_t g = blockIdx.x * 256u + threadIdx.x; g < pre[n]; g += gridDim.x * 256u) {
-        int s = 0;
-        for (int k = 1; k < n; ++k) s += pre[k] <= g ? 1 : 0;
-        const SceneDesc &d = sd[s];
-        range_block(d.v, d.cam, d.stamp, d.tiles_x8, d.tiles_y8, g - pre[s],
-                    [&](uint32_t c, uint32_t zl, uint32_t zh) {
-                        if (!span_lds_add(L, ((uint32_t)s << 26) | c, zl, zh)) {
-                            uint32_t *cmin = d.v.pix_range;
-                            uint32_t *cmax = cmin + (size_t)((d.cam.width + kCell - 1) / kCell) *
-                                                        ((d.cam.height + kCell - 1) / kCell);
-                            atomicMin(&cmin[c], zl);
-                            atomicMax(&cmax[c], zh);
-                        }
-                    });
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < kSpanLds; e += 256) {
-        const uint32_t key = L.key[e];
-        if (key != kSpanEmpty) {
-            const SceneDesc &d = sd[key >> 26];
-            const uint32_t c = key & ((1u << 26) - 1u);
-            uint32_t *cmin = d.v.pix_range;
-            uint32_t *cmax = cmin + (size_t)((d.cam.width + kCell - 1) / kCell) * ((d.cam.height + kCell - 1) / kCell);
-            atomicMin(&cmin[c], L.lo[e]);
-            atomicMax(&cmax[c], L.hi[e]);
-        }
-    }
+    batch_range_body<kDense>(sd, n, pre, L, blockIdx.x, gridDim.x);
 }
 
 // One thread per (tile, ray, lane of the ray's group); wavefronts never
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256) void batch_persistent(const SceneDesc *__restr
 {
     cooperative_groups::grid_group grid = cooperative_groups::this_grid();
     __shared__ uint32_t pre[kMaxScenes + 1];
-    __shared__ SpanLds L;
+    __shared__ RangeLds L;
     const int tid = threadIdx.x, lane = tid & 63;
     // frame reset
     for (uint32_t s = blockIdx.x; s < (uint32_t)n; s += gridDim.x)
@@ -243,38 +244,9 @@ __global__ __launch_bounds__(256) void batch_persistent(const SceneDesc *__restr
     }
     grid.sync();
     // range pass over every scene's blocks
-    {
-        span_lds_init(L);
-        scene_prefix<true>(sd, n, pre);   // (synchronises the workgroup)
-        for (uint32_t g = blockIdx.x * 256u + tid; g < pre[n]; g += gridDim.x * 256u) {
-            int s = 0;
-            for (int k = 1; k < n; ++k) s += pre[k] <= g ? 1 : 0;
-            const SceneDesc &d = sd[s];
-            range_block(d.v, d.cam, d.stamp, d.tiles_x8, d.tiles_y8, g - pre[s],
-                        [&](uint32_t c, uint32_t zl, uint32_t zh) {
-                            if (!span_lds_add(L, ((uint32_t)s << 26) | c, zl, zh)) {
-                                uint32_t *cmin = d.v.pix_range;
-                                uint32_t *cmax = cmin + (size_t)((d.cam.width + kCell - 1) / kCell) *
-                                                            ((d.cam.height + kCell - 1) / kCell);
-                                atomicMin(&cmin[c], zl);
-                                atomicMax(&cmax[c], zh);
-                            }
-                        });
-        }
-        __syncthreads();
-        for (int e = tid; e < kSpanLds; e += 256) {
-            const uint32_t key = L.key[e];
-            if (key != kSpanEmpty) {
-                const SceneDesc &d = sd[key >> 26];
-                const uint32_t c = key & ((1u << 26) - 1u);
-                uint32_t *cmin = d.v.pix_range;
-                uint32_t *cmax =
-                    cmin + (size_t)((d.cam.width + kCell - 1) / kCell) * ((d.cam.height + kCell - 1) / kCell);
-                atomicMin(&cmin[c], L.lo[e]);
-                atomicMax(&cmax[c], L.hi[e]);
-            }
-        }
-    }
+    span_lds_init(L);
+    scene_prefix<true>(sd, n, pre);   // (synchronises the workgroup)
+    batch_range_body<kDense>(sd, n, pre, L, blockIdx.x, gridDim.x);
     grid.sync();
     // raycast: 256-thread chunks of the (tile, ray, lane) space; a wavefront's
     // 64 threads lie in one tile, so the tests below are wave-uniform
@@ -335,7 +307,10 @@ static hipError_t enqueue_raycast(tsdf_batch *b, hipStream_t s)
     const int n = (int)b->vols.size();
     hipLaunchKernelGGL(batch_range_clear, dim3((unsigned)(((long long)b->ray_total * 64 + 255) / 256)), dim3(256), 0, s, b->dev, n,
                        b->ray_total);
-    hipLaunchKernelGGL(batch_range, dim3(2048), dim3(256), 0, s, b->dev, n);
+    if (b->dense)
+        hipLaunchKernelGGL(batch_range<true>, dim3(2048), dim3(256), 0, s, b->dev, n);
+    else
+        hipLaunchKernelGGL(batch_range<false>, dim3(2048), dim3(256), 0, s, b->dev, n);
     const long long threads = (long long)b->ray_total * 64 * b->group;
     dim3 grid((unsigned)((threads + 63) / 64));
     if (b->storage == TSDF_F16) {
@@ -445,6 +420,7 @@ static tsdf_status stage_step(tsdf_batch *b, const float *const *depth_dev, cons
             d.cam.t[r] = p[4 * r + 3];
         }
         d.fc = make_fuse_cam(d.v, d.cam);
+        set_ray_origin(d.cam, d.v);
         d.depth = depth_dev ? depth_dev[k] : nullptr;
         d.vertex = (float4 *)vertex_dev[k];
         d.normal = (float4 *)normal_dev[k];

@@ -6,7 +6,7 @@
 //   mark     one lane per slot: an evicted block is copied out; an
 //            evicted slot below the new block count K is a hole, a kept slot
 //            at or above K is a mover (there are as many of each)
-//   move     one wavefront per mover: its voxels, key, bound and box go to a
+//   move     one wavefront per mover: its voxels, key and masks go to a
 //            hole, so the kept blocks end up in slots [0, K); a hole is only
 //            written after the mark pass read it, and a mover is never a hole
 //   rebuild  the pool counter becomes K; the hash table, the occupancy bits
@@ -113,11 +113,9 @@ __global__ __launch_bounds__(256) void evict_move_kernel(VolumeView v, const uin
             T[(size_t)dst * kBlockVoxels + q * 64 + lane] = T[(size_t)src * kBlockVoxels + q * 64 + lane];
             P[(size_t)dst * kBlockVoxels + q * 64 + lane] = P[(size_t)src * kBlockVoxels + q * 64 + lane];
         }
-        if (lane == 0) {
-            v.pool_keys[dst] = v.pool_keys[src];
-            v.block_min[dst] = v.block_min[src];
-            v.block_box[dst] = v.block_box[src];
-        }
+        v.masks[dst].inside[lane] = v.masks[src].inside[lane];
+        v.masks[dst].value[lane] = v.masks[src].value[lane];
+        if (lane == 0) v.pool_keys[dst] = v.pool_keys[src];
     }
 }
 
@@ -129,7 +127,7 @@ __global__ void evict_fill_kernel(uint32_t *__restrict__ p, uint64_t n, uint32_t
 __global__ void evict_set_count_kernel(DeviceState *st, uint32_t K) { st->pool_count = K; }
 
 // Re-enters the K kept blocks: hash entry (slot << 32 | key), occupancy bit
-// and dense-index entry (slot and sign flag, as the fusion writes them).
+// and dense-index entry (the slot).
 __global__ __launch_bounds__(256) void evict_rebuild_kernel(VolumeView v, uint32_t K)
 {
     for (uint32_t s = blockIdx.x * 256u + threadIdx.x; s < K; s += gridDim.x * 256u) {
@@ -144,9 +142,8 @@ __global__ __launch_bounds__(256) void evict_rebuild_kernel(VolumeView v, uint32
         if (!placed) atomicOr(&v.state->status, (uint32_t)TSDF_FLAG_HASH_FULL);
         int bx, by, bz;
         unpack_key(key, bx, by, bz);
-        const uint64_t b = block_linear(v, bx, by, bz);
-        atomicOr(&v.occupancy[b >> 5], 1u << (b & 31));
-        if (v.block_index) v.block_index[b] = (int32_t)s | (v.block_min[s] > kKeyZero ? kIndexPositive : 0);
+        occupy(v, bx, by, bz);
+        if (v.block_index) v.block_index[block_linear(v, bx, by, bz)] = (int32_t)s;
     }
 }
 
@@ -227,7 +224,8 @@ tsdf_status tsdf_evict_blocks(tsdf_volume *vol, const int32_t lo[3], const int32
     hipLaunchKernelGGL(evict_fill_kernel, dim3(kEvictGrid), dim3(256), 0, stream, (uint32_t *)v.hash, hash_words,
                        0xffffffffu);
     const uint64_t vb = virtual_blocks(v);
-    hipLaunchKernelGGL(evict_fill_kernel, dim3(kEvictGrid), dim3(256), 0, stream, v.occupancy, (vb + 31) / 32, 0u);
+    hipLaunchKernelGGL(evict_fill_kernel, dim3(kEvictGrid), dim3(256), 0, stream, (uint32_t *)v.occ,
+                       2 * occ_total_words(v), 0u);
     if (v.block_index)
         hipLaunchKernelGGL(evict_fill_kernel, dim3(kEvictGrid), dim3(256), 0, stream, (uint32_t *)v.block_index, vb,
                            0xffffffffu);

@@ -505,8 +505,8 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
             slot = hash_insert_unique(v, key);
             if (slot >= 0) {
                 fresh = 1;
-                uint64_t b = block_linear(v, bx, by, bz);
-                atomicOr(&v.occupancy[b >> 5], 1u << (b & 31));
+                occupy(v, bx, by, bz);
+                if (v.block_index) v.block_index[block_linear(v, bx, by, bz)] = slot;
             }
         }
     }
@@ -514,27 +514,33 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
     fresh = __shfl(fresh, 0);
     __builtin_amdgcn_s_setprio(0);
     if (slot < 0) return;
-    // the block's bound and box as they stand, loaded ahead of the voxel data
-    uint32_t old_min = kKeyPosInf, old_box = 0;
-    if (lane == 0 && !fresh) {
-        old_min = v.block_min[slot];
-        old_box = v.block_box[slot];
+    // the column's voxel masks as they stand, loaded ahead of the voxel data
+    uint8_t *inside_mask = v.masks[slot].inside + lane, *value_mask = v.masks[slot].value + lane;
+    uint32_t old_inside = 0, old_value = 0;
+    if (!fresh) {
+        old_inside = *inside_mask;
+        old_value = *value_mask;
     }
 
     S *bt = poolT + (size_t)slot * kBlockVoxels + lane;
     S *bp = poolP + (size_t)slot * kBlockVoxels + lane;
-    // lower bound of the block's non-chi values as stored, and the voxels of
-    // this lane's column that hold a non-chi value now, both kept for the raycast
-    uint32_t kmin = kKeyPosInf, live = 0;
+    // inside and non-chi voxels among those of this lane's column that are
+    // written, by their values as stored
+    uint32_t inside = 0, value = 0;
+    auto note = [&](int z, float T) {
+        const float t = stored_value<S>(T);
+        const bool has = fabsf(t) <= 1.0f;
+        value |= (has ? 1u : 0u) << z;
+        inside |= (has && t <= 0.0f ? 1u : 0u) << z;
+    };
     if (fresh) {
 #pragma unroll
         for (int z = 0; z < 8; ++z) {
             const bool m = (vmask >> z) & 1u;
             store_s(bt + 64 * z, m ? Tk[z] : kChi);
             store_s(bp + 64 * z, m ? stored_weight<S>(first_p(v, pk[z])) : 0.0f);
-            if (m) kmin = min(kmin, order_key(stored_value<S>(Tk[z])));
+            if (m) note(z, Tk[z]);
         }
-        live = vmask;
     } else {
         // phase 5: load every z-slice that holds an update (whole slices:
         // 64 contiguous voxels), then update and store the valid voxels
@@ -557,10 +563,7 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
                     update_voxel<kRule>(v, T[z], P[z], Tk[z], pk[z]);
                     store_s(bt + 64 * z, T[z]);
                     store_s(bp + 64 * z, stored_weight<S>(P[z]));
-                    if (fabsf(T[z]) <= 1.0f) {
-                        kmin = min(kmin, order_key(stored_value<S>(T[z])));
-                        live |= 1u << z;
-                    }
+                    note(z, T[z]);
                 }
             }
         };
@@ -571,17 +574,8 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
         else
             update(std::integral_constant<int, TSDF_RULE_WEIGHTED>());
     }
-    // the owner wavefront folds its new values into the bound (values only
-    // ever lower it, so it stays below the true minimum)
-    kmin = wave_min_u32(kmin);
-    const uint32_t box = wave_box(live);
-    if (lane == 0) {
-        const uint32_t m = min(old_min, kmin);
-        v.block_min[slot] = m;
-        v.block_box[slot] = box_union(old_box, box);
-        if (v.block_index)
-            v.block_index[block_linear(v, bx, by, bz)] = slot | (m > kKeyZero ? kIndexPositive : 0);
-    }
+    *inside_mask = (uint8_t)((old_inside & ~vmask) | inside);
+    *value_mask = (uint8_t)((old_value & ~vmask) | value);
     const uint32_t cnt = __popc(vmask);
     acc.upd += cnt;
     acc.fresh += fresh ? cnt : 0u;

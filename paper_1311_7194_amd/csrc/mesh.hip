@@ -161,8 +161,7 @@ __device__ void load_tile(const VolumeView &v, uint32_t slot, uint32_t key, McLd
         int32_t s = -1;
         if (nx < v.nblk[0] && ny < v.nblk[1] && nz < v.nblk[2]) {
             if (v.block_index) {
-                const int32_t e = v.block_index[block_linear(v, nx, ny, nz)];
-                s = e < 0 ? -1 : (e & kIndexSlotMask);
+                s = v.block_index[block_linear(v, nx, ny, nz)];
             } else {
                 s = hash_find(v, pack_key(nx, ny, nz));
             }

@@ -7,27 +7,35 @@
 // and F(s_{n+1}) <= 0 valid; the bracket is refined to the root and central
 // differences one voxel apart give the normal.
 //
-// Range shrinking.  The paper rasterises the faces of occupied blocks into
-// per-pixel start and end textures so that rays only traverse the depth span
-// of occupied blocks.  Here a compute pass does the same at the granularity
-// of 4x4-pixel cells: for every allocated block it projects the box of
-// stencil bases that can give a valid sample (the bounding box of the
-// block's non-chi voxels, extended by one voxel upwards) and widens the
-// [min, max] camera depth of every cell holding a pixel centre the box's
-// projection may cover (boxes whose projection spans more than 64 cells
-// widen whole 8x8-pixel tiles instead).  Every valid sample lies in such a
-// box, so starting and ending each ray at its cell's span (joined with its
-// tile's) skips only invalid samples.
+// Block records and range shrinking.  The paper rasterises the faces of
+// occupied blocks into per-pixel start and end textures so that rays only
+// traverse the depth span of occupied blocks.  Here a compute pass over the
+// allocated blocks in view does more, from two bits per voxel that fusion
+// keeps (not chi; at or below zero): it finds the cells where a bracket can
+// end (no chi voxel, one at or below zero) and where one can begin (no chi
+// voxel, one above zero), stores them with the pool offsets of the block's
+// upper neighbours in a record per block, projects the box of the cells of the
+// first kind and widens the [min, max] camera depth of every 4x4-pixel cell
+// holding a pixel centre the projection may cover (boxes over more than 64
+// cells widen whole 8x8-pixel tiles instead).  Every bracket's end lies in
+// such a box, so starting and ending each ray at its cell's span (joined with
+// its tile's) loses none.
 //
-// March.  A group of G lanes marches one ray: lane j evaluates sample
-// n_base + j, shuffles pair every sample with its predecessor and a ballot
-// finds the first crossing, so a ray advances G samples per step.  Samples
-// live in voxel-centre coordinates q = (x - origin)/voxel - 1/2, where the 8
-// voxels around a sample are floor(q) + {0,1}^3.  When the group's last
-// sample lies in a cell whose base block is unallocated, every sample up to
-// the cell's exit is invalid and the group jumps past it; when all 8 blocks
-// that the cell's stencils reach hold only positive values, no crossing can
-// end inside the cell and the group jumps to the cell's last sample.
+// March.  A group of G lanes marches one ray, up to 32 samples per step, and a
+// sample costs one bit pair of its block's record instead of its eight voxels:
+// F is evaluated only where a bracket can begin at one sample and end at the
+// next (1-2 times a ray).  Samples live in voxel-centre coordinates
+// q = (x - origin)/voxel - 1/2, where the 8 voxels around a sample are
+// floor(q) + {0,1}^3.  When a step finds nothing and its last sample lies in a
+// block without cells where a bracket can end, the group jumps past it, or past
+// the largest empty aligned group of 4^3 or 16^3 blocks around it.
+//
+// What bounds it: instruction issue and the chains of dependent loads (the
+// march's two per step), not bytes.  Evaluating F at every sample of the band
+// kept the vector units 80 % busy on the 640x480 orbit (1 mm); with the
+// records, and the refinement finishing on the ray's cubic inside a cell:
+// 263 -> 195 us there (8 lanes per ray), 128 -> 109 us on the 1280x960 hand
+// (0.15 mm, 4 lanes), 188 -> 90 us with the hash only (4 mm, FP16).
 #include "raycast_device.h"
 
 namespace tsdf {
@@ -37,23 +45,23 @@ __global__ void range_clear_kernel(VolumeView v, int tiles_x, int tiles_y, int w
     range_clear_body(v, tiles_x, tiles_y, width, height, (long long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+template <bool kDense>
 __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, uint32_t stamp, int tiles_x,
                                                     int tiles_y)
 {
-    __shared__ SpanLds L;
+    __shared__ RangeLds L;
+    const uint32_t n = min(v.state->pool_count, v.capacity);
+    if (blockIdx.x * (uint32_t)kRangeChunk >= n) return;   // (the whole workgroup)
     span_lds_init(L);
-    __syncthreads();
     const int cw = (cam.width + kCell - 1) / kCell, ch = (cam.height + kCell - 1) / kCell;
     uint32_t *cmin = v.pix_range, *cmax = v.pix_range + (size_t)cw * ch;
-    const uint32_t n = min(v.state->pool_count, v.capacity);
-    for (uint32_t slot = blockIdx.x * 256u + threadIdx.x; slot < n; slot += gridDim.x * 256u)
-        range_block(v, cam, stamp, tiles_x, tiles_y, slot, [&](uint32_t c, uint32_t zl, uint32_t zh) {
+    for (uint32_t first = blockIdx.x * (uint32_t)kRangeChunk; first < n; first += gridDim.x * (uint32_t)kRangeChunk)
+        range_chunk<kDense>(v, cam, stamp, tiles_x, tiles_y, first, n, L, [&](uint32_t c, uint32_t zl, uint32_t zh) {
             if (!span_lds_add(L, c, zl, zh)) {
                 atomicMin(&cmin[c], zl);   // no return value: the lane does not wait
                 atomicMax(&cmax[c], zh);
             }
         });
-    __syncthreads();
     for (int e = threadIdx.x; e < kSpanLds; e += 256) {
         const uint32_t c = L.key[e];
         if (c != kSpanEmpty) {
@@ -117,13 +125,18 @@ hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, 
     hipLaunchKernelGGL(range_clear_kernel, dim3((n_tiles * 64 + 255) / 256), dim3(256), 0, s, v, tiles_x, tiles_y,
                        cam.width, cam.height);
     // range pass over the allocated blocks (grid-stride; the block count stays on the device)
-    hipLaunchKernelGGL(range_kernel, dim3(2048), dim3(256), 0, s, v, cam, stamp, tiles_x, tiles_y);
+    if (v.block_index)
+        hipLaunchKernelGGL(range_kernel<true>, dim3(2048), dim3(256), 0, s, v, cam, stamp, tiles_x, tiles_y);
+    else
+        hipLaunchKernelGGL(range_kernel<false>, dim3(2048), dim3(256), 0, s, v, cam, stamp, tiles_x, tiles_y);
     return hipGetLastError();
 }
 
-hipError_t launch_march(const VolumeView &v, const Camera &cam, uint32_t stamp, int group, float4 *vertex,
+hipError_t launch_march(const VolumeView &v, const Camera &camera, uint32_t stamp, int group, float4 *vertex,
                         float4 *normal, hipStream_t s, bool mark)
 {
+    Camera cam = camera;
+    set_ray_origin(cam, v);
     const int tiles_x = (cam.width + kRT - 1) / kRT, tiles_y = (cam.height + kRT - 1) / kRT;
     const int G = (group == 1 || group == 2 || group == 4 || group == 16) ? group : 8;
     const long long threads = (long long)tiles_x * tiles_y * 64 * G;

@@ -10,9 +10,6 @@ namespace tsdf {
 constexpr int kRT = 8;                      // raycast tile edge in pixels
 constexpr uint32_t kInfBits = 0x7f800000u;  // +inf as float bits
 constexpr int kCellFootprint = 64;          // largest footprint (cells) a block widens cell by cell
-constexpr uint32_t kInfoEmpty = 1u << 30;    // march: the sample's cell block is absent
-constexpr uint32_t kInfoPositive = 1u << 31; // march: every value the cell's stencils reach is positive
-
 // ------------------------------------------------------------ range maps
 
 constexpr int kCellsPerTile = kRT / kCell;   // cells along a tile edge
@@ -44,17 +41,30 @@ __device__ __forceinline__ void range_clear_body(const VolumeView &v, int tiles_
 
 // ------------------------------------------------------------ range pass
 
+// Block of the virtual grid -> pool slot, or -1.  The block must lie in the grid.
+template <bool kDense>
+__device__ __forceinline__ int32_t block_slot(const VolumeView &v, int bx, int by, int bz)
+{
+    if constexpr (kDense) return v.block_index[(uint32_t)block_linear(v, bx, by, bz)];
+    return occupied(v, bx, by, bz) ? hash_find(v, pack_key(bx, by, bz)) : -1;
+}
+
 // Cell spans gathered in LDS by one workgroup before they go to memory:
 // consecutive pool slots are neighbours in space, so their blocks widen the
 // same cells, and one pair of memory atomics per distinct cell replaces one
 // per block.  Keys are (scene << 26) | cell.
-constexpr int kSpanLds = 2048;
+constexpr int kSpanLds = 512;
 constexpr uint32_t kSpanEmpty = 0xffffffffu;
-struct SpanLds {
-    uint32_t key[kSpanLds], lo[kSpanLds], hi[kSpanLds];
+constexpr int kRangeChunk = 64;   // pool slots a workgroup takes at a time
+struct RangeLds {
+    uint32_t key[kSpanLds], lo[kSpanLds], hi[kSpanLds];   // span table
+    uint32_t slot[kRangeChunk], bkey[kRangeChunk];        // the chunk's blocks in view
+    uint32_t box[kRangeChunk];                            // their boxes
+    uint4 rect[kRangeChunk];                              // what these cover: cells c0 | c1 << 16, d0 | d1 << 16, depths
+    uint32_t n;
 };
 
-__device__ __forceinline__ void span_lds_init(SpanLds &L)
+__device__ __forceinline__ void span_lds_init(RangeLds &L)
 {
     for (int e = threadIdx.x; e < kSpanLds; e += blockDim.x) {
         L.key[e] = kSpanEmpty;
@@ -64,9 +74,9 @@ __device__ __forceinline__ void span_lds_init(SpanLds &L)
 }
 
 // Widens the entry of `key` (false when its probe run is full).
-__device__ __forceinline__ bool span_lds_add(SpanLds &L, uint32_t key, uint32_t zl, uint32_t zh)
+__device__ __forceinline__ bool span_lds_add(RangeLds &L, uint32_t key, uint32_t zl, uint32_t zh)
 {
-    uint32_t h = (key * 2654435761u) >> (32 - 11);
+    uint32_t h = (key * 2654435761u) >> (32 - 9);
 #pragma unroll 1
     for (int p = 0; p < 8; ++p) {
         const uint32_t k = atomicCAS(&L.key[h], kSpanEmpty, key);
@@ -80,35 +90,32 @@ __device__ __forceinline__ bool span_lds_add(SpanLds &L, uint32_t key, uint32_t 
     return false;
 }
 
-// One allocated block (pool slot) of the range pass.  Cell spans go to
-// `emit(cell, zl, zh)`; tile spans and the near-plane stamp go to memory.
-template <typename Emit>
-__device__ __forceinline__ void range_block(const VolumeView &v, const Camera &cam, uint32_t stamp, int tiles_x,
-                                            int tiles_y, uint32_t slot, Emit &&emit)
+// Projection of a box of voxel-centre coordinates q in [8B + lo, 8B + hi]
+// (x = origin + (q + 1/2) voxel): its camera depths and the pixel centres it
+// may cover.
+struct BoxView {
+    float zlo, zhi;
+    int i0, i1, j0, j1;
+    bool behind;    // reaches the camera plane: depths and pixels are not bounded
+    bool visible;   // in front of the camera and over at least one pixel centre (or behind)
+};
+
+__device__ __forceinline__ BoxView project_box(const VolumeView &v, const Camera &cam, int bx, int by, int bz,
+                                               const int lo[3], const int hi[3])
 {
-    uint32_t *tmin = v.tile_range;
-    uint32_t *tmax = v.tile_range + (size_t)tiles_x * tiles_y;
     // camera axes in float: x_c = R^T (x - t)
     const float R[9] = {(float)cam.R[0], (float)cam.R[1], (float)cam.R[2], (float)cam.R[3], (float)cam.R[4],
                         (float)cam.R[5], (float)cam.R[6], (float)cam.R[7], (float)cam.R[8]};
     const float fx = (float)cam.fx, fy = (float)cam.fy, cx = (float)cam.cx, cy = (float)cam.cy;
-    // a valid sample's stencil voxels are all non-chi, so its base voxel lies
-    // in its block's box of non-chi voxels: q in [8B + lo, 8B + hi + 1] with
-    // x = origin + (q + 1/2) voxel; a block without such voxels adds nothing
-    const uint32_t box = v.block_box[slot];
-    const uint32_t key = v.pool_keys[slot];
-    if (!(box & kBoxValid) || key == kEmptyKey) return;   // no voxels, or a slot whose insertion failed
-    int bx, by, bz;
-    unpack_key(key, bx, by, bz);
-    const float bwx = (float)((box_hi(box, 0) - box_lo(box, 0) + 1) * v.vs);
-    const float bwy = (float)((box_hi(box, 1) - box_lo(box, 1) + 1) * v.vs);
-    const float bwz = (float)((box_hi(box, 2) - box_lo(box, 2) + 1) * v.vs);
+    const float bwx = (float)((hi[0] - lo[0]) * v.vs), bwy = (float)((hi[1] - lo[1]) * v.vs),
+                bwz = (float)((hi[2] - lo[2]) * v.vs);
     // its min corner relative to the camera centre, in double then float
-    const float ox = (float)(v.origin[0] + (8.0 * bx + box_lo(box, 0) + 0.5) * v.vs - cam.t[0]);
-    const float oy = (float)(v.origin[1] + (8.0 * by + box_lo(box, 1) + 0.5) * v.vs - cam.t[1]);
-    const float oz = (float)(v.origin[2] + (8.0 * bz + box_lo(box, 2) + 0.5) * v.vs - cam.t[2]);
+    const float ox = (float)(v.origin[0] + (8.0 * bx + lo[0] + 0.5) * v.vs - cam.t[0]);
+    const float oy = (float)(v.origin[1] + (8.0 * by + lo[1] + 0.5) * v.vs - cam.t[1]);
+    const float oz = (float)(v.origin[2] + (8.0 * bz + lo[2] + 0.5) * v.vs - cam.t[2]);
     float zlo = 3.4e38f, zhi = -3.4e38f, ulo = 3.4e38f, uhi = -3.4e38f, vlo = 3.4e38f, vhi = -3.4e38f;
-    bool behind = false;
+    BoxView w;
+    w.behind = false;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const float dx = ox + ((k & 1) ? bwx : 0.0f), dy = oy + ((k & 2) ? bwy : 0.0f),
@@ -118,17 +125,12 @@ __device__ __forceinline__ void range_block(const VolumeView &v, const Camera &c
         const float zc = R[2] * dx + R[5] * dy + R[8] * dz;
         zlo = fminf(zlo, zc);
         zhi = fmaxf(zhi, zc);
-        behind |= !(zc > 1e-4f);
+        w.behind |= !(zc > 1e-4f);
         const float rz = 1.0f / zc;
         ulo = fminf(ulo, fx * xc * rz + cx);
         uhi = fmaxf(uhi, fx * xc * rz + cx);
         vlo = fminf(vlo, fy * yc * rz + cy);
         vhi = fmaxf(vhi, fy * yc * rz + cy);
-    }
-    if (zhi <= 0.0f) return;            // wholly behind the camera
-    if (behind) {                         // reaches the camera plane: rays start at the camera
-        v.state->near_stamp = stamp;
-        return;
     }
     // pixel centres (i, j) inside the projected box; eps bounds the float
     // error of the projected corners (positions rounded to float relative to
@@ -137,35 +139,222 @@ __device__ __forceinline__ void range_block(const VolumeView &v, const Camera &c
                       1e-3f;
     const float ulo_e = fmaxf(ulo - eps, -1.0f), uhi_e = fminf(uhi + eps, (float)cam.width);
     const float vlo_e = fmaxf(vlo - eps, -1.0f), vhi_e = fminf(vhi + eps, (float)cam.height);
-    const int i0 = max((int)ceilf(ulo_e), 0), i1 = min((int)floorf(uhi_e), cam.width - 1);
-    const int j0 = max((int)ceilf(vlo_e), 0), j1 = min((int)floorf(vhi_e), cam.height - 1);
-    if (!(ulo_e <= uhi_e && vlo_e <= vhi_e) || i0 > i1 || j0 > j1) return;
-    const uint32_t zl = __float_as_uint(fmaxf(zlo * (1.0f - 1e-5f) - 1e-6f, 0.0f));
-    const uint32_t zh = __float_as_uint(zhi * (1.0f + 1e-5f) + 1e-6f);
-    const int c0 = i0 / kCell, c1 = i1 / kCell, d0 = j0 / kCell, d1 = j1 / kCell;
-    if ((c1 - c0 + 1) * (d1 - d0 + 1) <= kCellFootprint) {
-        // small footprint: widen the span of every cell it covers
-        const int cw = (cam.width + kCell - 1) / kCell;
-        for (int d = d0; d <= d1; ++d)
-            for (int c = c0; c <= c1; ++c) emit((uint32_t)(d * cw + c), zl, zh);
-        return;
-    }
-    // large footprint (blocks close to the camera): widen whole tiles
-    for (int tj = j0 / kRT; tj <= j1 / kRT; ++tj)
-        for (int ti = i0 / kRT; ti <= i1 / kRT; ++ti) {
-            const size_t t = (size_t)tj * tiles_x + ti;
-            if (tmin[t] > zl) atomicMin(&tmin[t], zl);
-            if (tmax[t] < zh) atomicMax(&tmax[t], zh);
+    w.zlo = zlo;
+    w.zhi = zhi;
+    w.i0 = max((int)ceilf(ulo_e), 0);
+    w.i1 = min((int)floorf(uhi_e), cam.width - 1);
+    w.j0 = max((int)ceilf(vlo_e), 0);
+    w.j1 = min((int)floorf(vhi_e), cam.height - 1);
+    w.visible = zhi > 0.0f && (w.behind || (ulo_e <= uhi_e && vlo_e <= vhi_e && w.i0 <= w.i1 && w.j0 <= w.j1));
+    return w;
+}
+
+// Records of the blocks in view of a chunk (L.slot, L.bkey: `count` of them),
+// by 16 lanes each (r = lane & 15): lanes 0..7 look up the block and its upper
+// neighbours B + {0,1}^3, lanes 0..8 combine one row (fixed y) of voxel masks
+// each, row 8 being the first row of the upper y neighbours.  F is a convex
+// combination of its cell's eight voxels, so a bracket can end (F <= 0) only
+// in a cell without a chi voxel and with one at or below zero, and begin
+// (F > 0) only in one without a chi voxel and with one above zero.  L.box
+// receives the bounding box of the cells of the first kind.
+//
+// The work is a chain of three dependent loads (neighbour slots, masks) and
+// little arithmetic, so a thread's four blocks go through it together.
+template <bool kDense>
+__device__ __forceinline__ void block_records(const VolumeView &v, uint32_t count, RangeLds &L)
+{
+    constexpr int kPer = kRangeChunk / 16;
+    const int r = threadIdx.x & 15, group = threadIdx.x & 48, e0 = threadIdx.x >> 4;
+    const int row = r & 7, ny = r == 8 ? 2 : 0;   // the row's y, and the y neighbour it is taken from
+    int32_t sl[kPer];
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        if (16u * t >= count) break;   // uniform over the workgroup
+        const uint32_t e = min((uint32_t)(e0 + 16 * t), count - 1u);
+        int bx, by, bz;
+        unpack_key(L.bkey[e], bx, by, bz);
+        const int x = bx + (r & 1), y = by + ((r >> 1) & 1), z = bz + ((r >> 2) & 1);
+        const bool in = x < v.nblk[0] && y < v.nblk[1] && z < v.nblk[2];
+        if constexpr (kDense) {
+            const int32_t i = v.block_index[(uint32_t)(in ? block_linear(v, x, y, z) : block_linear(v, bx, by, bz))];
+            sl[t] = in ? i : -1;
+        } else {
+            sl[t] = r < 8 && in ? block_slot<false>(v, x, y, z) : -1;
         }
+    }
+    unsigned long long oI[kPer], oV[kPer], zI[kPer], zV[kPer];
+    uint32_t xI[kPer], xV[kPer], xzI[kPer], xzV[kPer];
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        if (16u * t >= count) break;
+        const int32_t s0 = __shfl(sl[t], group | ny), sx = __shfl(sl[t], group | ny | 1),
+                      sz = __shfl(sl[t], group | ny | 4), sxz = __shfl(sl[t], group | ny | 5);
+        // an absent block's masks are those of this block, replaced by zeros below
+        const int32_t self = __shfl(sl[t], group);
+        const VoxelMasks *m0 = v.masks + (s0 < 0 ? self : s0), *mx = v.masks + (sx < 0 ? self : sx),
+                         *mz = v.masks + (sz < 0 ? self : sz), *mxz = v.masks + (sxz < 0 ? self : sxz);
+        const unsigned long long *r0 = (const unsigned long long *)m0, *rz = (const unsigned long long *)mz;
+        oI[t] = r0[row];
+        oV[t] = r0[8 + row];
+        zI[t] = rz[row];
+        zV[t] = rz[8 + row];
+        xI[t] = mx->inside[8 * row];
+        xV[t] = mx->value[8 * row];
+        xzI[t] = mxz->inside[8 * row];
+        xzV[t] = mxz->value[8 * row];
+        if (s0 < 0) oV[t] = 0;     // (without a value the rest does not matter)
+        if (sx < 0) xV[t] = 0;
+        if (sz < 0) zV[t] = 0;
+        if (sxz < 0) xzV[t] = 0;
+    }
+    const unsigned long long kLow = 0x0101010101010101ull, kBut7 = 0x7f7f7f7f7f7f7f7full;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        if (16u * t >= count) break;
+        const uint32_t e = min((uint32_t)(e0 + 16 * t), count - 1u);
+        BlockRec *rec = v.recs + L.slot[e];
+        if (r < 8) rec->base[r] = (sl[t] < 0 ? v.capacity : (uint32_t)sl[t]) * (uint32_t)kBlockVoxels;   // absent: chi
+        // per row, byte x and bit z: some voxel of the cell inside (any), all
+        // inside (all), none chi (val)
+        // bit z: voxels z and z + 1, the latter from the z neighbour for z = 7
+        const unsigned long long up = ((oI[t] >> 1) & kBut7) | ((zI[t] & kLow) << 7);
+        unsigned long long all = oI[t] & up, any = oI[t] | up;
+        unsigned long long val = oV[t] & (((oV[t] >> 1) & kBut7) | ((zV[t] & kLow) << 7));
+        const uint32_t xup = (xI[t] >> 1) | ((xzI[t] & 1u) << 7);
+        const uint32_t xall = xI[t] & xup, xany = xI[t] | xup, xval = xV[t] & ((xV[t] >> 1) | ((xzV[t] & 1u) << 7));
+        // byte x: columns x and x + 1
+        any |= (any >> 8) | ((unsigned long long)xany << 56);
+        all &= (all >> 8) | ((unsigned long long)xall << 56);
+        val &= (val >> 8) | ((unsigned long long)xval << 56);
+        // rows y and y + 1
+        any |= (unsigned long long)__shfl_down((long long)any, 1);
+        all &= (unsigned long long)__shfl_down((long long)all, 1);
+        val &= (unsigned long long)__shfl_down((long long)val, 1);
+        const unsigned long long A = r < 8 ? any & val : 0ull;
+        const unsigned long long B = val & ~all;
+        if (r < 8) {
+            uint32_t w[4];   // columns 2k and 2k + 1: the bytes of A and B interleaved
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                w[k] = __builtin_amdgcn_perm((uint32_t)(B >> (k & 2 ? 32 : 0)), (uint32_t)(A >> (k & 2 ? 32 : 0)),
+                                             k & 1 ? 0x07030602u : 0x05010400u);
+            ((uint4 *)rec->cell)[r] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        // bounding box: z bits and x bits of the row, then over the rows
+        const uint32_t lo = (uint32_t)A, hi = (uint32_t)(A >> 32);
+        uint32_t zb = lo | hi;
+        zb |= zb >> 16;
+        zb = (zb | (zb >> 8)) & 0xffu;
+        // columns of the row that are not empty: bit 7 of each byte, gathered
+        const uint32_t nl = (((lo & 0x7f7f7f7fu) + 0x7f7f7f7fu) | lo) & 0x80808080u;
+        const uint32_t nh = (((hi & 0x7f7f7f7fu) + 0x7f7f7f7fu) | hi) & 0x80808080u;
+        const uint32_t xb = (((nl >> 7) * 0x01020408u) >> 24 & 0xfu) | ((((nh >> 7) * 0x01020408u) >> 24 & 0xfu) << 4);
+        uint32_t m = zb | (xb << 8) | (A ? 1u << (16 + r) : 0u);
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) m |= (uint32_t)__shfl_xor((int)m, off);
+        if (r == 0 && e0 + 16 * t < (int)count) {
+            uint32_t box = 0;
+            if (m) {
+                const uint32_t z = m & 0xffu, x = (m >> 8) & 0xffu, y = (m >> 16) & 0xffu;
+                box = box_make(__builtin_ctz(x), __builtin_ctz(y), __builtin_ctz(z), 31 - __builtin_clz(x),
+                               31 - __builtin_clz(y), 31 - __builtin_clz(z));
+            }
+            rec->box = box;
+            L.box[e] = box;
+        }
+    }
+}
+
+// The pool slots [first, first + kRangeChunk) below n of one scene, by a
+// workgroup of 256 threads: the blocks in view, their active cells, and the
+// spans of those.  Cell spans go to `emit(cell, zl, zh)`; tile spans and the
+// near-plane stamp go to memory.  Ends with a barrier.
+template <bool kDense, typename Emit>
+__device__ __forceinline__ void range_chunk(const VolumeView &v, const Camera &cam, uint32_t stamp, int tiles_x,
+                                            int tiles_y, uint32_t first, uint32_t n, RangeLds &L, Emit &&emit)
+{
+    const int tid = threadIdx.x;
+    if (tid == 0) L.n = 0;
+    __syncthreads();
+    if (tid < kRangeChunk) {
+        // samples based in block B have q in [8B, 8B + 8], and a pixel's rays
+        // need the records of the blocks up to one voxel off them (normals)
+        const uint32_t slot = first + tid;
+        const uint32_t key = slot < n ? v.pool_keys[slot] : kEmptyKey;
+        bool in = false;
+        if (key != kEmptyKey) {   // (a slot whose insertion failed holds no block)
+            int bx, by, bz;
+            unpack_key(key, bx, by, bz);
+            const int lo[3] = {-1, -1, -1}, hi[3] = {9, 9, 9};
+            in = project_box(v, cam, bx, by, bz, lo, hi).visible;
+        }
+        const unsigned long long m = __ballot(in);   // one wavefront
+        if (in) {
+            const int e = __popcll(m & ((1ull << tid) - 1ull));
+            L.slot[e] = slot;
+            L.bkey[e] = key;
+        }
+        if (tid == 0) L.n = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    const uint32_t count = L.n;
+    if (count) block_records<kDense>(v, count, L);
+    __syncthreads();
+    if ((uint32_t)tid < count) {
+        uint4 rect = make_uint4(1u, 1u, 0u, 0u);   // no cells
+        const uint32_t box = L.box[tid];
+        if (box & kBoxValid) {
+            int bx, by, bz;
+            unpack_key(L.bkey[tid], bx, by, bz);
+            // samples based in these cells: q in [8B + lo, 8B + hi + 1]
+            const int lo[3] = {box_lo(box, 0), box_lo(box, 1), box_lo(box, 2)};
+            const int hi[3] = {box_hi(box, 0) + 1, box_hi(box, 1) + 1, box_hi(box, 2) + 1};
+            const BoxView w = project_box(v, cam, bx, by, bz, lo, hi);
+            if (w.visible && w.behind) {
+                v.state->near_stamp = stamp;   // reaches the camera plane: rays start at the camera
+            } else if (w.visible) {
+                const uint32_t zl = __float_as_uint(fmaxf(w.zlo * (1.0f - 1e-5f) - 1e-6f, 0.0f));
+                const uint32_t zh = __float_as_uint(w.zhi * (1.0f + 1e-5f) + 1e-6f);
+                const int c0 = w.i0 / kCell, c1 = w.i1 / kCell, d0 = w.j0 / kCell, d1 = w.j1 / kCell;
+                if ((c1 - c0 + 1) * (d1 - d0 + 1) <= kCellFootprint) {
+                    rect = make_uint4((uint32_t)c0 | ((uint32_t)c1 << 16), (uint32_t)d0 | ((uint32_t)d1 << 16), zl, zh);
+                } else {
+                    // large footprint (blocks close to the camera): widen whole tiles
+                    uint32_t *tmin = v.tile_range;
+                    uint32_t *tmax = v.tile_range + (size_t)tiles_x * tiles_y;
+                    for (int tj = w.j0 / kRT; tj <= w.j1 / kRT; ++tj)
+                        for (int ti = w.i0 / kRT; ti <= w.i1 / kRT; ++ti) {
+                            const size_t t = (size_t)tj * tiles_x + ti;
+                            if (tmin[t] > zl) atomicMin(&tmin[t], zl);
+                            if (tmax[t] < zh) atomicMax(&tmax[t], zh);
+                        }
+                }
+            }
+        }
+        L.rect[tid] = rect;
+    }
+    __syncthreads();
+    // small footprint: widen the span of every cell it covers (four lanes a block)
+    if ((uint32_t)(tid >> 2) < count) {
+        const uint4 rect = L.rect[tid >> 2];
+        const int c0 = rect.x & 0xffffu, c1 = rect.x >> 16, d0 = rect.y & 0xffffu, d1 = rect.y >> 16;
+        const int w = c1 - c0 + 1, ncell = w * (d1 - d0 + 1), cw = (cam.width + kCell - 1) / kCell;
+        if (w > 0)
+            for (int k = tid & 3; k < ncell; k += 4) {
+                const int dy = k / w;
+                emit((uint32_t)((d0 + dy) * cw + c0 + (k - dy * w)), rect.z, rect.w);
+            }
+    }
+    __syncthreads();
 }
 
 // ------------------------------------------------------------ march
 
+// Rays in voxel-centre coordinates q = (x - origin) / voxel - 1/2: q = q0 + s dq,
+// q0 the camera centre (Camera::q0, the same for every ray).
 struct Ray {
-    double q0[3];    // q at s = 0 (camera centre)
-    double dq[3];    // dq/ds
-    double inv[3];   // ds/dq (0 where the ray is parallel to the axis)
-    double d[3];     // unit world direction
+    const double *q0;
+    double dq[3];    // dq/ds: the unit world direction over the voxel size
 };
 
 template <typename S>
@@ -175,70 +364,44 @@ __device__ __forceinline__ float ld<float>(const float *p) { return *p; }
 template <>
 __device__ __forceinline__ float ld<__half>(const __half *p) { return __half2float(*p); }
 
-// Pool element offsets (slot * 512) of cell block B and its upper
-// neighbours B + {0,1}^3; absent blocks point at the pool's chi block, so a
-// stencil reaching them reads chi and is invalid without a branch.  Also
-// whether every non-chi value in those 8 blocks is positive (then no sample
-// of the cell can have F <= 0: F is a convex combination of them).
-struct SlotCache {
-    int B[3];
+// The block a lane's last sample was based in: its packed coordinates, and the
+// pool offsets of it and its upper neighbours (absent ones: the chi block, so
+// that a stencil reaching them reads chi and is invalid without a branch).
+struct BlockCache {
+    uint32_t key;
     uint32_t base[8];
-    bool empty;      // block B itself is absent
-    bool positive;
 };
 
-// Dense index: one load per neighbour; the entry carries the block's sign flag.
 template <bool kDense>
-__device__ __forceinline__ void fill_cache(const VolumeView &v, SlotCache &c, int bx, int by, int bz)
+__device__ __forceinline__ void enter_block(const VolumeView &v, BlockCache &cache, const int c[3])
 {
-    c.B[0] = bx;
-    c.B[1] = by;
-    c.B[2] = bz;
-    const uint32_t chi_base = v.capacity * (uint32_t)kBlockVoxels;
-    bool pos = true;
-    if constexpr (kDense) {
-        // B itself is inside the grid (its stencils are); neighbours may not
-        // be: those read B's own entry and are then taken as absent
-        const uint32_t n0 = (uint32_t)v.nblk[0], n01 = n0 * (uint32_t)v.nblk[1];
-        const uint32_t lin = (uint32_t)block_linear(v, bx, by, bz);
-        const bool inx = bx + 1 < v.nblk[0], iny = by + 1 < v.nblk[1], inz = bz + 1 < v.nblk[2];
-        int32_t raw[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const bool in = (!(k & 1) || inx) && (!(k & 2) || iny) && (!(k & 4) || inz);
-            const uint32_t nb = lin + (in ? (k & 1) + ((k & 2) ? n0 : 0u) + ((k & 4) ? n01 : 0u) : 0u);
-            raw[k] = v.block_index[nb];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const bool in = (!(k & 1) || inx) && (!(k & 2) || iny) && (!(k & 4) || inz);
-            const int32_t e = in ? raw[k] : -1;
-            c.base[k] = e < 0 ? chi_base : (uint32_t)(e & kIndexSlotMask) * (uint32_t)kBlockVoxels;
-            pos &= (e < 0) || (e & kIndexPositive);
-            if (k == 0) c.empty = e < 0;
-        }
+    const int bx = c[0] >> 3, by = c[1] >> 3, bz = c[2] >> 3;
+    const uint32_t key = pack_key(bx, by, bz);
+    if (key == cache.key) return;
+    cache.key = key;
+    const int32_t slot = block_slot<kDense>(v, bx, by, bz);
+    if (slot >= 0) {
+        const uint4 *b = (const uint4 *)v.recs[slot].base;
+        const uint4 lo = b[0], hi = b[1];
+        cache.base[0] = lo.x;
+        cache.base[1] = lo.y;
+        cache.base[2] = lo.z;
+        cache.base[3] = lo.w;
+        cache.base[4] = hi.x;
+        cache.base[5] = hi.y;
+        cache.base[6] = hi.z;
+        cache.base[7] = hi.w;
     } else {
-        uint32_t kmin = kKeyPosInf;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int x = bx + (k & 1), y = by + ((k >> 1) & 1), z = bz + ((k >> 2) & 1);
-            int32_t sl = -1;
-            if (x < v.nblk[0] && y < v.nblk[1] && z < v.nblk[2] && occupied(v, x, y, z))
-                sl = hash_find(v, pack_key(x, y, z));
-            c.base[k] = sl < 0 ? chi_base : (uint32_t)sl * (uint32_t)kBlockVoxels;
-            if (sl >= 0) kmin = min(kmin, v.block_min[sl]);
-            if (k == 0) c.empty = sl < 0;
-        }
-        pos = kmin > kKeyZero;
+        for (int k = 0; k < 8; ++k) cache.base[k] = v.capacity * (uint32_t)kBlockVoxels;
     }
-    c.positive = pos;
 }
 
-// Trilinear F at integer base c (global voxel indices) with fractions f,
-// using offsets from the cache (c must lie in cell c.B).  False when invalid.
+// Trilinear F at integer base c (global voxel indices) with fractions f, c in
+// the cached block.  False when invalid.
 template <typename S>
-__device__ __forceinline__ bool interp_cached(const VolumeView &v, const SlotCache &cache, const int c[3],
-                                              const float f[3], float &F)
+__device__ __forceinline__ bool interp(const VolumeView &v, const BlockCache &cache, const int c[3], const float f[3],
+                                       float &F)
 {
     const S *__restrict__ pool = (const S *)v.poolT;
     const uint32_t l0 = c[0] & 7, l1 = c[1] & 7, l2 = c[2] & 7;
@@ -290,36 +453,45 @@ __device__ __forceinline__ bool stencil(const VolumeView &v, const double q[3], 
     return inside;
 }
 
-// F at q, refilling the lane's cache when the stencil's base block changes.
+// F at q, NaN when the sample is invalid.
 template <typename S, bool kDense>
-__device__ __forceinline__ bool sample_q(const VolumeView &v, SlotCache &cache, const double q[3], float &F)
+__device__ __forceinline__ float sample(const VolumeView &v, BlockCache &cache, const double q[3])
 {
     int c[3];
     float f[3];
-    if (!stencil(v, q, c, f)) return false;
-    if ((c[0] >> 3) != cache.B[0] || (c[1] >> 3) != cache.B[1] || (c[2] >> 3) != cache.B[2])
-        fill_cache<kDense>(v, cache, c[0] >> 3, c[1] >> 3, c[2] >> 3);
-    return interp_cached<S>(v, cache, c, f, F);
+    float F = __builtin_nanf("");
+    if (stencil(v, q, c, f)) {
+        enter_block<kDense>(v, cache, c);
+        float Fs;
+        if (interp<S>(v, cache, c, f, Fs)) F = Fs;
+    }
+    return F;
 }
 
-// First lattice index past the cell of block B along the ray (the caller's
-// samples before it all have their base voxel in B).  The division by h is a
+// First lattice index past the cells of block B, or of the aligned group of
+// 2^sh blocks per axis around it, along the ray (the caller's samples before
+// it all have their base voxel in there).  The division by h is a
 // product with 1/h: the index found lies within one of the exit, and the
 // test of its sample then returns the exit or one index before it (a later
 // resume point is never returned).
-__device__ __forceinline__ int cell_exit_sample(const Ray &r, const int B[3], double h, double inv_h)
+__device__ __forceinline__ int cell_exit_sample(const Ray &r, const int B[3], int sh, double h, double inv_h)
 {
     double s_exit = 1e300;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (r.dq[a] > 0.0) s_exit = fmin(s_exit, (8.0 * (B[a] + 1) - r.q0[a]) * r.inv[a]);
-        else if (r.dq[a] < 0.0) s_exit = fmin(s_exit, (8.0 * B[a] - r.q0[a]) * r.inv[a]);
+        const int lo = (B[a] >> sh) << (sh + 3);
+        // (a reciprocal to about an ulp, which the test below allows for)
+        double inv = __builtin_amdgcn_rcp(r.dq[a]);
+        inv = fma(inv, fma(-r.dq[a], inv, 1.0), inv);
+        inv = fma(inv, fma(-r.dq[a], inv, 1.0), inv);
+        const double face = (double)(r.dq[a] > 0.0 ? lo + (8 << sh) : lo);
+        if (r.dq[a] != 0.0) s_exit = fmin(s_exit, (face - r.q0[a]) * inv);
     }
     const int m = (int)fmin(floor(s_exit * inv_h), 2.0e9);
     double qm[3];
     q_at(r, (double)m * h, qm);
-    const bool still = ((int)floor(qm[0]) >> 3) == B[0] && ((int)floor(qm[1]) >> 3) == B[1] &&
-                       ((int)floor(qm[2]) >> 3) == B[2];
+    const bool still = ((int)floor(qm[0]) >> (sh + 3)) == (B[0] >> sh) && ((int)floor(qm[1]) >> (sh + 3)) == (B[1] >> sh) &&
+                       ((int)floor(qm[2]) >> (sh + 3)) == (B[2] >> sh);
     return still ? m + 1 : m;
 }
 
@@ -352,8 +524,9 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     const double h = 0.5 * v.vs;
 
     Ray r;
+    r.q0 = cam.q0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) r.q0[a] = r.dq[a] = r.inv[a] = r.d[a] = 0.0;
+    for (int a = 0; a < 3; ++a) r.dq[a] = 0.0;
     int n_lo = 1, n_end = 0;   // sample indices (a ray crosses the grid in fewer than 2^31 samples)
     float zmin_t = 0.0f, zmax_t = -1.0f;
     bool near = false;
@@ -372,12 +545,11 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     if (active && (near || zmin_t <= zmax_t)) {
         const double dc0 = (i - cam.cx) / cam.fx, dc1 = (jpix - cam.cy) / cam.fy;
         const double len = sqrt(dc0 * dc0 + dc1 * dc1 + 1.0);
+        double inv[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            r.d[a] = (cam.R[3 * a] * dc0 + cam.R[3 * a + 1] * dc1 + cam.R[3 * a + 2]) / len;
-            r.q0[a] = (cam.t[a] - v.origin[a]) * v.inv_vs - 0.5;
-            r.dq[a] = r.d[a] * v.inv_vs;
-            r.inv[a] = r.dq[a] != 0.0 ? 1.0 / r.dq[a] : 0.0;
+            r.dq[a] = (cam.R[3 * a] * dc0 + cam.R[3 * a + 1] * dc1 + cam.R[3 * a + 2]) / len * v.inv_vs;
+            inv[a] = r.dq[a] != 0.0 ? 1.0 / r.dq[a] : 0.0;
         }
         // valid samples need every stencil voxel in the grid: q in [0, G-1]
         double s_in = 0.0, s_out = 1e300;
@@ -388,7 +560,7 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             if (r.dq[a] == 0.0) {
                 miss |= (r.q0[a] < 0.0 || r.q0[a] > hiq);
             } else {
-                const double s0 = (0.0 - r.q0[a]) * r.inv[a], s1 = (hiq - r.q0[a]) * r.inv[a];
+                const double s0 = (0.0 - r.q0[a]) * inv[a], s1 = (hiq - r.q0[a]) * inv[a];
                 s_in = fmax(s_in, fmin(s0, s1));
                 s_out = fmin(s_out, fmax(s0, s1));
             }
@@ -403,96 +575,175 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
         }
     }
 
-    // ---- march: the group evaluates samples n_base .. n_base + G - 1 per step.
-    // An invalid sample carries F = NaN, so every comparison with it fails.
+    // ---- march: per step a group tests the samples n_base .. n_base + kSpan - 1
+    // (lane j those at j, j + G, ...), two bits each: whether a bracket can end
+    // in the sample's cell and whether one can begin there.  Only where one can
+    // end at a sample and begin at the one before, the group evaluates F: at the
+    // sample before, at it and (with the lanes left) at those after it, and
+    // looks for the first crossing among them.  An invalid sample carries
+    // F = NaN, so every comparison with it fails.
+    //
+    // A step is a chain of two dependent loads (block, cell) whatever the
+    // number of samples, and the rays of a wavefront wait for the longest:
+    // kPerLane samples a lane make the steps fewer.
+    constexpr int kPerLane = G >= 16 ? 2 : G == 8 ? 4 : 8;
+    constexpr int kSpan = G * kPerLane;   // at most 32: a bit each
     const float kNaN = __builtin_nanf("");
-    SlotCache cache;
-    cache.B[0] = cache.B[1] = cache.B[2] = -(1 << 30);
+    BlockCache cache;
+    cache.key = kEmptyKey;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) cache.base[k] = v.capacity * (uint32_t)kBlockVoxels;   // the chi block
-    cache.empty = true;
-    cache.positive = false;
+    for (int k = 0; k < 8; ++k) cache.base[k] = v.capacity * (uint32_t)kBlockVoxels;
     const double inv_h = 2.0 * v.inv_vs;
     int n_base = n_lo;
     bool done = !(active && n_lo <= n_end);
     bool hit = false;
-    float Fc = kNaN;     // carried last sample of the previous step
+    bool begin = true;       // whether a bracket can begin at sample n_base - 1 (true: not known)
     double s_lo = 0.0, s_hi = 0.0;
     float F_lo = 0.0f, F_hi = 0.0f;
     while (__ballot(!done)) {
-        const int n = n_base + j;
-        double q[3];
-        q_at(r, (double)n * h, q);
-        int c[3];
-        float f[3];
-        const bool inside = stencil(v, q, c, f) && !done && n <= n_end;
-        const int b0 = c[0] >> 3, b1 = c[1] >> 3, b2 = c[2] >> 3;
-        const bool need = inside && (b0 != cache.B[0] || b1 != cache.B[1] || b2 != cache.B[2]);
-        if (need) fill_cache<kDense>(v, cache, b0, b1, b2);
-        if constexpr (kMark) {
-            if (need && !cache.empty) {
-                const uint64_t lb = block_linear(v, b0, b1, b2);
-                atomicOr(&v.mark_bits[lb >> 5], 1u << (lb & 31));
-            }
-        }
-        float F = kNaN;
-        if (inside && !cache.empty) {
-            float Fs;
-            if (interp_cached<S>(v, cache, c, f, Fs)) F = Fs;
-        }
-        const uint32_t info = inside ? ((uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) |
-                                        (cache.empty ? kInfoEmpty : (cache.positive ? kInfoPositive : 0u)))
-                                     : 0u;
-        // pair every sample with its predecessor (lane j - 1, or the carry)
-        const float Fp_sh = __shfl(F, group_lane<G>(lane, (j + G - 1) & (G - 1)));
-        const float Fp = j == 0 ? Fc : Fp_sh;
-        const bool cross = !done && n <= n_end && Fp > 0.0f && F <= 0.0f;
-        const unsigned long long m = __ballot(cross);
-        const uint32_t gm = (uint32_t)(m >> (lane & ~(G - 1))) & ((G == 32 ? 0xffffffffu : (1u << G) - 1u));
-        // (done and gm are the same in every lane of a group, so the group's
-        // lanes all take part in these shuffles)
-        if (!done && gm) {
-            const int first = __builtin_ctz(gm);
-            const int nh = n_base + first;
-            s_lo = (double)(nh - 1) * h;
-            s_hi = (double)nh * h;
-            F_lo = __shfl(Fp, group_lane<G>(lane, first));
-            F_hi = __shfl(F, group_lane<G>(lane, first));
-            hit = true;
-            done = true;
-        }
-        // advance: the group's last lane decides a jump over its cell
-        const int last = G - 1;
-        const float F_last = __shfl(F, group_lane<G>(lane, last));
-        const uint32_t info_last = (uint32_t)__shfl((int)info, group_lane<G>(lane, last));
-        if (!done) {
-            const int n_last = n_base + last;
-            int next = n_last + 1;
-            bool carry = true;
-            if (n_last > n_end) {
-                done = true;
-            } else if (info_last & (kInfoEmpty | kInfoPositive)) {
-                const int Bc[3] = {(int)(info_last & 1023u), (int)((info_last >> 10) & 1023u),
-                                   (int)((info_last >> 20) & 1023u)};
-                const int exit_n = cell_exit_sample(r, Bc, h, inv_h);   // first sample past the cell
-                // empty: every sample before the exit is invalid; positive: none
-                // before the cell's last sample can end a crossing
-                const int target = (info_last & kInfoEmpty) ? exit_n : exit_n - 1;
-                if (target > next) {
-                    next = target;
-                    carry = false;
+        bool found = done;   // (a finished group takes no part in the steps)
+        while (__ballot(!found)) {
+            int32_t slot[kPerLane];
+            uint32_t cell[kPerLane];   // column of the cell's low corner | bit << 8
+            uint32_t last_key = 0;
+            unsigned long long occ0 = 0, occ1 = 0;
+            bool inside = false;
+#pragma unroll
+            for (int k = 0; k < kPerLane; ++k) {
+                const int n = n_base + k * G + j;
+                double q[3];
+                q_at(r, (double)n * h, q);
+                int c[3];
+                inside = !found && n <= n_end;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    c[a] = (int)floor(q[a]);
+                    inside &= (uint32_t)c[a] < (uint32_t)(v.dims[a] - 1);
+                }
+                cell[k] = (uint32_t)((c[0] & 7) | ((c[1] & 7) << 3) | ((c[2] & 7) << 8));
+                slot[k] = -1;
+                if (inside) {
+                    const int bx = c[0] >> 3, by = c[1] >> 3, bz = c[2] >> 3;
+                    slot[k] = block_slot<kDense>(v, bx, by, bz);
+                    if (k == kPerLane - 1) {
+                        last_key = pack_key(bx, by, bz);
+                        if (j == G - 1) {
+                            occ0 = v.occ[occ_word(v, 0, bx, by, bz)];
+                            occ1 = v.occ[occ_word(v, 1, bx, by, bz)];
+                        }
+                    }
                 }
             }
-            Fc = carry ? F_last : kNaN;
-            n_base = next;
-            if (n_base > n_end) done = true;
+            uint32_t ends = 0, begins = 0, box = 0;
+#pragma unroll
+            for (int k = 0; k < kPerLane; ++k)
+                if (slot[k] >= 0) {
+                    const BlockRec *rec = v.recs + slot[k];
+                    const uint32_t w = (uint32_t)rec->cell[cell[k] & 63u] >> (cell[k] >> 8);
+                    ends |= (w & 1u) << (k * G + j);
+                    begins |= ((w >> 8) & 1u) << (k * G + j);
+                    if (k == kPerLane - 1 && j == G - 1) box = rec->box;
+                }
+#pragma unroll
+            for (int off = 1; off < G; off <<= 1) {
+                ends |= (uint32_t)__shfl_xor((int)ends, off);
+                begins |= (uint32_t)__shfl_xor((int)begins, off);
+            }
+            const uint32_t cand = ends & ((begins << 1) | (begin ? 1u : 0u));
+            // (found, begin and the masks are the same in every lane of a group)
+            // the group's last sample decides a jump past the cells of its block
+            // when no bracket can end there, or of the largest aligned group of
+            // blocks around it that is empty (bits 30-31: log4 of its edge)
+            const uint32_t skip = inside && !box ? last_key | (occ0 ? 0u : occ1 ? 1u << 30 : 2u << 30) : kEmptyKey;
+            const uint32_t jump = (uint32_t)__shfl((int)skip, group_lane<G>(lane, G - 1));
+            if (!found) {
+                if (cand) {
+                    n_base += __builtin_ctz(cand);
+                    found = true;
+                } else {
+                    n_base += kSpan;
+                    begin = (begins >> (kSpan - 1)) & 1u;
+                    if (jump != kEmptyKey) {
+                        int B[3];
+                        unpack_key(jump, B[0], B[1], B[2]);
+                        const int exit_n = cell_exit_sample(r, B, 2 * (int)(jump >> 30), h, inv_h);
+                        if (exit_n > n_base) {
+                            n_base = exit_n;
+                            begin = true;
+                        }
+                    }
+                    if (n_base > n_end) {
+                        done = true;
+                        found = true;
+                    }
+                }
+            }
+        }
+        // F at samples n_base - 1 (slot 0) .. n_base + kEval - 2, a lane each
+        // (with one lane per ray: two rounds)
+        constexpr int kEval = G == 1 ? 2 : G;
+        float F[G == 1 ? 2 : 1];
+#pragma unroll
+        for (int t = 0; t < (G == 1 ? 2 : 1); ++t) {
+            const int n = n_base - 1 + (G == 1 ? t : j);
+            F[t] = kNaN;
+            if (!done && n >= 1 && n <= n_end) {
+                double q[3];
+                q_at(r, (double)n * h, q);
+                F[t] = sample<S, kDense>(v, cache, q);
+                if constexpr (kMark) {
+                    if (F[t] == F[t]) {
+                        int bx, by, bz;
+                        unpack_key(cache.key, bx, by, bz);
+                        const uint64_t lb = block_linear(v, bx, by, bz);
+                        atomicOr(&v.mark_bits[lb >> 5], 1u << (lb & 31));
+                    }
+                }
+            }
+        }
+        if constexpr (G == 1) {
+            if (!done) {
+                if (F[0] > 0.0f && F[1] <= 0.0f) {
+                    s_lo = (double)(n_base - 1) * h;
+                    s_hi = (double)n_base * h;
+                    F_lo = F[0];
+                    F_hi = F[1];
+                    hit = done = true;
+                } else {
+                    begin = F[1] > 0.0f;
+                    if (++n_base > n_end) done = true;
+                }
+            }
+        } else {
+            const float Fp = __shfl(F[0], group_lane<G>(lane, (j + G - 1) & (G - 1)));
+            const unsigned long long m = __ballot(!done && j > 0 && Fp > 0.0f && F[0] <= 0.0f);
+            const uint32_t gm = (uint32_t)(m >> (lane & ~(G - 1))) & ((1u << G) - 1u);
+            const int first = gm ? __builtin_ctz(gm) : 1;
+            const float Fl = __shfl(F[0], group_lane<G>(lane, first - 1)), Fh = __shfl(F[0], group_lane<G>(lane, first));
+            const float F_last = __shfl(F[0], group_lane<G>(lane, G - 1));
+            if (!done) {
+                if (gm) {
+                    s_lo = (double)(n_base + first - 2) * h;
+                    s_hi = (double)(n_base + first - 1) * h;
+                    F_lo = Fl;
+                    F_hi = Fh;
+                    hit = done = true;
+                } else {
+                    n_base += kEval - 1;
+                    begin = F_last > 0.0f;
+                    if (n_base > n_end) done = true;
+                }
+            }
         }
     }
 
-    // ---- refinement: quaternary search inside [s_lo, s_hi] (F_lo > 0 >= F_hi).
-    // Each step samples the 3 inner quarter points (point m by lane m % G of
-    // the group, in ceil(3 / G) rounds), so the points and hence the result do
-    // not depend on the group size; 6 steps shrink the bracket 4096-fold.
+    // ---- refinement: quaternary search inside [s_lo, s_hi] (F_lo > 0 >= F_hi),
+    // six steps that shrink the bracket 4096-fold.  Each looks at the 3 inner
+    // quarter points (point m by lane m % G of the group, in ceil(3 / G)
+    // rounds), so the points and hence the result do not depend on the group
+    // size.  Inside one cell F along the ray is a cubic: once a step's bracket
+    // lies in one, the steps after it evaluate the cubic through the step's
+    // points instead of the volume (most rays: after the second step).
     constexpr int kPts = 3, kSteps = 6, kRounds = (kPts + G - 1) / G;
     double a = s_lo, b = s_hi;
     float Fa = F_lo, Fb = F_hi;
@@ -507,8 +758,7 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             if (refine && m < kPts) {
                 double qm[3];
                 q_at(r, a + (b - a) * (double)(m + 1) * 0.25, qm);
-                float Fs;
-                if (sample_q<S, kDense>(v, cache, qm, Fs)) Fm = Fs;
+                Fm = sample<S, kDense>(v, cache, qm);
             }
 #pragma unroll
             for (int mm = rd * G; mm < (rd + 1) * G && mm < kPts; ++mm)
@@ -525,18 +775,49 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             if (bad) {
                 refine = false;   // an invalid point inside the bracket: keep the bracket
             } else {
-                float F_km1 = Fa, F_k = Fb;
-#pragma unroll
-                for (int mm = 0; mm < kPts; ++mm) {
-                    if (mm == k - 1) F_km1 = Fp[mm];
-                    if (mm == k) F_k = Fp[mm];
-                }
+                double qa[3], qb[3];
+                q_at(r, a, qa);
+                q_at(r, b, qb);
+                const bool one_cell = floor(qa[0]) == floor(qb[0]) && floor(qa[1]) == floor(qb[1]) &&
+                                      floor(qa[2]) == floor(qb[2]);
+                // the four of the five points around the root's quarter
+                const bool upper = k >= 2;
+                const float f0 = upper ? Fp[0] : Fa, f1 = upper ? Fp[1] : Fp[0], f2 = upper ? Fp[2] : Fp[1],
+                            f3 = upper ? Fb : Fp[2];
+                float lo = k == 0 ? Fa : k == 1 ? Fp[0] : k == 2 ? Fp[1] : Fp[2];
+                float hi = k == 0 ? Fp[0] : k == 1 ? Fp[1] : k == 2 ? Fp[2] : Fb;
                 const double na = k == 0 ? a : a + (b - a) * (double)k * 0.25;
                 const double nb = k == kPts ? b : a + (b - a) * (double)(k + 1) * 0.25;
-                Fa = F_km1;
-                Fb = F_k;
-                a = na;
-                b = nb;
+                if (one_cell) {
+                    // P(u) through f0..f3 at u = 0..3 (Newton's forward differences)
+                    const float d1 = f1 - f0, e1 = f2 - f1, e2 = f3 - f2;
+                    const float d2 = 0.5f * (e1 - d1), d3 = ((e2 - e1) - (e1 - d1)) * (1.0f / 6.0f);
+                    const float u0 = (float)(k - (upper ? 1 : 0));
+                    float t = 0.0f, dt = 1.0f;   // the bracket is u0 + [t, t + dt]
+                    for (int st = it + 1; st < kSteps; ++st) {
+                        dt *= 0.25f;
+                        float p[kPts];
+#pragma unroll
+                        for (int m = 0; m < kPts; ++m) {
+                            const float u = u0 + (t + (float)(m + 1) * dt);
+                            p[m] = fmaf(u, fmaf(u - 1.0f, fmaf(u - 2.0f, d3, d2), d1), f0);
+                        }
+                        const float l = lo, u = hi;
+                        const int kk = p[0] <= 0.0f ? 0 : p[1] <= 0.0f ? 1 : p[2] <= 0.0f ? 2 : 3;
+                        lo = kk == 0 ? l : kk == 1 ? p[0] : kk == 2 ? p[1] : p[2];
+                        hi = kk == 0 ? p[0] : kk == 1 ? p[1] : kk == 2 ? p[2] : u;
+                        t = fmaf((float)kk, dt, t);
+                    }
+                    const double w = nb - na;
+                    a = na + w * (double)t;
+                    b = na + w * (double)(t + dt);
+                    refine = false;
+                } else {
+                    a = na;
+                    b = nb;
+                }
+                Fa = lo;
+                Fb = hi;
             }
         }
     }
@@ -552,32 +833,29 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
 #pragma unroll
         for (int e = 0; e < 6; ++e) Fs[e] = kNaN;
         // sample e in {+x, -x, +y, -y, +z, -z} is taken by lane e % G of the
-        // group.  A lane taking several samples gives each its own copy of the
-        // slot cache (the march's, refilled where the stencil leaves its
-        // block), so their index and voxel loads are all in flight together.
+        // group.  A lane taking several samples looks up every block before it
+        // reads a voxel, so the loads are all in flight together.
         constexpr int kPer = (6 + G - 1) / G;
         int nc[kPer][3];
         float nf[kPer][3];
         bool nin[kPer];
-        SlotCache ncache[kPer];
+        BlockCache ncache[kPer];
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
             const int e = j + t * G;
             nin[t] = hit && e < 6;
+            ncache[t] = cache;
             if (nin[t]) {
                 double qe[3] = {qh[0], qh[1], qh[2]};
                 qe[e >> 1] += (e & 1) ? -1.0 : 1.0;
                 nin[t] = stencil(v, qe, nc[t], nf[t]);
+                if (nin[t]) enter_block<kDense>(v, ncache[t], nc[t]);
             }
-            ncache[t] = cache;
-            if (nin[t] && ((nc[t][0] >> 3) != cache.B[0] || (nc[t][1] >> 3) != cache.B[1] ||
-                           (nc[t][2] >> 3) != cache.B[2]))
-                fill_cache<kDense>(v, ncache[t], nc[t][0] >> 3, nc[t][1] >> 3, nc[t][2] >> 3);
         }
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
             float Fv;
-            if (nin[t] && interp_cached<S>(v, ncache[t], nc[t], nf[t], Fv)) {
+            if (nin[t] && interp<S>(v, ncache[t], nc[t], nf[t], Fv)) {
 #pragma unroll
                 for (int e = 0; e < 6; ++e)
                     if (e == j + t * G) Fs[e] = Fv;
@@ -596,8 +874,9 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
         float4 vout = make_float4(0.f, 0.f, 0.f, 0.f), nout = vout;
         const float gl = sqrtf(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
         if (ok && gl > 0.0f) {
-            vout = make_float4((float)(cam.t[0] + sh * r.d[0]), (float)(cam.t[1] + sh * r.d[1]),
-                               (float)(cam.t[2] + sh * r.d[2]), 1.0f);
+            const double m = sh * v.vs;   // along dq in voxels
+            vout = make_float4((float)(cam.t[0] + m * r.dq[0]), (float)(cam.t[1] + m * r.dq[1]),
+                               (float)(cam.t[2] + m * r.dq[2]), 1.0f);
             nout = make_float4(g[0] / gl, g[1] / gl, g[2] / gl, 1.0f);
         }
         const size_t pix = (size_t)jpix * cam.width + i;

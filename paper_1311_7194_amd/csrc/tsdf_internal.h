@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+#include <math.h>
 #include <stdint.h>
 #include <string.h>
 
@@ -42,19 +43,39 @@ struct Counters {
     unsigned long long total[kCtrLanes][CTR_N];
 };
 
+// One bit per voxel of a block: byte x + 8 y holds the column's eight voxels,
+// bit z.  Kept by fusion, which knows both for the voxels it writes.
+struct alignas(128) VoxelMasks {
+    uint8_t inside[64];   // T_hat <= 0 (and not chi)
+    uint8_t value[64];    // not chi
+};
+
+// What the raycast needs of a block besides its voxels; the range pass writes
+// it for every block in view before the rays start.
+struct alignas(64) BlockRec {
+    uint16_t cell[64];    // per column x + 8 y of cells (low corners): bit z where a bracket can end,
+                          // bit 8 + z where one can begin
+    uint32_t base[8];     // pool element offsets of the block and its upper neighbours B + {0,1}^3
+    uint32_t box;         // bounding box of the cells where a bracket can end (0: none)
+    uint32_t pad[7];
+};
+static_assert(sizeof(VoxelMasks) == 128 && sizeof(BlockRec) == 192, "per-block lines");
+
 // Pointers into the caller's device buffer.
 struct VolumeView {
     DeviceState *state;
     Counters *ctr;
     unsigned long long *hash;   // hash_slots entries: (slot << 32) | key, ~0 = empty
     uint32_t *pool_keys;        // capacity entries: key of the block in each pool slot
-    uint32_t *block_min;        // capacity entries: ordered key of a lower bound of the block's non-chi T
-    uint32_t *block_box;        // capacity entries: bounding box of the block's non-chi voxels (see box_*)
+    VoxelMasks *masks;          // capacity entries: inside and non-chi voxels of each block
+    BlockRec *recs;             // capacity entries: the raycast's record of each block in view
     uint32_t *tile_range;       // raycast: per 8x8 pixel tile (min depth bits, max depth bits)
     uint32_t *pix_range;        // raycast: per kCell x kCell pixel cell (min depth bits, max depth bits)
     uint32_t *mark_bits;        // one bit per virtual block: blocks a footprint query's rays read
-    uint32_t *occupancy;        // one bit per block of the virtual grid
-    int32_t *block_index;       // optional dense index per virtual block: slot | positive << 30, -1 = empty
+    unsigned long long *occ;    // allocated blocks: a bit each, a word per 4^3 blocks (see occ_*), then the
+                                // same over those words
+    uint32_t occ_words;         // words of the first level
+    int32_t *block_index;       // optional dense index per virtual block: pool slot, -1 = empty
     uint32_t *cand_bits;        // per-frame candidate dedup bits (all clear between frames)
     uint32_t *cand_list;        // max_candidates keys
     float2 *pixmap;             // per pixel (depth or 0, measurement variance p_hat)
@@ -80,6 +101,7 @@ struct Camera {
     double R[9];      // row-major camera-to-world rotation
     double t[3];
     double fx, fy, cx, cy;
+    double q0[3];     // camera centre in voxel-centre coordinates (t - origin) / voxel - 1/2 (set_ray_origin)
     int32_t width, height;
 };
 
@@ -88,6 +110,11 @@ struct NoiseParams {
     float coeff;
     const void *mlp;
 };
+
+inline void set_ray_origin(Camera &cam, const VolumeView &v)
+{
+    for (int a = 0; a < 3; ++a) cam.q0[a] = fma(cam.t[a] - v.origin[a], v.inv_vs, -0.5);
+}
 
 // Block key: 10 bits per axis.
 __host__ __device__ inline uint32_t pack_key(int bx, int by, int bz)
@@ -154,10 +181,9 @@ __device__ inline int32_t hash_insert_unique(const VolumeView &v, uint32_t key)
     return -1;
 }
 
-// Bounding box of a block's non-chi voxels, local coordinates 0..7: bits
-// 0-8 the low corner (x, y, z, 3 bits each), bits 9-17 the high corner,
-// bit 31 set when the box is not empty.  Boxes only grow (a voxel that
-// returns to chi stays inside), so they stay conservative.
+// Box of voxels or cells of a block, local coordinates 0..7: bits 0-8 the low
+// corner (x, y, z, 3 bits each), bits 9-17 the high corner, bit 31 set when
+// the box is not empty.
 constexpr uint32_t kBoxValid = 1u << 31;
 
 __host__ __device__ inline uint32_t box_make(int x0, int y0, int z0, int x1, int y1, int z1)
@@ -169,72 +195,39 @@ __host__ __device__ inline uint32_t box_make(int x0, int y0, int z0, int x1, int
 __host__ __device__ inline int box_lo(uint32_t b, int axis) { return (int)((b >> (3 * axis)) & 7u); }
 __host__ __device__ inline int box_hi(uint32_t b, int axis) { return (int)((b >> (9 + 3 * axis)) & 7u); }
 
-__host__ __device__ inline uint32_t box_union(uint32_t a, uint32_t b)
-{
-    if (!(a & kBoxValid)) return b;
-    if (!(b & kBoxValid)) return a;
-    int lo[3], hi[3];
-    for (int k = 0; k < 3; ++k) {
-        lo[k] = box_lo(a, k) < box_lo(b, k) ? box_lo(a, k) : box_lo(b, k);
-        hi[k] = box_hi(a, k) > box_hi(b, k) ? box_hi(a, k) : box_hi(b, k);
-    }
-    return box_make(lo[0], lo[1], lo[2], hi[0], hi[1], hi[2]);
-}
-
-// Box of the voxels of a wavefront's block that `zmask` (bit z: voxel
-// (x, y, z) of this lane's column, lane = x + 8 y) marks; 0 when none.
-__device__ inline uint32_t wave_box(uint32_t zmask)
-{
-    const unsigned long long L = __ballot(zmask != 0u);
-    if (!L) return 0u;
-    uint32_t zb = 0;
-#pragma unroll
-    for (int z = 0; z < 8; ++z) zb |= (__ballot((zmask >> z) & 1u) != 0ull ? 1u : 0u) << z;
-    uint32_t xb = 0, yb = 0;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const uint32_t row = (uint32_t)(L >> (8 * r)) & 0xffu;
-        xb |= row;
-        yb |= (row != 0u ? 1u : 0u) << r;
-    }
-    return box_make(__builtin_ctz(xb), __builtin_ctz(yb), __builtin_ctz(zb), 31 - __builtin_clz(xb),
-                    31 - __builtin_clz(yb), 31 - __builtin_clz(zb & 0xffu));
-}
-
 // Largest pool: slot * 512 + voxel stays below 2^31 (32-bit pool offsets).
 constexpr uint32_t kMaxCapacity = 1u << 22;
-constexpr int32_t kIndexPositive = 1 << 30;   // dense index: every non-chi value of the block is > 0
-constexpr int32_t kIndexSlotMask = kIndexPositive - 1;
-
-// Order-preserving map float -> uint32 (for integer min over floats).
-__host__ __device__ inline uint32_t order_key(float f)
+// Two-level occupancy.  Word `occ_word(v, 0, ...)` has a bit per block of an
+// aligned 4^3 group of blocks; word occ_word(v, 1, ...) a bit per group of an
+// aligned 4^3 group of groups.  A ray reads one word for 32^3 (or 128^3) voxels.
+__host__ __device__ inline uint32_t occ_dim(const VolumeView &v, int level, int axis)
 {
-    uint32_t b;
-    memcpy(&b, &f, 4);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+    return (uint32_t)(v.nblk[axis] + (4 << (2 * level)) - 1) >> (2 + 2 * level);
 }
-__host__ __device__ inline float order_value(uint32_t k)
+__host__ __device__ inline uint32_t occ_word(const VolumeView &v, int level, int bx, int by, int bz)
 {
-    uint32_t b = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
-    float f;
-    memcpy(&f, &b, 4);
-    return f;
+    const int sh = 2 + 2 * level;
+    return (level ? v.occ_words : 0u) +
+           ((uint32_t)(bz >> sh) * occ_dim(v, level, 1) + (uint32_t)(by >> sh)) * occ_dim(v, level, 0) + (uint32_t)(bx >> sh);
 }
-constexpr uint32_t kKeyPosInf = 0xff800000u;   // order_key(+inf)
-constexpr uint32_t kKeyZero = 0x80000000u;     // order_key(+0.0f)
-
-// Wave-wide minimum.
-__device__ inline uint32_t wave_min_u32(uint32_t x)
+__host__ __device__ inline int occ_bit(int level, int bx, int by, int bz)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x = min(x, (uint32_t)__shfl_xor((int)x, off));
-    return x;
+    const int sh = 2 * level;
+    return ((bx >> sh) & 3) | (((by >> sh) & 3) << 2) | (((bz >> sh) & 3) << 4);
 }
-
+__host__ __device__ inline uint64_t occ_total_words(const VolumeView &v)
+{
+    return (uint64_t)occ_dim(v, 0, 0) * occ_dim(v, 0, 1) * occ_dim(v, 0, 2) +
+           (uint64_t)occ_dim(v, 1, 0) * occ_dim(v, 1, 1) * occ_dim(v, 1, 2);
+}
+__device__ inline void occupy(const VolumeView &v, int bx, int by, int bz)
+{
+    atomicOr(&v.occ[occ_word(v, 0, bx, by, bz)], 1ull << occ_bit(0, bx, by, bz));
+    atomicOr(&v.occ[occ_word(v, 1, bx, by, bz)], 1ull << occ_bit(1, bx, by, bz));
+}
 __device__ inline bool occupied(const VolumeView &v, int bx, int by, int bz)
 {
-    uint64_t b = block_linear(v, bx, by, bz);
-    return (v.occupancy[b >> 5] >> (b & 31)) & 1u;
+    return (v.occ[occ_word(v, 0, bx, by, bz)] >> occ_bit(0, bx, by, bz)) & 1ull;
 }
 
 // ---- launchers (return hipError_t of the launch)

@@ -74,8 +74,7 @@ __global__ __launch_bounds__(256) void import_kernel(VolumeView v, const int32_t
         if (slot < 0) {
             slot = hash_insert_unique(v, key);
             if (slot >= 0) {
-                uint64_t b = block_linear(v, bx, by, bz);
-                atomicOr(&v.occupancy[b >> 5], 1u << (b & 31));
+                occupy(v, bx, by, bz);
             }
         }
     }
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(256) void import_kernel(VolumeView v, const int32_t
     if (slot < 0) return;
     S *dT = (S *)v.poolT + (size_t)slot * kBlockVoxels;
     S *dP = (S *)v.poolP + (size_t)slot * kBlockVoxels;
-    uint32_t kmin = kKeyPosInf, zmask = 0;
+    uint32_t inside = 0, value = 0;
     // lane = x + 8 y holds the column of voxels lane + 64 z
     for (int k = lane; k < kBlockVoxels; k += 64) {
         const S t = T[(size_t)w * kBlockVoxels + k];
@@ -91,17 +90,13 @@ __global__ __launch_bounds__(256) void import_kernel(VolumeView v, const int32_t
         dP[k] = P[(size_t)w * kBlockVoxels + k];
         const float f = (float)t;
         if (fabsf(f) <= 1.0f) {
-            kmin = min(kmin, order_key(f));
-            zmask |= 1u << (k >> 6);
+            value |= 1u << (k >> 6);
+            inside |= (f <= 0.0f ? 1u : 0u) << (k >> 6);
         }
     }
-    kmin = wave_min_u32(kmin);
-    const uint32_t box = wave_box(zmask);
-    if (lane == 0) {
-        v.block_min[slot] = kmin;
-        v.block_box[slot] = box;
-        if (v.block_index) v.block_index[block_linear(v, bx, by, bz)] = slot | (kmin > kKeyZero ? kIndexPositive : 0);
-    }
+    v.masks[slot].inside[lane] = (uint8_t)inside;
+    v.masks[slot].value[lane] = (uint8_t)value;
+    if (lane == 0 && v.block_index) v.block_index[block_linear(v, bx, by, bz)] = slot;
 }
 
 hipError_t launch_import(const VolumeView &v, const int32_t *keys, const void *T, const void *P, uint32_t n,
@@ -121,9 +116,9 @@ hipError_t launch_import(const VolumeView &v, const int32_t *keys, const void *T
 // ------------------------------------------------------------ layout
 
 struct Layout {
-    uint64_t state, ctr, hash, occupancy, block_index, cand_bits, cand_list, pixmap, pool_keys, block_min, block_box, tile_range, pix_range, mark_bits,
+    uint64_t state, ctr, hash, occupancy, block_index, cand_bits, cand_list, pixmap, pool_keys, masks, recs, tile_range, pix_range, mark_bits,
         poolT, poolP, total;
-    uint64_t bitmap_words, tile_words, nblocks;
+    uint64_t bitmap_words, occ_words, tile_words, nblocks;
 };
 
 static uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
@@ -163,8 +158,11 @@ static Layout layout_of(const tsdf_volume_desc *d)
     off = align256(off + sizeof(Counters));
     L.hash = off;
     off = align256(off + 8ull * d->hash_slots);
+    VolumeView w;
+    for (int a = 0; a < 3; ++a) w.nblk[a] = d->dims[a] / kBlock;
+    L.occ_words = occ_total_words(w);
     L.occupancy = off;
-    off = align256(off + 4ull * L.bitmap_words);
+    off = align256(off + 8ull * L.occ_words);
     L.block_index = off;
     if (d->dense_index) off = align256(off + 4ull * nblocks);
     L.cand_bits = off;
@@ -177,10 +175,10 @@ static Layout layout_of(const tsdf_volume_desc *d)
     off = align256(off + 8ull * (uint64_t)d->max_width * (uint64_t)d->max_height);
     L.pool_keys = off;
     off = align256(off + 4ull * d->capacity_blocks);
-    L.block_min = off;
-    off = align256(off + 4ull * d->capacity_blocks);
-    L.block_box = off;
-    off = align256(off + 4ull * d->capacity_blocks);
+    L.masks = off;
+    off = align256(off + sizeof(VoxelMasks) * (uint64_t)d->capacity_blocks);
+    L.recs = off;
+    off = align256(off + sizeof(BlockRec) * (uint64_t)d->capacity_blocks);
     L.tile_words = (uint64_t)((d->max_width + 7) / 8) * (uint64_t)((d->max_height + 7) / 8);
     L.tile_range = off;
     off = align256(off + 8ull * L.tile_words);
@@ -325,7 +323,7 @@ static Camera make_camera(const tsdf_intrinsics *K, const double *pose)
 
 static tsdf_status hip_status(hipError_t e) { return e == hipSuccess ? TSDF_OK : TSDF_EHIP; }
 
-static tsdf_status clear_volume(tsdf_volume *v, hipStream_t s)
+static tsdf_status clear_volume(tsdf_volume *v, hipStream_t s, bool created)
 {
     const Layout &L = v->layout;
     hipError_t e = fill_u32((uint32_t *)(v->base + L.state), sizeof(DeviceState) / 4, 0u, s);
@@ -334,10 +332,14 @@ static tsdf_status clear_volume(tsdf_volume *v, hipStream_t s)
     if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.tile_range), L.tile_words, 0x7f800000u, s);
     if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.tile_range) + L.tile_words, L.tile_words, 0u, s);
     if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.hash), 2ull * v->desc.hash_slots, 0xffffffffu, s);
-    if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.occupancy), L.bitmap_words, 0u, s);
+    if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.occupancy), 2 * L.occ_words, 0u, s);
     if (e == hipSuccess && v->desc.dense_index)
         e = fill_u32((uint32_t *)(v->base + L.block_index), L.nblocks, 0xffffffffu, s);
     if (e == hipSuccess) e = fill_u32((uint32_t *)(v->base + L.cand_bits), L.bitmap_words, 0u, s);
+    // the raycast's records hold pool offsets: in range from the start (a reset
+    // keeps them so)
+    if (e == hipSuccess && created)
+        e = fill_u32((uint32_t *)(v->base + L.recs), sizeof(BlockRec) / 4 * (uint64_t)v->desc.capacity_blocks, 0u, s);
     // the chi block (T = 2 in either storage type, P = 0)
     const uint64_t elem = v->desc.storage == TSDF_F16 ? 2 : 4;
     const uint64_t chi_off = elem * kBlockVoxels * (uint64_t)v->desc.capacity_blocks;
@@ -394,17 +396,17 @@ tsdf_status tsdf_create_volume(const tsdf_volume_desc *desc, void *dev_buf, uint
     w.state = (DeviceState *)(v->base + L.state);
     w.ctr = (Counters *)(v->base + L.ctr);
     w.pool_keys = (uint32_t *)(v->base + L.pool_keys);
-    w.block_min = (uint32_t *)(v->base + L.block_min);
+    w.masks = (VoxelMasks *)(v->base + L.masks);
     w.tile_range = (uint32_t *)(v->base + L.tile_range);
     w.pix_range = (uint32_t *)(v->base + L.pix_range);
-    w.block_box = (uint32_t *)(v->base + L.block_box);
+    w.recs = (BlockRec *)(v->base + L.recs);
     w.mark_bits = (uint32_t *)(v->base + L.mark_bits);
     w.max_width = desc->max_width;
     w.max_height = desc->max_height;
     v->raycast_stamp = 0;
     v->ray_group = 8;
     w.hash = (unsigned long long *)(v->base + L.hash);
-    w.occupancy = (uint32_t *)(v->base + L.occupancy);
+    w.occ = (unsigned long long *)(v->base + L.occupancy);
     w.block_index = desc->dense_index ? (int32_t *)(v->base + L.block_index) : nullptr;
     w.cand_bits = (uint32_t *)(v->base + L.cand_bits);
     w.cand_list = (uint32_t *)(v->base + L.cand_list);
@@ -416,6 +418,7 @@ tsdf_status tsdf_create_volume(const tsdf_volume_desc *desc, void *dev_buf, uint
         w.nblk[a] = desc->dims[a] / kBlock;
         w.origin[a] = desc->origin[a];
     }
+    w.occ_words = occ_dim(w, 0, 0) * occ_dim(w, 0, 1) * occ_dim(w, 0, 2);
     w.vs = desc->voxel_size;
     w.inv_vs = 1.0 / desc->voxel_size;
     w.delta = desc->trunc_voxels * desc->voxel_size;
@@ -429,7 +432,7 @@ tsdf_status tsdf_create_volume(const tsdf_volume_desc *desc, void *dev_buf, uint
     w.hash_mask = desc->hash_slots - 1;
     w.max_candidates = v->desc.max_candidates;
     w.storage = desc->storage;
-    tsdf_status st = clear_volume(v, stream);
+    tsdf_status st = clear_volume(v, stream, true);
     if (st != TSDF_OK) {
         delete v;
         return st;
@@ -472,7 +475,7 @@ tsdf_status tsdf_set_update_rule(tsdf_volume *vol, int32_t rule, int32_t weight_
 tsdf_status tsdf_reset_volume(tsdf_volume *vol, hipStream_t stream)
 {
     if (!vol) return TSDF_EINVAL;
-    return clear_volume(vol, stream);
+    return clear_volume(vol, stream, false);
 }
 
 tsdf_status tsdf_integrate_frame(tsdf_volume *vol, const float *depth_dev, const tsdf_intrinsics *K,
