@@ -49,168 +49,217 @@ __global__ __launch_bounds__(256) void forward_kernel(const uint16_t *__restrict
 
 // ---------------------------------------------------------------- training
 
-// Wave sum of a float (butterfly; every lane ends with the total).
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // Sample index of position k in the epoch's visiting order: an affine
 // permutation k -> (a k + b) mod n with a coprime to n (chosen by the host).
-// (a < n and k < n <= 2^31 keep a k + b inside 64 bits).
-__device__ __forceinline__ int64_t visit(int64_t k, int64_t n, uint64_t a, uint64_t b)
+// (a < n and k < n <= 2^31 keep a k + b inside 64 bits).  `inv` is
+// floor((2^64 - 1) / n): the quotient from its high product is at most two
+// short, which replaces two 64-bit divisions per sample.
+__device__ __forceinline__ uint64_t mod_n(uint64_t x, uint64_t n, uint64_t inv)
 {
-    return (int64_t)(((uint64_t)a * (uint64_t)(k % n) + b) % (uint64_t)n);
+    uint64_t r = x - __umul64hi(x, inv) * n;
+    if (r >= n) r -= n;
+    if (r >= n) r -= n;
+    return r;
+}
+__device__ __forceinline__ int64_t visit(int64_t k, int64_t n, uint64_t inv, uint64_t a, uint64_t b)
+{
+    return (int64_t)mod_n(a * mod_n((uint64_t)k, (uint64_t)n, inv) + b, (uint64_t)n, inv);
 }
 
-constexpr int kTrainWaves = 2;   // 128 samples per workgroup keeps LDS under 64 KiB
+constexpr int kTrainSamples = 128;   // per workgroup
+constexpr int kTrainWaves = 4;       // 32 samples (one matrix tile) each
+constexpr int kTS = 40;              // row stride of the bf16 tiles: 16-byte rows of 8, spread over the banks
 
+// Per-wavefront scratch.  The bf16 activations and errors are kept in both
+// orders (sample rows, unit rows), so that every matrix operand is one 16-byte
+// read per lane and K step.
+struct TrainWaveLds {
+    union {
+        struct {
+            alignas(16) uint16_t h1[32][kTS];    // [sample][unit]
+            alignas(16) uint16_t h1t[32][kTS];   // [unit][sample]
+            union {
+                struct {
+                    alignas(16) uint16_t e2[32][kTS];    // bf16(dL/da2), [sample][unit]
+                    alignas(16) uint16_t e2t[32][kTS];   // [unit][sample]
+                };
+                float t3[32][kMlpHidden + 1];    // before them: output-layer terms per (sample, unit)
+            };
+        };
+        float dw2[kMlpHidden * kMlpHidden];      // the wavefront's dW2, once the tiles are dead
+    };
+    alignas(16) float g1[32][36];                // silu'(a1), [unit][sample]
+    alignas(16) float x0[32][4];
+    alignas(16) float ds[32];
+    float red[kMlpHidden * kMlpIn + 3 * kMlpHidden + 2];   // the wavefront's other gradients and loss
+};
 struct TrainLds {
     MlpParamsLds P;
-    MlpWaveLds wave[kTrainWaves];              // forward scratch; t3 then holds dL/dh1, h1 then dW2
-    uint16_t e2[kTrainWaves][64][kMlpHidden + 4];   // bf16(dL/da2) per sample
-    float ds[kTrainWaves][64];
-    float red[kTrainWaves][kMlpHidden * kMlpIn + 3 * kMlpHidden + 2];
+    alignas(16) uint16_t w2[32][kTS];    // W2 as bf16 bits, [out][in]
+    alignas(16) uint16_t w2t[32][kTS];   // [in][out]
+    TrainWaveLds wave[kTrainWaves];
 };
+static_assert(sizeof(TrainLds) <= 80 * 1024, "two workgroups per CU");
 
-// One workgroup = 128 samples of the batch; writes the workgroup's summed
-// gradient (1249 values) and loss into partial[blockIdx.x].
-__global__ __launch_bounds__(128) void train_kernel(const uint16_t *__restrict__ params,
-                                                    const float4 *__restrict__ x, const float *__restrict__ r,
-                                                    int64_t n_samples, int64_t first, int64_t batch, uint64_t pa,
-                                                    uint64_t pb, float *__restrict__ partial)
+__device__ __forceinline__ i16x8_t tile_operand(const uint16_t *row)
+{
+    return *(const i16x8_t *)row;
+}
+
+// One workgroup = 128 samples of the batch, 32 per wavefront; writes the
+// workgroup's summed gradient (1249 values) and loss into partial[blockIdx.x].
+//
+// A batch of 65536 gives the chip 2048 wavefronts, two per SIMD, so the kernel
+// is one wavefront's chain of instruction latencies: 32 samples a wavefront
+// rather than 64 halve it, the sums over samples run down the accumulator rows
+// a lane holds (layer 1 took 160 butterfly sums of six exchanges each), and no
+// activation is computed twice.  In the accumulator layout a lane holds unit
+// o = lane % 32 of the samples 8 (q / 4) + 4 (lane / 32) + q % 4.
+__global__ __launch_bounds__(64 * kTrainWaves) __attribute__((amdgpu_waves_per_eu(2))) void train_kernel(const uint16_t *__restrict__ params,
+                                                                 const float4 *__restrict__ x,
+                                                                 const float *__restrict__ r, int64_t n_samples,
+                                                                 uint64_t n_inv, int64_t first, int64_t batch,
+                                                                 uint64_t pa, uint64_t pb, float *__restrict__ partial)
 {
     __shared__ TrainLds S;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     constexpr int NT = 64 * kTrainWaves;
-    mlp_stage_params(S.P, params, tid, NT);
-    __syncthreads();
-    const int64_t kb = blockIdx.x * (int64_t)NT + tid;   // position inside the batch
+    TrainWaveLds &W = S.wave[wv];
+    // this lane's sample, loaded ahead of the parameters (lanes m and m + 32 share it)
+    const int m = lane & 31, hf = lane >> 5;
+    const int64_t kb = blockIdx.x * (int64_t)kTrainSamples + 32 * wv + m;   // position inside the batch
     const bool live = kb < batch;
-    float xa[4] = {0.f, 0.f, 0.f, 0.f}, rr = 0.f;
+    float4 xv = make_float4(0.f, 0.f, 0.f, 0.f);
+    float rr = 0.f;
     if (live) {
-        const int64_t idx = visit(first + kb, n_samples, pa, pb);
-        const float4 xv = x[idx];
-        xa[0] = xv.x;
-        xa[1] = xv.y;
-        xa[2] = xv.z;
-        xa[3] = xv.w;
+        const int64_t idx = visit(first + kb, n_samples, n_inv, pa, pb);
+        xv = x[idx];
         rr = r[idx];
     }
-    float a2[2][16];
-    const float s = mlp_forward_wave(S.P, params + MLP_W2, S.wave[wv], xa, lane, a2);
-    const float e = __expf(-s);
-    const float loss = live ? 0.5f * (s + rr * rr * e) : 0.0f;
-    const float ds = live ? 0.5f * (1.0f - rr * rr * e) : 0.0f;
-    S.ds[wv][lane] = ds;
+    mlp_stage_params(S.P, params, tid, NT);
+#pragma unroll
+    for (int q = 0; q < kMlpHidden * kMlpHidden / NT; ++q) {
+        const int e = tid + q * NT, o = e >> 5, i = e & 31;
+        const uint16_t w = params[MLP_W2 + e];
+        S.w2[o][i] = w;
+        S.w2t[i][o] = w;
+    }
     __syncthreads();
 
-    // output layer and dL/da2 in the accumulator layout (lane: unit o = lane % 32)
-    const int col = lane & 31;
-    const float w3 = S.P.p[MLP_W3 + col];
-    float gW3 = 0.f, gb2 = 0.f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int row = 32 * t + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-            const float dsr = S.ds[wv][row];
-            const float h2 = bf16_round(silu(a2[t][q]));
-            const float da2 = dsr * w3 * silu_grad(a2[t][q]);
-            gW3 += dsr * h2;
-            gb2 += da2;
-            S.e2[wv][row][col] = bf16_bits(da2);
-        }
-    __syncthreads();
-
-    // dW2[o][i] = sum_m e2[m][o] h1[m][i]: M = o, N = i, K = samples (16 per step)
-    f32x16_t w2c;
-    {
-        const int kh = 8 * (lane >> 5);
-        f32x16_t c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            i16x8_t a, b;
-#pragma unroll
-            for (int el = 0; el < 8; ++el) {
-                a[el] = (short)S.e2[wv][16 * kk + kh + el][col];
-                b[el] = (short)S.wave[wv].h1[16 * kk + kh + el][col];
-            }
-            c = mfma_bf16_k16(a, b, c);
-        }
-        w2c = c;
-    }
-    // dh1[m][i] = sum_o e2[m][o] W2[o][i]: M = samples (two tiles), N = i, K = o
-    {
-        const int kh = 8 * (lane >> 5);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            f32x16_t c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                i16x8_t a, b;
-#pragma unroll
-                for (int el = 0; el < 8; ++el) {
-                    a[el] = (short)S.e2[wv][32 * t + col][16 * kk + kh + el];
-                    b[el] = (short)params[MLP_W2 + (16 * kk + kh + el) * kMlpHidden + col];
-                }
-                c = mfma_bf16_k16(a, b, c);
-            }
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int m = 32 * t + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-                S.wave[wv].t3[m][col] = c[q];   // dL/dh1, transposed to one sample per row
-            }
-        }
-    }
-    __syncthreads();   // every wavefront has read h1: its space now takes the dW2 tile
-    float *w2part = reinterpret_cast<float *>(&S.wave[wv].h1[0][0]);
+    // layer 1: this lane's sample, units 16 hf .. 16 hf + 15
+    const float x0[4] = {bf16_round(xv.x), bf16_round(xv.y), bf16_round(xv.z), bf16_round(xv.w)};
+    if (hf == 0) *(float4 *)W.x0[m] = make_float4(x0[0], x0[1], x0[2], x0[3]);
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-        const int o = 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-        w2part[o * kMlpHidden + col] = w2c[q];
-    }
-
-    // layer 1, one sample per lane: da1 = dh1 silu'(a1); dW1 = da1 x0^T, db1 = da1
-    float x0[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x0[i] = bf16_round(xa[i]);
-    float g1[kMlpHidden * kMlpIn], gb1[kMlpHidden];
-#pragma unroll
-    for (int o = 0; o < kMlpHidden; ++o) {
+        const int o = 16 * hf + q;
         float a = S.P.p[MLP_B1 + o];
 #pragma unroll
         for (int i = 0; i < kMlpIn; ++i) a += S.P.p[MLP_W1 + o * kMlpIn + i] * x0[i];
-        const float da1 = S.wave[wv].t3[lane][o] * silu_grad(a);
-        gb1[o] = da1;
-#pragma unroll
-        for (int i = 0; i < kMlpIn; ++i) g1[o * kMlpIn + i] = da1 * x0[i];
+        const uint16_t h = bf16_bits(silu(a));
+        W.h1[m][o] = h;
+        W.h1t[o][m] = h;
+        W.g1[o][m] = silu_grad(a);
     }
-    // wave reductions, then across the 4 wavefronts
-    float *red = S.red[wv];
+    __syncthreads();
+
+    // layer 2: a2[m][o] = sum_i h1[m][i] W2[o][i] + b2[o]
+    const int col = lane & 31, kh = 8 * hf;
+    f32x16_t c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16_t a2 = c;
 #pragma unroll
-    for (int k = 0; k < kMlpHidden * kMlpIn; ++k) {
-        const float v = wave_sum(g1[k]);
-        if (lane == 0) red[k] = v;
-    }
+    for (int kk = 0; kk < 2; ++kk)
+        a2 = mfma_bf16_k16(tile_operand(&W.h1[col][16 * kk + kh]), tile_operand(&S.w2[col][16 * kk + kh]), a2);
+    const float b2 = S.P.p[MLP_B2 + col], w3 = S.P.p[MLP_W3 + col];
+    float h2[16];
 #pragma unroll
-    for (int k = 0; k < kMlpHidden; ++k) {
-        const float v = wave_sum(gb1[k]);
-        if (lane == 0) red[kMlpHidden * kMlpIn + k] = v;
+    for (int q = 0; q < 16; ++q) {
+        a2[q] += b2;
+        h2[q] = bf16_round(silu(a2[q]));
+        W.t3[8 * (q >> 2) + 4 * hf + (q & 3)][col] = w3 * h2[q];
     }
-    {
-        // gW3 and gb2 live in lanes o and o + 32 (two row halves)
-        const float w3s = gW3 + __shfl_xor(gW3, 32), b2s = gb2 + __shfl_xor(gb2, 32);
-        if (lane < 32) {
-            red[kMlpHidden * kMlpIn + kMlpHidden + lane] = b2s;
-            red[kMlpHidden * kMlpIn + 2 * kMlpHidden + lane] = w3s;
+    __syncthreads();
+
+    // output of this lane's sample: each half sums 16 units
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) s += W.t3[m][16 * hf + q];
+    s += __shfl_xor(s, 32);
+    s += S.P.p[MLP_B3];
+    const float e = __expf(-s);
+    const float loss = live ? 0.5f * (s + rr * rr * e) : 0.0f;
+    const float ds = live ? 0.5f * (1.0f - rr * rr * e) : 0.0f;
+    if (hf == 0) W.ds[m] = ds;
+    __syncthreads();
+
+    // output layer and dL/da2
+    float gW3 = 0.f, gb2 = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float4 d4 = *(const float4 *)&W.ds[8 * g + 4 * hf];
+        const float d[4] = {d4.x, d4.y, d4.z, d4.w};
+        uint16_t eb[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int q = 4 * g + k;
+            const float da2 = d[k] * w3 * silu_grad(a2[q]);
+            gW3 += d[k] * h2[q];
+            gb2 += da2;
+            eb[k] = bf16_bits(da2);
+            W.e2[8 * g + 4 * hf + k][col] = eb[k];
         }
-        const float b3s = wave_sum(ds), ls = wave_sum(loss);
+        *(uint2 *)&W.e2t[col][8 * g + 4 * hf] =
+            make_uint2((uint32_t)eb[0] | ((uint32_t)eb[1] << 16), (uint32_t)eb[2] | ((uint32_t)eb[3] << 16));
+    }
+    __syncthreads();
+
+    // dW2[o][i] = sum_m e2[m][o] h1[m][i] and dh1[m][i] = sum_o e2[m][o] W2[o][i]
+    f32x16_t w2c = c, dh = c;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        w2c = mfma_bf16_k16(tile_operand(&W.e2t[col][16 * kk + kh]), tile_operand(&W.h1t[col][16 * kk + kh]), w2c);
+        dh = mfma_bf16_k16(tile_operand(&W.e2[col][16 * kk + kh]), tile_operand(&S.w2t[col][16 * kk + kh]), dh);
+    }
+    // layer 1, unit col: da1 = dh1 silu'(a1); dW1 = sum_m da1 x0^T, db1 = sum_m da1
+    float gw[kMlpIn] = {0.f, 0.f, 0.f, 0.f}, gb1 = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float4 s4 = *(const float4 *)&W.g1[col][8 * g + 4 * hf];
+        const float sg[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float da1 = dh[4 * g + k] * sg[k];
+            const float4 xq = *(const float4 *)W.x0[8 * g + 4 * hf + k];
+            gb1 += da1;
+            gw[0] += da1 * xq.x;
+            gw[1] += da1 * xq.y;
+            gw[2] += da1 * xq.z;
+            gw[3] += da1 * xq.w;
+        }
+    }
+    // the two row halves of a unit, then the samples' own sums over the 32 lanes of one half
+    gb1 += __shfl_xor(gb1, 32);
+    gb2 += __shfl_xor(gb2, 32);
+    gW3 += __shfl_xor(gW3, 32);
+#pragma unroll
+    for (int i = 0; i < kMlpIn; ++i) gw[i] += __shfl_xor(gw[i], 32);
+    float b3s = ds, ls = loss;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) {
+        b3s += __shfl_xor(b3s, off);
+        ls += __shfl_xor(ls, off);
+    }
+    __syncthreads();   // every wavefront has read its tiles: their space takes dW2
+#pragma unroll
+    for (int q = 0; q < 16; ++q) W.dw2[(8 * (q >> 2) + 4 * hf + (q & 3)) * kMlpHidden + col] = w2c[q];
+    if (hf == 0) {
+#pragma unroll
+        for (int i = 0; i < kMlpIn; ++i) W.red[col * kMlpIn + i] = gw[i];
+        W.red[kMlpHidden * kMlpIn + col] = gb1;
+        W.red[kMlpHidden * kMlpIn + kMlpHidden + col] = gb2;
+        W.red[kMlpHidden * kMlpIn + 2 * kMlpHidden + col] = gW3;
         if (lane == 0) {
-            red[kMlpHidden * kMlpIn + 3 * kMlpHidden] = b3s;
-            red[kMlpHidden * kMlpIn + 3 * kMlpHidden + 1] = ls;
+            W.red[kMlpHidden * kMlpIn + 3 * kMlpHidden] = b3s;
+            W.red[kMlpHidden * kMlpIn + 3 * kMlpHidden + 1] = ls;
         }
     }
     __syncthreads();
@@ -218,7 +267,7 @@ __global__ __launch_bounds__(128) void train_kernel(const uint16_t *__restrict__
     for (int k = tid; k < kMlpHidden * kMlpIn + 3 * kMlpHidden + 2; k += NT) {
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kTrainWaves; ++w) v += S.red[w][k];
+        for (int w = 0; w < kTrainWaves; ++w) v += S.wave[w].red[k];
         int dst;
         if (k < 128) dst = MLP_W1 + k;
         else if (k < 160) dst = MLP_B1 + (k - 128);
@@ -228,22 +277,41 @@ __global__ __launch_bounds__(128) void train_kernel(const uint16_t *__restrict__
         else dst = kMlpParams;   // loss, stored in the padding
         out[dst] = v;
     }
-    for (int k = tid; k < kMlpHidden * kMlpHidden; k += NT) {
+#pragma unroll
+    for (int q = 0; q < kMlpHidden * kMlpHidden / NT; ++q) {
+        const int k = tid + q * NT;
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kTrainWaves; ++w) v += reinterpret_cast<const float *>(&S.wave[w].h1[0][0])[k];
+        for (int w = 0; w < kTrainWaves; ++w) v += S.wave[w].dw2[k];
         out[MLP_W2 + k] = v;
     }
 }
 
-// grad[p] = (sum over workgroups of partial[wg][p]) / batch; loss likewise.
-__global__ void reduce_kernel(const float *__restrict__ partial, int n_wg, int64_t batch, float *__restrict__ grad,
-                              float *__restrict__ loss)
+// grad[p] = (sum over workgroups of partial[wg][p]) / batch in double; loss
+// likewise.  One workgroup per 64 parameters: its 16 wavefronts take every
+// 16th partial each (consecutive lanes read consecutive parameters), then add
+// up through LDS.  One lane per parameter over all partials is a chain of 512
+// loads: 122 us for a batch of 65536, against 5 us.
+constexpr int kReduceWaves = 16;
+__global__ __launch_bounds__(64 * kReduceWaves) void reduce_kernel(const float *__restrict__ partial, int n_wg,
+                                                                   int64_t batch, float *__restrict__ grad,
+                                                                   float *__restrict__ loss)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kMlpParams) return;
+    __shared__ double sum[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane;
     double acc = 0.0;
-    for (int w = 0; w < n_wg; ++w) acc += partial[(size_t)w * kMlpParamsPadded + p];
+    if (p <= kMlpParams) {
+        const float *src = partial + p;
+#pragma unroll 8
+        for (int w = wv; w < n_wg; w += kReduceWaves) acc += src[(size_t)w * kMlpParamsPadded];
+    }
+    sum[wv][lane] = acc;
+    __syncthreads();
+    if (wv != 0 || p > kMlpParams) return;
+    acc = 0.0;
+#pragma unroll
+    for (int w = 0; w < kReduceWaves; ++w) acc += sum[w][lane];
     if (p < kMlpParams) grad[p] = (float)(acc / (double)batch);
     else if (loss) loss[0] = (float)(acc / (double)batch);
 }
@@ -294,15 +362,47 @@ __global__ __launch_bounds__(256) void sample_count_kernel(const float *depth, c
     if (threadIdx.x == 0) counts[blockIdx.x] = (uint32_t)c;
 }
 
-__global__ void scan_kernel(uint32_t *counts, int nblocks, uint64_t *base, uint64_t *total)
+// Exclusive scan of the workgroups' counts on top of the running total, by one
+// workgroup: 1024 counts a round, four per lane (a single lane takes a round
+// trip per count: 62 us for the 1200 of a 640x480 frame, against 4 us).
+__global__ __launch_bounds__(256) void scan_kernel(const uint32_t *__restrict__ counts, int nblocks,
+                                                   uint64_t *__restrict__ base, uint64_t *__restrict__ total)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    uint64_t acc = total[0];
-    for (int b = 0; b < nblocks; ++b) {
-        base[b] = acc;
-        acc += counts[b];
+    __shared__ uint32_t wave_sum[4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint64_t carry = total[0];
+    for (int b0 = 0; b0 < nblocks; b0 += 1024) {
+        const int k0 = b0 + 4 * threadIdx.x;
+        uint32_t c[4], s = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c[q] = k0 + q < nblocks ? counts[k0 + q] : 0u;
+            s += c[q];
+        }
+        uint32_t inc = s;   // (at most 1024 counts of 256: 32 bits)
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)inc, off);
+            if (lane >= off) inc += y;
+        }
+        if (lane == 63) wave_sum[wv] = inc;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wv) before += wave_sum[w];
+            all += wave_sum[w];
+        }
+        uint64_t run = carry + before + inc - s;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (k0 + q < nblocks) base[k0 + q] = run;
+            run += c[q];
+        }
+        carry += all;
+        __syncthreads();   // the next round rewrites the wavefronts' sums
     }
-    total[0] = acc;
+    if (threadIdx.x == 0) total[0] = carry;
 }
 
 __global__ __launch_bounds__(256) void sample_write_kernel(const float *depth, const float4 *feat,
@@ -358,7 +458,7 @@ tsdf_status tsdf_mlp_forward(const void *params_dev, const float *x_dev, int64_t
 uint64_t tsdf_mlp_workspace_bytes(int64_t batch)
 {
     if (batch <= 0) return 0;
-    return (uint64_t)((batch + 64 * kTrainWaves - 1) / (64 * kTrainWaves)) * kMlpParamsPadded * sizeof(float);
+    return (uint64_t)((batch + kTrainSamples - 1) / kTrainSamples) * kMlpParamsPadded * sizeof(float);
 }
 
 tsdf_status tsdf_mlp_loss_grad(const void *params_dev, const float *x_dev, const float *r_dev, int64_t n_samples,
@@ -369,11 +469,13 @@ tsdf_status tsdf_mlp_loss_grad(const void *params_dev, const float *x_dev, const
         return TSDF_EINVAL;
     if (perm_a == 0 || perm_a >= (uint64_t)n_samples || perm_b >= (uint64_t)n_samples || n_samples > (1ll << 31))
         return TSDF_EINVAL;
-    const int n_wg = (int)((batch + 64 * kTrainWaves - 1) / (64 * kTrainWaves));
+    const int n_wg = (int)((batch + kTrainSamples - 1) / kTrainSamples);
+    const uint64_t n_inv = ~0ull / (uint64_t)n_samples;
     hipLaunchKernelGGL(train_kernel, dim3(n_wg), dim3(64 * kTrainWaves), 0, stream, (const uint16_t *)params_dev,
-                       (const float4 *)x_dev, r_dev, n_samples, first, batch, perm_a, perm_b, (float *)workspace_dev);
+                       (const float4 *)x_dev, r_dev, n_samples, n_inv, first, batch, perm_a, perm_b,
+                       (float *)workspace_dev);
     if (hipGetLastError() != hipSuccess) return TSDF_EHIP;
-    hipLaunchKernelGGL(reduce_kernel, dim3((kMlpParams + 1 + 255) / 256), dim3(256), 0, stream,
+    hipLaunchKernelGGL(reduce_kernel, dim3((kMlpParams + 1 + 63) / 64), dim3(64 * kReduceWaves), 0, stream,
                        (const float *)workspace_dev, n_wg, batch, grad_dev, loss_dev);
     return hipGetLastError() == hipSuccess ? TSDF_OK : TSDF_EHIP;
 }
@@ -420,7 +522,7 @@ tsdf_status tsdf_mlp_collect_samples(const float *depth_dev, const float *feat_d
     uint64_t *base = (uint64_t *)((uint8_t *)workspace_dev + (((uint64_t)nb * 4 + 7) & ~7ull));
     hipLaunchKernelGGL(sample_count_kernel, dim3(nb), dim3(256), 0, stream, depth_dev, (const float4 *)feat_dev,
                        valid_dev, (const float4 *)vertex_dev, cam, n, counts);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(64), 0, stream, counts, nb, base, count_dev);
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, stream, (const uint32_t *)counts, nb, base, count_dev);
     hipLaunchKernelGGL(sample_write_kernel, dim3(nb), dim3(256), 0, stream, depth_dev, (const float4 *)feat_dev,
                        valid_dev, (const float4 *)vertex_dev, cam, n, (const uint64_t *)base, cap,
                        (float4 *)x_out_dev, r_out_dev);

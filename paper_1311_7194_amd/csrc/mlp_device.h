@@ -73,82 +73,15 @@ __device__ __forceinline__ void mlp_stage_params(MlpParamsLds &s, const uint16_t
     }
 }
 
-// Per-wavefront LDS scratch for the layer-2 operands and the output reduction.
-struct MlpWaveLds {
-    uint16_t h1[64][kMlpHidden + 4];   // bf16 layer-1 activations per sample (padded rows)
-    float t3[64][kMlpHidden + 1];      // per (sample, hidden unit) output-layer terms
-};
-
-// Layer 2 for the 64 samples of a wavefront on the matrix cores:
-// acc[tile] = h1[32 tile rows][32] x W2^T[32][32] (bf16 in, fp32 out), two
-// K = 16 steps per tile.
-__device__ __forceinline__ void mlp_layer2_mfma(const MlpWaveLds &w, const uint16_t *__restrict__ W2bits, int lane,
-                                                f32x16_t acc[2])
-{
-    const int col = lane & 31, kh = 8 * (lane >> 5);
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        f32x16_t c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < kMlpHidden / 16; ++kk) {
-            i16x8_t a, b;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                a[e] = (short)w.h1[32 * t + col][16 * kk + kh + e];
-                // B[k][n] = W2[n][k]: output unit n = col, input k
-                b[e] = (short)W2bits[col * kMlpHidden + 16 * kk + kh + e];
-            }
-            c = mfma_bf16_k16(a, b, c);
-        }
-        acc[t] = c;
-    }
-}
-
-// Forward pass of the 64 samples held by one wavefront (one sample per lane;
-// x are the raw features).  P: parameters (LDS floats), W2bits: W2 as bf16
-// bits.  Returns log sigma^2 for the lane's sample; when a2out is non-null
-// the layer-2 pre-activations are kept in the accumulator layout (for the
-// backward pass).  Every thread of the workgroup must call it (it holds
-// workgroup barriers).
-
-__device__ __forceinline__ float mlp_forward_wave(const MlpParamsLds &P, const uint16_t *__restrict__ W2bits,
-                                                  MlpWaveLds &w, const float x[4], int lane, float a2out[2][16])
-{
-    const float x0[4] = {bf16_round(x[0]), bf16_round(x[1]), bf16_round(x[2]), bf16_round(x[3])};
-#pragma unroll
-    for (int o = 0; o < kMlpHidden; ++o) {
-        float a = P.p[MLP_B1 + o];
-#pragma unroll
-        for (int i = 0; i < kMlpIn; ++i) a += P.p[MLP_W1 + o * kMlpIn + i] * x0[i];
-        w.h1[lane][o] = bf16_bits(silu(a));
-    }
-    __syncthreads();
-    f32x16_t acc[2];
-    mlp_layer2_mfma(w, W2bits, lane, acc);
-    const int col = lane & 31;
-    const float b2 = P.p[MLP_B2 + col], w3 = P.p[MLP_W3 + col];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 32 * t + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            const float a2 = acc[t][r] + b2;
-            if (a2out) a2out[t][r] = a2;
-            w.t3[row][col] = w3 * bf16_round(silu(a2));
-        }
-    __syncthreads();
-    float s = P.p[MLP_B3];
-#pragma unroll
-    for (int o = 0; o < kMlpHidden; ++o) s += w.t3[lane][o];
-    return s;
-}
-
-// Inference-only forward pass with a small LDS footprint (the integration
+// Forward pass of the 64 samples held by one wavefront (one sample per lane; x
+// are the raw features) with a small LDS footprint (the integration
 // path runs it in every preparation workgroup, where LDS bounds occupancy):
 // one bf16 activation tile per wavefront holds h1 for layer 2, then h2 for
 // the output layer, which also runs on the matrix cores (W3 as the only
-// non-zero column of B).  Same rounding points as mlp_forward_wave; only the
-// order of the output layer's FP32 sum differs.
+// non-zero column of B).  Returns log sigma^2 for the lane's sample.  Every
+// thread of the workgroup must call it (it holds workgroup barriers).  Training
+// (mlp.hip) rounds at the same points; only the order of the output layer's
+// FP32 sum differs.
 struct MlpInferLds {
     uint16_t h[64][kMlpHidden + 4];   // bf16 activations, one sample per row
     float out[64];
