@@ -5,10 +5,10 @@
 //                     projective match into the model maps, rejection, and
 //                     per-thread sums of the unscaled normal equations and the
 //                     box of the kept points; workgroups write partial sums
-//   icp_solve_kernel  one workgroup: adds the partials, forms the scaled
-//                     system from the unscaled sums, eigen-decomposes it,
-//                     keeps the directions above the threshold, and composes
-//                     the pose
+//   icp_solve_kernel  one workgroup adds the partials; its first wavefront
+//                     forms the scaled system from the unscaled sums, eigen-
+//                     decomposes it, keeps the directions above the threshold,
+//                     and composes the pose, one matrix entry per lane
 //
 // Every step of the matching is evaluated in double precision without
 // contractions, in a fixed operation order, so that which pixel a point
@@ -129,10 +129,23 @@ __global__ __launch_bounds__(kIcpThreads) void icp_pairs_kernel(const float *__r
     double v[32], bx[8];
     init_acc(v, bx);
     const uint32_t npix = (uint32_t)W * (uint32_t)H;   // at most 16384^2 < 2^32
-    for (uint32_t pix = blockIdx.x * kIcpThreads + threadIdx.x; pix < npix; pix += gridDim.x * kIcpThreads) {
+    const uint32_t stride = gridDim.x * kIcpThreads;
+    const uint32_t first = blockIdx.x * kIcpThreads + threadIdx.x;
+    // the next pixel's depths are loaded while a pixel waits for its model
+    // vertex (indices clamped into the map: what lies past it is not used)
+    auto load = [&](uint32_t pix, float d[3]) {
+        const uint32_t last = npix - 1u;
+        d[0] = depth[min(pix, last)];
+        d[1] = depth[min(pix + 1u, last)];
+        d[2] = depth[min(pix + (uint32_t)W, last)];
+    };
+    float next[3];
+    load(first, next);
+    for (uint32_t pix = first; pix < npix; pix += stride) {
+        const float d0 = next[0], dr = next[1], dd = next[2];
+        load(pix + stride, next);
         const int j = (int)(pix / (uint32_t)W), i = (int)(pix - (uint32_t)j * (uint32_t)W);
         if (i + 1 >= W || j + 1 >= H) continue;
-        const float d0 = depth[pix], dr = depth[pix + 1], dd = depth[pix + W];
         if (!(depth_ok(d0) && depth_ok(dr) && depth_ok(dd))) continue;
         // live point and its neighbours through the pixel centres, camera frame
         const double ui = ((double)i - a.cx) / a.fx, ui1 = ((double)(i + 1) - a.cx) / a.fx;
@@ -158,9 +171,8 @@ __global__ __launch_bounds__(kIcpThreads) void icp_pairs_kernel(const float *__r
         const double fu = floor(a.fx * xm / zm + a.cx + 0.5), fv = floor(a.fy * ym / zm + a.cy + 0.5);
         if (!(fu >= 0.0 && fu < (double)W && fv >= 0.0 && fv < (double)H)) continue;
         const long long m = (long long)fv * W + (long long)fu;
-        const float4 V = mvert[m];
+        const float4 V = mvert[m], N = mnorm[m];   // in flight together
         if (!(V.w > 0.0f)) continue;
-        const float4 N = mnorm[m];
         const double q[3] = {V.x, V.y, V.z}, n[3] = {N.x, N.y, N.z};
         // rejection: distance, then normal deviation
         const double dq[3] = {p[0] - q[0], p[1] - q[1], p[2] - q[2]};
@@ -192,57 +204,83 @@ __global__ __launch_bounds__(kIcpThreads) void icp_pairs_kernel(const float *__r
     if (threadIdx.x < kPartial) partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = L.tot[threadIdx.x];
 }
 
-// Parallel cyclic Jacobi for a symmetric 6x6 matrix on one wavefront.  Lane
-// l < 36 holds element (l / 6, l % 6) of A and of the eigenvector matrix V.
-// A sweep is five rounds of three disjoint plane rotations: in round k the
-// index x5 = 3k mod 5 pairs with 5 and the others as (x5 + 1, x5 + 4) and
-// (x5 + 2, x5 + 3) mod 5 (indices x, y < 5 pair when x + y = k mod 5), which
-// covers all 15 pairs.  Disjoint rotations commute and do not touch each
-// other's 2x2 blocks, so a round applies its three at once: A <- J^T A J,
-// V <- V J.  The pivots are read out of their lanes as wave-uniform values
-// and every lane computes the three rotations itself.
-__device__ __forceinline__ double lane_value(double x, int lane)
+// Orders a wavefront's LDS accesses (data passed between its lanes).
+__device__ __forceinline__ void wave_sync()
 {
-    const unsigned long long u = __double_as_longlong(x);
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
-    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Reciprocal and reciprocal square root to about an ulp: the hardware
-// estimate and two Newton steps.  The rotations only have to (nearly) zero
-// their pivot and stay orthogonal, which c = 1/sqrt(1 + t^2), s = t c does
-// to rounding whatever the accuracy of t.
-__device__ __forceinline__ double fast_rcp(double x)
+// Plane rotation that zeroes apq: t = tan of its angle from the tangent formula
+// in single precision and one Newton step of t^2 + 2 th t - 1 = 0 (to about
+// 1e-14), c = 1/sqrt(1 + t^2) and s = t c to rounding, so that it is orthogonal
+// whatever the accuracy of t.  The chain of FP64 latencies is what a sweep
+// costs; most of this one runs in FP32.
+__device__ __forceinline__ void plane_rotation(double app, double aqq, double apq, double &c, double &s, double &t)
 {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-
-__device__ __forceinline__ double fast_rsqrt(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * fma(-0.5 * x * y, y, 1.5);
-    return y * fma(-0.5 * x * y, y, 1.5);
-}
-
-__device__ __forceinline__ void plane_rotation(double app, double aqq, double apq, double &c, double &s)
-{
-    if (apq == 0.0) {
-        c = 1.0;
-        s = 0.0;
-        return;
-    }
-    const double th = 0.5 * (aqq - app) * fast_rcp(apq);
-    const double at = fabs(th);
-    // t = sign(th) / (|th| + sqrt(th^2 + 1)), with sqrt(h) = h / sqrt(h);
-    // beyond |th| = 1e100 (where th^2 would overflow) t = 1 / (2 |th|) to rounding
-    const double h = at < 1e100 ? fma(at, at, 1.0) : 1.0;
-    const double den = at < 1e100 ? at + h * fast_rsqrt(h) : 2.0 * at;
-    const double t = (th >= 0.0 ? 1.0 : -1.0) * fast_rcp(den);
-    c = fast_rsqrt(fma(t, t, 1.0));
+    double q = __builtin_amdgcn_rcp(apq);
+    q = fma(q, fma(-apq, q, 1.0), q);
+    q = fma(q, fma(-apq, q, 1.0), q);
+    // th = (aqq - app) / (2 apq), t = sign(th) / (|th| + sqrt(th^2 + 1)); beyond
+    // 1e15 the rotation is the identity to rounding
+    const double th = 0.5 * (aqq - app) * q;
+    const float tf = (float)th, at = fabsf(tf);
+    const float t0 = copysignf(__builtin_amdgcn_rcpf(at + __builtin_amdgcn_sqrtf(fmaf(at, at, 1.0f))), tf);
+    t = (double)t0;
+    t = fma(-fma(t, fma(2.0, th, t), -1.0), (double)(0.5f * __builtin_amdgcn_rcpf(t0 + tf)), t);
+    if (!(fabs(th) < 1e15) || apq == 0.0) t = 0.0;   // (also an undefined th)
+    const double x = fma(t, t, 1.0);
+    const double y = (double)__builtin_amdgcn_rsqf((float)x);
+    const double e = fma(-x * y, y, 1.0);            // 1 - x y^2, about 1e-7
+    c = fma(y * e, fma(0.375, e, 0.5), y);           // to e^3
     s = t * c;
+}
+
+// Cyclic Jacobi for a symmetric 6x6 matrix on one wavefront.  Every lane holds
+// the whole matrix (its upper triangle) and lane r < 6 row r of the
+// eigenvector matrix V: nothing is exchanged between lanes.  A sweep is five
+// rounds of three disjoint plane rotations: in round k the index x5 = 3k mod 5
+// pairs with 5 and the others as (x5 + 1, x5 + 4) and (x5 + 2, x5 + 3) mod 5,
+// which covers all 15 pairs.  Disjoint rotations commute and do not touch each
+// other's 2x2 blocks, so their chains overlap: A <- J^T A J, V <- V J.
+struct Sym6 {
+    double a[6][6];   // upper triangle (fully unrolled: registers)
+    __device__ __forceinline__ double &operator()(int r, int c) { return r <= c ? a[r][c] : a[c][r]; }
+};
+
+template <int kRound>
+__device__ __forceinline__ void jacobi_round(Sym6 &A, double v[6])
+{
+    constexpr int x5 = (3 * kRound) % 5;
+    constexpr int P[3] = {x5, (x5 + 1) % 5 < (x5 + 4) % 5 ? (x5 + 1) % 5 : (x5 + 4) % 5,
+                          (x5 + 2) % 5 < (x5 + 3) % 5 ? (x5 + 2) % 5 : (x5 + 3) % 5};
+    constexpr int Q[3] = {5, (x5 + 1) % 5 < (x5 + 4) % 5 ? (x5 + 4) % 5 : (x5 + 1) % 5,
+                          (x5 + 2) % 5 < (x5 + 3) % 5 ? (x5 + 3) % 5 : (x5 + 2) % 5};
+    double c[3], s[3], t[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) plane_rotation(A(P[i], P[i]), A(Q[i], Q[i]), A(P[i], Q[i]), c[i], s[i], t[i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int p = P[i], q = Q[i];
+        A(p, p) = fma(-t[i], A(p, q), A(p, p));
+        A(q, q) = fma(t[i], A(p, q), A(q, q));
+        if (t[i] != 0.0) A(p, q) = 0.0;
+#pragma unroll
+        for (int k = i + 1; k < 3; ++k) {   // the block against another pair
+            const int f = P[k], g = Q[k];
+            const double pf = A(p, f), pg = A(p, g), qf = A(q, f), qg = A(q, g);
+            const double rpf = c[i] * pf - s[i] * qf, rpg = c[i] * pg - s[i] * qg;
+            const double rqf = s[i] * pf + c[i] * qf, rqg = s[i] * pg + c[i] * qg;
+            A(p, f) = c[k] * rpf - s[k] * rpg;
+            A(p, g) = s[k] * rpf + c[k] * rpg;
+            A(q, f) = c[k] * rqf - s[k] * rqg;
+            A(q, g) = s[k] * rqf + c[k] * rqg;
+        }
+        const double vp = v[p], vq = v[q];
+        v[p] = c[i] * vp - s[i] * vq;
+        v[q] = s[i] * vp + c[i] * vq;
+    }
 }
 
 // Called by the 64 lanes of one wavefront; sA and sV0 (read) and sV, sLam
@@ -251,266 +289,262 @@ __device__ __forceinline__ void plane_rotation(double app, double aqq, double ap
 // eigenvectors come out for A itself.
 __device__ void jacobi6_wave(const double *sA, const double *sV0, double *sV, double *sLam)
 {
-    const int lane = threadIdx.x & 63;
-    const bool own = lane < 36;
-    const int r = own ? lane / 6 : 0, c = own ? lane % 6 : 0;
-    double a = own ? sA[lane] : 0.0;
-    double v = own ? (sV0 ? sV0[lane] : (r == c ? 1.0 : 0.0)) : 0.0;
+    const int lane = threadIdx.x & 63, r = lane < 6 ? lane : 0;
+    Sym6 A;
+    double v[6];
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+#pragma unroll
+        for (int q = p; q < 6; ++q) A(p, q) = sA[6 * p + q];
+        v[p] = sV0 ? sV0[6 * r + p] : (p == r ? 1.0 : 0.0);
+    }
     for (int sweep = 0; sweep < 64; ++sweep) {
         double off = 0.0, diag = 0.0;
-        for (int p = 0; p < 6; ++p) {
-            const double d = lane_value(a, 7 * p);
-            diag += d * d;
-            for (int q = p + 1; q < 6; ++q) {
-                const double o = lane_value(a, 6 * p + q);
-                off += o * o;
-            }
-        }
-        if (!(off > 1e-26 * diag)) break;   // off-diagonal norm below 1e-13 of the diagonal's
-        for (int k = 0; k < 5; ++k) {
-            const int x5 = (3 * k) % 5;
-            int P[3], Q[3];
-            P[0] = x5;
-            Q[0] = 5;
-            P[1] = min((x5 + 1) % 5, (x5 + 4) % 5);
-            Q[1] = max((x5 + 1) % 5, (x5 + 4) % 5);
-            P[2] = min((x5 + 2) % 5, (x5 + 3) % 5);
-            Q[2] = max((x5 + 2) % 5, (x5 + 3) % 5);
-            double cs[3], sn[3];
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
-                plane_rotation(lane_value(a, 7 * P[i]), lane_value(a, 7 * Q[i]), lane_value(a, 6 * P[i] + Q[i]), cs[i],
-                               sn[i]);
-            // this lane's row and column: pair, partner, and column of J
-            // (J[x][x] = cos, J[partner][x] = -sin for the pair's smaller index, +sin otherwise)
-            const int ir = (r == P[0] || r == Q[0]) ? 0 : ((r == P[1] || r == Q[1]) ? 1 : 2);
-            const int ic = (c == P[0] || c == Q[0]) ? 0 : ((c == P[1] || c == Q[1]) ? 1 : 2);
-            const int pr = ir == 0 ? P[0] : (ir == 1 ? P[1] : P[2]), qr = ir == 0 ? Q[0] : (ir == 1 ? Q[1] : Q[2]);
-            const int pc = ic == 0 ? P[0] : (ic == 1 ? P[1] : P[2]), qc = ic == 0 ? Q[0] : (ic == 1 ? Q[1] : Q[2]);
-            const int r2 = r == pr ? qr : pr, c2 = c == pc ? qc : pc;
-            const double cr = ir == 0 ? cs[0] : (ir == 1 ? cs[1] : cs[2]);
-            const double cc = ic == 0 ? cs[0] : (ic == 1 ? cs[1] : cs[2]);
-            const double snr = ir == 0 ? sn[0] : (ir == 1 ? sn[1] : sn[2]);
-            const double snc = ic == 0 ? sn[0] : (ic == 1 ? sn[1] : sn[2]);
-            const double sr = r == pr ? -snr : snr, sc = c == pc ? -snc : snc;
-            const double a_rc2 = __shfl(a, 6 * r + c2), a_r2c = __shfl(a, 6 * r2 + c), a_r2c2 = __shfl(a, 6 * r2 + c2);
-            const double v_rc2 = __shfl(v, 6 * r + c2);
-            const double an = (cr * cc * a + cr * sc * a_rc2) + (sr * cc * a_r2c + sr * sc * a_r2c2);
-            a = c == r2 ? 0.0 : an;   // the rotated pair's off-diagonal entries
-            v = v * cc + v_rc2 * sc;
+        for (int p = 0; p < 6; ++p) {
+            diag = fma(A(p, p), A(p, p), diag);
+#pragma unroll
+            for (int q = p + 1; q < 6; ++q) off = fma(A(p, q), A(p, q), off);
+        }
+        // off-diagonal norm below 1e-13 of the diagonal's (the same in every lane)
+        if (!(__builtin_amdgcn_readfirstlane(off > 1e-26 * diag))) break;
+        jacobi_round<0>(A, v);
+        jacobi_round<1>(A, v);
+        jacobi_round<2>(A, v);
+        jacobi_round<3>(A, v);
+        jacobi_round<4>(A, v);
+    }
+    if (lane < 6) {
+#pragma unroll
+        for (int p = 0; p < 6; ++p) {
+            sV[6 * lane + p] = v[p];
+            if (p == lane) sLam[p] = A(p, p);
         }
     }
-    if (own) {
-        sV[lane] = v;
-        if (r == c) sLam[r] = a;
-    }
+    wave_sync();
 }
 
-// The system solved in this iteration (scaled when shrink is set).
-struct IcpSystem {
-    double A[36], b[6], m[3], S[3];
-    double N, e2;
+// Scratch of the solve kernel.
+struct SolveLds {
+    double tot[kPartial];           // the reduced sums and maxima
+    double A[36], b[6];             // the system solved (scaled when shrink is set)
+    double V0[36], B[36];           // warm start: previous eigenvectors, V0^T A V0
+    double V[36], lam[6];           // eigenvectors (columns) and eigenvalues
+    double w[6], xh[6];             // coefficients of the kept directions, solution
+    double sc[6];                   // sines and cosines of the increment's angles
+    double P[12];                   // the current pose
 };
 
-// From the reduced sums: the unscaled blocks Acc = sum c c^T, Acn = sum c n^T,
-// Ann = sum n n^T and sum g e; with shrink, the scaled system by the change
-// of variables c^ = S^-1 (c - M n), M n = m x n:
-//   S^-1 (Acc - Acn M^T - M Acn^T + M Ann M^T) S^-1,  S^-1 (Acn - M Ann),  Ann,
-//   right-hand side -S^-1 (sum c e - M sum n e), -sum n e.
-__device__ void system_of(const double *v, const IcpArgs &a, IcpSystem &sys)
+// Entry (r, c) of the 6x6 sum g g^T from its upper triangle.
+__device__ __forceinline__ double sum_gg(const double *tot, int r, int c)
 {
-    double A[36];
-    int k = 0;
-    for (int r = 0; r < 6; ++r)
-        for (int c = r; c < 6; ++c) A[6 * r + c] = A[6 * c + r] = v[k++];
-    double b[6];
-    for (int r = 0; r < 6; ++r) b[r] = -v[21 + r];
-    const double N = v[28];
-    double m[3] = {0.0, 0.0, 0.0}, S[3] = {1.0, 1.0, 1.0};
-    if (a.shrink && N > 0.0) {
-        for (int r = 0; r < 3; ++r) {
-            const double lo = -v[32 + r], hi = v[35 + r];
-            m[r] = 0.5 * (lo + hi);
-            const double ext = hi - lo;
-            S[r] = ext > 0.0 ? ext : 1.0;
-        }
-        const double M[9] = {0.0, -m[2], m[1], m[2], 0.0, -m[0], -m[1], m[0], 0.0};
-        double MAnn[9], AcnMt[9];
-        for (int r = 0; r < 3; ++r)
-            for (int c = 0; c < 3; ++c) {
-                double s1 = 0.0, s2 = 0.0;
-                for (int l = 0; l < 3; ++l) {
-                    s1 += M[3 * r + l] * A[6 * (l + 3) + 3 + c];    // M Ann
-                    s2 += A[6 * r + 3 + l] * M[3 * c + l];          // Acn M^T
-                }
-                MAnn[3 * r + c] = s1;
-                AcnMt[3 * r + c] = s2;
-            }
-        double Bcc[9], Bcn[9], bc[3];
-        for (int r = 0; r < 3; ++r)
-            for (int c = 0; c < 3; ++c) {
-                double mam = 0.0;
-                for (int l = 0; l < 3; ++l) mam += MAnn[3 * r + l] * M[3 * c + l];   // M Ann M^T
-                Bcc[3 * r + c] = (A[6 * r + c] - AcnMt[3 * r + c] - AcnMt[3 * c + r] + mam) / (S[r] * S[c]);
-                Bcn[3 * r + c] = (A[6 * r + 3 + c] - MAnn[3 * r + c]) / S[r];
-            }
-        for (int r = 0; r < 3; ++r) {
-            double mb = 0.0;
-            for (int l = 0; l < 3; ++l) mb += M[3 * r + l] * v[24 + l];
-            bc[r] = -(v[21 + r] - mb) / S[r];
-        }
-        for (int r = 0; r < 3; ++r) {
-            b[r] = bc[r];
-            for (int c = 0; c < 3; ++c) {
-                A[6 * r + c] = Bcc[3 * r + c];
-                A[6 * r + 3 + c] = Bcn[3 * r + c];
-                A[6 * (3 + c) + r] = Bcn[3 * r + c];
-            }
-        }
-    }
-    for (int q = 0; q < 36; ++q) sys.A[q] = A[q];
-    for (int q = 0; q < 6; ++q) sys.b[q] = b[q];
-    for (int q = 0; q < 3; ++q) {
-        sys.m[q] = m[q];
-        sys.S[q] = S[q];
-    }
-    sys.N = N;
-    sys.e2 = v[27];
+    const int i = min(r, c), j = max(r, c);
+    return tot[6 * i - i * (i - 1) / 2 + (j - i)];
 }
 
-// Thresholded solution from the eigen-decomposition (V columns, lam), back-
-// substitution, and the pose update; writes the result record.
-__device__ void solve_and_update(const IcpSystem &sys, const double *V, const double *lam_in, const IcpArgs &a,
-                                 const double *pose, tsdf_icp_result *res)
+// Adds up (or takes the maximum of) ten values over the 64 lanes by recursive
+// halving: at each exchange a lane keeps one half of its values and sends the
+// other.  Lane 4 k holds the total of value k.
+template <bool kMax>
+__device__ __forceinline__ double wave_total10(const double v[10])
 {
-    const double N = sys.N;
-    for (int q = 0; q < 36; ++q) res->C[q] = sys.A[q];
-    for (int q = 0; q < 6; ++q) res->b[q] = sys.b[q];
-    for (int q = 0; q < 3; ++q) {
-        res->m[q] = sys.m[q];
-        res->S[q] = sys.S[q];
+    const int lane = threadIdx.x & 63;
+    auto op = [](double x, double y) { return kMax ? fmax(x, y) : x + y; };
+    const double none = kMax ? -INFINITY : 0.0;
+    double h8[8], h4[4], h2[2];
+    const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const double up = k + 8 < 10 ? v[k + 8] : none;
+        h8[k] = op(b5 ? up : v[k], __shfl_xor(b5 ? v[k] : up, 32));
     }
-    res->residual2 = sys.e2;
-    res->pairs = (int64_t)N;
-    double P[12];
-    for (int q = 0; q < 12; ++q) P[q] = pose_at(pose, a, q);
-    double x[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, lam[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int kept = 0;
-    if (N > 0.0) {
-        for (int e = 0; e < 6; ++e) lam[e] = lam_in[e];
-        double xh[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int e = 0; e < 6; ++e) {
-            const bool keep = lam[e] > 0.0 && (a.theta >= 0.0 ? lam[e] / N > a.theta : true);
-            if (!keep) continue;
-            ++kept;
-            double vb = 0.0;
-            for (int r = 0; r < 6; ++r) vb += V[6 * r + e] * sys.b[r];
-            for (int r = 0; r < 6; ++r) xh[r] += V[6 * r + e] * (vb / lam[e]);
-        }
-        // back to the unscaled increment: r = S^-1 r^, t = t^ - r x m
-        const double *S = sys.S, *m = sys.m;
-        const double rr[3] = {xh[0] / S[0], xh[1] / S[1], xh[2] / S[2]};
-        const double rxm[3] = {rr[1] * m[2] - rr[2] * m[1], rr[2] * m[0] - rr[0] * m[2], rr[0] * m[1] - rr[1] * m[0]};
-        for (int q = 0; q < 3; ++q) {
-            x[q] = rr[q];
-            x[3 + q] = xh[3 + q] - rxm[q];
-        }
-        // R_inc = Rz(gamma) Ry(beta) Rx(alpha); pose' = R_inc pose + t_inc
-        double sa, ca, sb, cb, sg, cg;
-        sincos(x[0], &sa, &ca);
-        sincos(x[1], &sb, &cb);
-        sincos(x[2], &sg, &cg);
-        const double Rx[9] = {1.0, 0.0, 0.0, 0.0, ca, -sa, 0.0, sa, ca};
-        const double Ry[9] = {cb, 0.0, sb, 0.0, 1.0, 0.0, -sb, 0.0, cb};
-        const double Rz[9] = {cg, -sg, 0.0, sg, cg, 0.0, 0.0, 0.0, 1.0};
-        double Ryx[9], Ri[9];
-        for (int r = 0; r < 3; ++r)
-            for (int c = 0; c < 3; ++c) {
-                double s = 0.0;
-                for (int l = 0; l < 3; ++l) s += Ry[3 * r + l] * Rx[3 * l + c];
-                Ryx[3 * r + c] = s;
-            }
-        for (int r = 0; r < 3; ++r)
-            for (int c = 0; c < 3; ++c) {
-                double s = 0.0;
-                for (int l = 0; l < 3; ++l) s += Rz[3 * r + l] * Ryx[3 * l + c];
-                Ri[3 * r + c] = s;
-            }
-        double Pn[12];
-        for (int r = 0; r < 3; ++r) {
-            for (int c = 0; c < 4; ++c) {
-                double s = 0.0;
-                for (int l = 0; l < 3; ++l) s += Ri[3 * r + l] * P[4 * l + c];
-                Pn[4 * r + c] = s;
-            }
-            Pn[4 * r + 3] += x[3 + r];
-        }
-        for (int q = 0; q < 12; ++q) P[q] = Pn[q];
-        // eigenvalues per pair, ascending
-        for (int e = 0; e < 6; ++e) lam[e] /= N;
-        for (int e = 1; e < 6; ++e)
-            for (int f = e; f > 0 && lam[f - 1] > lam[f]; --f) {
-                const double t = lam[f];
-                lam[f] = lam[f - 1];
-                lam[f - 1] = t;
-            }
-    }
-    for (int q = 0; q < 12; ++q) res->pose[q] = P[q];
-    for (int q = 0; q < 6; ++q) {
-        res->x[q] = x[q];
-        res->lambda[q] = lam[q];
-    }
-    res->kept = kept;
-    res->pad = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h4[k] = op(b4 ? h8[k + 4] : h8[k], __shfl_xor(b4 ? h8[k] : h8[k + 4], 16));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) h2[k] = op(b3 ? h4[k + 2] : h4[k], __shfl_xor(b3 ? h4[k] : h4[k + 2], 8));
+    double h = op(b2 ? h2[1] : h2[0], __shfl_xor(b2 ? h2[0] : h2[1], 4));
+    h = op(h, __shfl_xor(h, 2));
+    return op(h, __shfl_xor(h, 1));
 }
 
 // warm: start the eigen-decomposition from the previous iteration's
 // eigenvectors (kept in vwork): the system changes little from one iteration
 // to the next, so V^T A V is nearly diagonal and a sweep or two finish it.
+//
+// One workgroup: what it costs is the length of its chain of FP64 operations
+// and LDS round trips.  Each wavefront adds up ten of the sums (the last the
+// maxima); from there on one wavefront works with a lane per matrix entry.  A
+// single thread for the system, the back-substitution and the pose, and an
+// eigen-decomposition that exchanged the matrix between lanes: 14.3 us at
+// 160x120 and 15.9 at 640x480, now 10.1 and 10.7.
 __global__ __launch_bounds__(kIcpThreads) void icp_solve_kernel(const double *__restrict__ partial, int groups,
                                                                 const double *__restrict__ pose, IcpArgs a,
                                                                 tsdf_icp_result *__restrict__ res,
                                                                 double *__restrict__ vwork, int warm)
 {
-    __shared__ ReduceLds L;
-    __shared__ IcpSystem sys;
-    __shared__ double sV[36], sLam[6], sV0[36], sB[36], sA2[36];
-    const int t = threadIdx.x;
-    if (warm && t < 36) sV0[t] = vwork[t];
-    double v[32], bx[8];
-    init_acc(v, bx);
-#pragma unroll 4
-    for (int g = threadIdx.x; g < groups; g += kIcpThreads) {
+    __shared__ SolveLds L;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (wave < 3) {
+        double v[10];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] += partial[(size_t)k * groups + g];
+        for (int k = 0; k < 10; ++k) v[k] = 0.0;
+#pragma unroll 2
+        for (int g = lane; g < groups; g += 64)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) bx[k] = fmax(bx[k], partial[(size_t)(32 + k) * groups + g]);
+            for (int k = 0; k < 10; ++k) v[k] += partial[(size_t)(10 * wave + k) * groups + g];
+        const double s = wave_total10<false>(v);
+        if (!(lane & 3) && lane < 40) L.tot[10 * wave + (lane >> 2)] = s;
+    } else {
+        if (warm && lane < 36) L.V0[lane] = vwork[lane];
+        double v[10];
+#pragma unroll
+        for (int k = 0; k < 10; ++k) v[k] = -INFINITY;
+#pragma unroll 2
+        for (int g = lane; g < groups; g += 64)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[k] = fmax(v[k], partial[(size_t)(32 + k) * groups + g]);
+        const double s = wave_total10<true>(v);
+        if (!(lane & 3) && lane < 24) L.tot[32 + (lane >> 2)] = s;
     }
-    block_reduce(v, bx, L);
-    if (t == 0) system_of(L.tot, a, sys);
+    const double pose_mine = wave == 0 && lane < 12 ? pose_at(pose, a, lane) : 0.0;
     __syncthreads();
-    const bool use_warm = warm && sys.N > 0.0;
-    if (use_warm) {   // sB = (V0^T A V0), symmetrised
-        const int r = t / 6, c = t % 6;
-        if (t < 36) {
-            double s = 0.0;
-            for (int l = 0; l < 6; ++l) s += sys.A[6 * r + l] * sV0[6 * l + c];
-            sB[t] = s;
+    if (wave) return;
+
+    // The scaled system by the change of variables c^ = S^-1 (c - M n), M n =
+    // m x n: row r of the transform of (c, n) is D_r (e_r - sum_l M_rl e_3+l),
+    // D = (S^-1, 1), so an entry of T A T^T is a sum of nine.
+    const double N = L.tot[28];
+    double m[3] = {0.0, 0.0, 0.0}, S[3] = {1.0, 1.0, 1.0};
+    const bool scaled = a.shrink && N > 0.0;
+    if (scaled) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const double lo = -L.tot[32 + q], hi = L.tot[35 + q];
+            m[q] = 0.5 * (lo + hi);
+            const double ext = hi - lo;
+            S[q] = ext > 0.0 ? ext : 1.0;
         }
-        __syncthreads();
-        if (t < 36) {
-            double s = 0.0;
-            for (int k = 0; k < 6; ++k) s += sV0[6 * k + r] * sB[6 * k + c];
-            sA2[t] = s;
-        }
-        __syncthreads();
-        if (t < 36) sB[t] = 0.5 * (sA2[t] + sA2[6 * c + r]);
-        __syncthreads();
     }
-    if (t < 64 && sys.N > 0.0) jacobi6_wave(use_warm ? sB : sys.A, use_warm ? sV0 : nullptr, sV, sLam);
-    __syncthreads();
-    if (t < 36) vwork[t] = sys.N > 0.0 ? sV[t] : (t % 7 == 0 ? 1.0 : 0.0);
-    if (t == 0) solve_and_update(sys, sV, sLam, a, pose, res);
+    const bool own = lane < 36;
+    const int r = own ? lane / 6 : (lane - 36) % 6, c = own ? lane % 6 : 0;   // lanes 36..41: the right-hand side
+    auto at3 = [](const double x[3], int q) { return q == 0 ? x[0] : q == 1 ? x[1] : x[2]; };
+    auto row = [&](int q, int idx[3], double w[3]) {   // the transform's row q, unscaled
+        const int q1 = (q + 1) % 3, q2 = (q + 2) % 3;
+        idx[0] = q;
+        idx[1] = 3 + q1;
+        idx[2] = 3 + q2;
+        w[0] = 1.0;
+        w[1] = q < 3 ? at3(m, q2) : 0.0;
+        w[2] = q < 3 ? -at3(m, q1) : 0.0;
+    };
+    int ri[3], ci[3];
+    double rw[3], cw[3];
+    row(r, ri, rw);
+    row(c, ci, cw);
+    const double Sr = r < 3 ? at3(S, r) : 1.0, Sc = c < 3 ? at3(S, c) : 1.0;
+    double A = 0.0, b = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        double x = 0.0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x += cw[j] * sum_gg(L.tot, ri[i], ci[j]);
+        A += rw[i] * x;
+        b += rw[i] * L.tot[21 + ri[i]];
+    }
+    A /= Sr * Sc;
+    b = -b / Sr;
+    if (own) L.A[lane] = A;
+    else if (lane < 42) L.b[lane - 36] = b;
+    wave_sync();
+    // (r, c) and (c, r) are the same sum in another order
+    if (own) A = 0.5 * (A + L.A[6 * c + r]);
+    wave_sync();
+    if (own) L.A[lane] = A;
+    wave_sync();
+    const bool use_warm = warm && N > 0.0;
+    if (use_warm) {   // B = V0^T A V0, symmetrised
+        double x = 0.0;
+        for (int l = 0; l < 6; ++l) x += L.A[6 * r + l] * L.V0[6 * l + c];
+        if (own) L.V[lane] = x;
+        wave_sync();
+        x = 0.0;
+        for (int k = 0; k < 6; ++k) x += L.V0[6 * k + r] * L.V[6 * k + c];
+        if (own) L.B[lane] = x;
+        wave_sync();
+        x = 0.5 * (x + L.B[6 * c + r]);
+        wave_sync();
+        if (own) L.B[lane] = x;
+        wave_sync();
+    }
+    if (N > 0.0) jacobi6_wave(use_warm ? L.B : L.A, use_warm ? L.V0 : nullptr, L.V, L.lam);
+    if (own) vwork[lane] = N > 0.0 ? L.V[lane] : (r == c ? 1.0 : 0.0);
+
+    // the directions above the threshold: lane e < 6 has eigenvalue e
+    const int e = lane < 6 ? lane : 0;
+    const double lam = N > 0.0 ? L.lam[e] : 0.0;
+    const bool keep = lane < 6 && N > 0.0 && lam > 0.0 && (a.theta >= 0.0 ? lam / N > a.theta : true);
+    const int kept = __popcll(__ballot(keep));
+    if (lane < 6) {
+        double vb = 0.0;
+        for (int q = 0; q < 6; ++q) vb += L.V[6 * q + e] * L.b[q];
+        L.w[e] = keep ? vb / lam : 0.0;
+    }
+    wave_sync();
+    if (lane < 6) {
+        double x = 0.0;
+        for (int q = 0; q < 6; ++q)
+            if (L.w[q] != 0.0) x += L.V[6 * e + q] * L.w[q];
+        L.xh[e] = x;
+    }
+    wave_sync();
+    // back to the unscaled increment: r = S^-1 r^, t = t^ - r x m
+    double x[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (N > 0.0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[q] = L.xh[q] / S[q];
+        x[3] = L.xh[3] - (x[1] * m[2] - x[2] * m[1]);
+        x[4] = L.xh[4] - (x[2] * m[0] - x[0] * m[2]);
+        x[5] = L.xh[5] - (x[0] * m[1] - x[1] * m[0]);
+    }
+    // R_inc = Rz(gamma) Ry(beta) Rx(alpha); pose' = R_inc pose + t_inc
+    if (lane < 3) sincos(at3(x, lane), &L.sc[lane], &L.sc[3 + lane]);
+    if (lane < 12) L.P[lane] = pose_mine;
+    wave_sync();
+    if (lane < 12) {
+        const int pr = lane >> 2, pc = lane & 3;
+        double P = pose_mine;
+        if (N > 0.0) {
+            const double sa = L.sc[0], sb = L.sc[1], sg = L.sc[2], ca = L.sc[3], cb = L.sc[4], cg = L.sc[5];
+            const double y0 = pr == 0 ? cg * cb : pr == 1 ? sg * cb : -sb;
+            const double y1 = pr == 0 ? cg * (sb * sa) - sg * ca : pr == 1 ? sg * (sb * sa) + cg * ca : cb * sa;
+            const double y2 = pr == 0 ? cg * (sb * ca) + sg * sa : pr == 1 ? sg * (sb * ca) - cg * sa : cb * ca;
+            P = y0 * L.P[pc] + y1 * L.P[4 + pc] + y2 * L.P[8 + pc];
+            if (pc == 3) P += at3(x + 3, pr);
+        }
+        res->pose[lane] = P;   // (may be the current pose's own record: read before)
+    }
+    // eigenvalues per pair, ascending
+    if (lane < 6) {
+        int rank = 0;
+        for (int q = 0; q < 6; ++q) {
+            const double o = N > 0.0 ? L.lam[q] : 0.0;
+            rank += o < lam || (o == lam && q < lane);
+        }
+        res->lambda[rank] = N > 0.0 ? lam / N : 0.0;
+        res->b[lane] = L.b[lane];
+        res->x[lane] = lane < 3 ? at3(x, lane) : at3(x + 3, lane - 3);
+    }
+    if (lane < 3) {
+        res->m[lane] = at3(m, lane);
+        res->S[lane] = at3(S, lane);
+    }
+    if (own) res->C[lane] = A;
+    if (lane == 0) {
+        res->residual2 = L.tot[27];
+        res->pairs = (int64_t)N;
+        res->kept = kept;
+        res->pad = 0;
+    }
 }
 
 int icp_groups(int32_t width, int32_t height)
