@@ -223,22 +223,29 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
 // (grid z) the camera coordinates advance by R^T (0, 0, voxel): the decisions
 // start from the exact coordinates of the column's first voxel plus z times
 // that step, which differs from the defined double expression by at most
-// `err` metres; the decisions below are taken only where that difference
-// cannot change them, otherwise the defined expression is evaluated.
+// `err` metres.  The pixel index is taken from them in single precision; where
+// the image point lies within `eu`, `ev` of a pixel boundary, or the depth
+// below `zmin`, and for |s| within `thr_s` of delta, the defined expression
+// decides.
 struct FuseCam {
-    double sx, sy, sz;   // camera-frame step per voxel along grid z
-    double err;          // bound on |approximate - defined| camera coordinate
-    double ceu, cev;     // pixel margin: r * ce + cr, r = 1 / z_c
-    double cru, crv;
+    double sz;           // camera-depth step per voxel along grid z
     double thr_s;        // |s| within thr_s of delta: decided by the defined expression
+    float dX, dY, dZ;    // steps of fx x_c, fy y_c, z_c
+    float cxh, cyh;      // cx + 1/2, cy + 1/2
+    float zmin;          // smallest depth that single precision decides
+    float hu, hv;        // 1/2 - eu, 1/2 - ev
 };
 
 __host__ __device__ inline FuseCam make_fuse_cam(const VolumeView &v, const Camera &cam)
 {
     FuseCam f;
-    f.sx = cam.R[6] * v.vs;
-    f.sy = cam.R[7] * v.vs;
+    const double sx = cam.R[6] * v.vs, sy = cam.R[7] * v.vs;
     f.sz = cam.R[8] * v.vs;
+    f.dX = (float)(cam.fx * sx);
+    f.dY = (float)(cam.fy * sy);
+    f.dZ = (float)f.sz;
+    f.cxh = (float)(cam.cx + 0.5);
+    f.cyh = (float)(cam.cy + 0.5);
     // magnitude bound of every intermediate (positions, differences, camera coordinates)
     double m = 0.0, mt = 0.0;
     for (int a = 0; a < 3; ++a) {
@@ -247,34 +254,42 @@ __host__ __device__ inline FuseCam make_fuse_cam(const VolumeView &v, const Came
     }
     const double M = 3.0 * (m + mt) + 1.0;
     const double ulp = 1.1102230246251565e-16;   // 2^-53
-    f.err = 192.0 * ulp * M;
-    // |u~ - u| <= (fx + |a_u|) err / z_c + rounding, with |a_u| <= W + 2 + |c_x|
-    // wherever the decision can be near a pixel boundary inside the image
-    const double au = cam.width + 2.0 + fabs(cam.cx), av = cam.height + 2.0 + fabs(cam.cy);
-    f.ceu = 2.0 * f.err * (cam.fx + au);
-    f.cev = 2.0 * f.err * (cam.fy + av);
-    f.cru = 64.0 * ulp * au + 1e-300;
-    f.crv = 64.0 * ulp * av + 1e-300;
-    f.thr_s = 4.0 * f.err + 64.0 * ulp * M;
+    const double err = 192.0 * ulp * M;
+    f.thr_s = 4.0 * err + 64.0 * ulp * M;
+    // Pixel margin, e = 2^-24.  X = fx x_c as a float column start plus z dX is
+    // off by e (2 |X| + 14 |dX|), Z by e (2 Z + 14 vs), the hardware reciprocal
+    // by 2 e.  With Z >= 64 vs (and a float's rounding of that) the image point
+    // w = X / Z is off by e (2 + 4 + 1) |w| + e fx / 4, and adding cx + 1/2 by
+    // e (|u| + |cx| + 1); |w| <= max(|cx|, |W - cx|) + 2 and |u| <= W + 2
+    // wherever the decision can be near a pixel boundary inside the image.  A
+    // quarter more than the sum, and `err` against the defined expression.
+    const double e = 5.9604644775390625e-08;
+    const double zmin = fmax(64.0 * v.vs, 1e-30);
+    f.zmin = (float)(zmin * (1.0 + 8.0 * e));
+    const double wu = fmax(fabs(cam.cx), fabs(cam.width - cam.cx)) + 2.0;
+    const double wv = fmax(fabs(cam.cy), fabs(cam.height - cam.cy)) + 2.0;
+    const double eu = 1.25 * e * (7.0 * wu + 0.25 * cam.fx + cam.width + fabs(cam.cx) + 4.0) +
+                      2.0 * err * (cam.fx + wu) / zmin;
+    const double ev = 1.25 * e * (7.0 * wv + 0.25 * cam.fy + cam.height + fabs(cam.cy) + 4.0) +
+                      2.0 * err * (cam.fy + wv) / zmin;
+    // (negative: everything is decided by the defined expression; rounded down)
+    f.hu = (float)((0.5 - eu) - 1e-7);
+    f.hv = (float)((0.5 - ev) - 1e-7);
     return f;
 }
 
-// Nearest-pixel index from approximate camera coordinates (within fc.err of
-// the defined ones): the linear pixel index, -1 outside the image or behind
-// the camera, -2 when only the defined expression can decide.
-__device__ __forceinline__ int pixel_filter(const Camera &cam, const FuseCam &fc, double xc, double yc, double zc)
+// Nearest-pixel index from single-precision X = fx x_c, Y = fy y_c and Z = z_c:
+// the linear pixel index, -1 outside the image; `sure` is cleared where only
+// the defined expression can decide.
+__device__ __forceinline__ int pixel_filter(int width, int height, const FuseCam &fc, float X, float Y, float Z,
+                                            bool &sure)
 {
-    if (!(zc > 2.0 * fc.err)) return zc < -2.0 * fc.err ? -1 : -2;
-    double r = __builtin_amdgcn_rcp(zc);
-    r = fma(r, fma(-zc, r, 1.0), r);   // two Newton steps: r = 1/z_c to a few ulp
-    r = fma(r, fma(-zc, r, 1.0), r);
-    const double tu = fma(cam.fx * xc, r, cam.cx + 0.5), tv = fma(cam.fy * yc, r, cam.cy + 0.5);
-    const double fu = floor(tu), fv = floor(tv);
-    const double du = tu - fu, dv = tv - fv;
-    const double eu = fma(r, fc.ceu, fc.cru), ev = fma(r, fc.cev, fc.crv);
-    if (!(du > eu && du < 1.0 - eu && dv > ev && dv < 1.0 - ev)) return -2;
-    if (!(fu >= 0.0 && fu < (double)cam.width && fv >= 0.0 && fv < (double)cam.height)) return -1;
-    return (int)fv * cam.width + (int)fu;
+    const float r = __builtin_amdgcn_rcpf(Z);
+    const float tu = fmaf(X, r, fc.cxh), tv = fmaf(Y, r, fc.cyh);
+    const float fu = floorf(tu), fv = floorf(tv);
+    sure = Z >= fc.zmin && fabsf((tu - fu) - 0.5f) < fc.hu && fabsf((tv - fv) - 0.5f) < fc.hv;
+    const int i = (int)fu, j = (int)fv;   // (saturating far outside the image)
+    return ((uint32_t)i < (uint32_t)width && (uint32_t)j < (uint32_t)height) ? j * width + i : -1;
 }
 
 // The defined double expression: i = floor(fx x_c / z_c + cx + 1/2), same for j.
@@ -411,79 +426,88 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
     // that its latency overlaps them (only this wavefront inserts this key)
     unsigned long long first_entry = 0;
     if (lane == 0) first_entry = v.hash[hash_key(key) & v.hash_mask];
-    // x_c = R^T (x - t) = (R00 dx + R10 dy) + R20 dz: the bracket is the
-    // lane's (x, y) part, the last term varies with z
-    double ax, ay, az;
-    {
+    // the defined camera coordinates of voxel (lx, ly, z) of the block:
+    // x_c = R^T (x - t) = (R00 dx + R10 dy) + R20 dz, the bracket first
+    auto defined = [&](int z, double &xc, double &yc, double &zc) {
 #pragma clang fp contract(off)
         const double px = v.origin[0] + ((double)(bx * 8 + lx) + 0.5) * v.vs;
         const double py = v.origin[1] + ((double)(by * 8 + ly) + 0.5) * v.vs;
+        const double pz = v.origin[2] + ((double)(bz * 8 + z) + 0.5) * v.vs;
         const double dx = px - cam.t[0];
         const double dy = py - cam.t[1];
-        ax = cam.R[0] * dx + cam.R[3] * dy;
-        ay = cam.R[1] * dx + cam.R[4] * dy;
-        az = cam.R[2] * dx + cam.R[5] * dy;
-    }
-    // the defined camera coordinates of the column's first voxel (z = 0)
-    double x0, y0, z0;
-    {
-#pragma clang fp contract(off)
-        const double pz = v.origin[2] + ((double)(bz * 8) + 0.5) * v.vs;
         const double dz = pz - cam.t[2];
-        x0 = ax + cam.R[6] * dz;
-        y0 = ay + cam.R[7] * dz;
-        z0 = az + cam.R[8] * dz;
+        xc = (cam.R[0] * dx + cam.R[3] * dy) + cam.R[6] * dz;
+        yc = (cam.R[1] * dx + cam.R[4] * dy) + cam.R[7] * dz;
+        zc = (cam.R[2] * dx + cam.R[5] * dy) + cam.R[8] * dz;
+    };
+    double z0;
+    float X0, Y0, Z0;
+    {
+        double x0, y0;
+        defined(0, x0, y0, z0);
+        X0 = (float)(cam.fx * x0);
+        Y0 = (float)(cam.fy * y0);
+        Z0 = (float)z0;
     }
+    // phase 1: the pixel decisions of the column in single precision
+    int pix[8];
+    uint32_t unsure = 0;
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        bool sure;
+        pix[z] = pixel_filter(cam.width, cam.height, fc, fmaf((float)z, fc.dX, X0), fmaf((float)z, fc.dY, Y0),
+                              fmaf((float)z, fc.dZ, Z0), sure);
+        unsure |= (sure ? 0u : 1u) << z;
+    }
+    // phase 2 (about one voxel in a thousand): the defined expression decides,
+    // one voxel per lane and round
+    while (__ballot(unsure != 0u)) {
+        if (unsure) {
+            const int k = __builtin_ctz(unsure);
+            unsure &= unsure - 1u;
+            double xc, yc, zc;
+            defined(k, xc, yc, zc);
+            const int p = zc > 0.0 ? pixel_exact(cam.fx, cam.fy, cam.cx, cam.cy, cam.width, cam.height, xc, yc, zc)
+                                   : -1;
+#pragma unroll
+            for (int z = 0; z < 8; ++z) pix[z] = z == k ? p : pix[z];
+        }
+    }
+    // phase 3: the gathers, issued together (index 0 stands in for misses)
+    float2 pm[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) pm[z] = pixmap[max(pix[z], 0)];
+    // phase 4: s = D - z_c, |s| <= delta (a pixel without a measurement holds 0)
     float Tk[8], pk[8];
     uint32_t vmask = 0;
+    bool near = false;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        // phase 1: approximate camera coordinates and the pixel decision
-        int pix[4];
-        int exact = 0;
+    for (int z = 0; z < 8; ++z) {
+        const double sd = (double)pm[z].x - fma((double)z, fc.sz, z0);
+        near |= fabs(fabs(sd) - v.delta) <= fc.thr_s;
+        const bool ok = pix[z] >= 0 && pm[z].x > 0.0f && fabs(sd) <= v.delta;
+        Tk[z] = (float)(sd * v.inv_delta);
+        pk[z] = pm[z].y;
+        vmask |= (ok ? 1u : 0u) << z;
+    }
+    if (__ballot(near)) {   // |s| too near delta somewhere: the defined z_c for the whole block
+        vmask = 0;
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+            double xc, yc, zc;
+            defined(k, xc, yc, zc);
+            float D = 0.0f;
+            bool in = false;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double zf = (double)(4 * half + k);
-            const double xc = fma(zf, fc.sx, x0), yc = fma(zf, fc.sy, y0), zc = fma(zf, fc.sz, z0);
-            pix[k] = pixel_filter(cam, fc, xc, yc, zc);
-            exact |= (pix[k] == -2) << k;
-        }
-        // phase 2 (rare): voxels the approximation cannot decide take the
-        // defined expression
-        if (exact) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if ((exact >> k) & 1) {
-#pragma clang fp contract(off)
-                    const double pz = v.origin[2] + ((double)(bz * 8 + 4 * half + k) + 0.5) * v.vs;
-                    const double dz = pz - cam.t[2];
-                    const double zc = az + cam.R[8] * dz;
-                    pix[k] = zc > 0.0 ? pixel_exact(cam.fx, cam.fy, cam.cx, cam.cy, cam.width, cam.height,
-                                                    ax + cam.R[6] * dz, ay + cam.R[7] * dz, zc)
-                                      : -1;
-                }
+            for (int z = 0; z < 8; ++z) {
+                D = z == k ? pm[z].x : D;
+                in = z == k ? pix[z] >= 0 : in;
             }
-        }
-        // phase 3: the gathers, issued together (index 0 stands in for misses)
-        float2 pm[4];
+            const double sd = (double)D - zc;
+            const float T = (float)(sd * v.inv_delta);
+            vmask |= (in && D > 0.0f && fabs(sd) <= v.delta ? 1u : 0u) << k;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) pm[k] = pixmap[pix[k] >= 0 ? pix[k] : 0];
-        // phase 4: s = D - z_c, |s| <= delta; the defined z_c where the
-        // pixel needed it or s lies near the threshold
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int z = 4 * half + k;
-            double sd = (double)pm[k].x - fma((double)z, fc.sz, z0);
-            if (((exact >> k) & 1) || fabs(fabs(sd) - v.delta) <= fc.thr_s) {
-#pragma clang fp contract(off)
-                const double pz = v.origin[2] + ((double)(bz * 8 + z) + 0.5) * v.vs;
-                const double dz = pz - cam.t[2];
-                sd = (double)pm[k].x - (az + cam.R[8] * dz);
-            }
-            const bool ok = pix[k] >= 0 && pm[k].x > 0.0f && fabs(sd) <= v.delta;
-            Tk[z] = (float)(sd * v.inv_delta);
-            pk[z] = pm[k].y;
-            vmask |= (uint32_t)ok << z;
+            for (int z = 0; z < 8; ++z) Tk[z] = z == k ? T : Tk[z];
         }
     }
     if (lane == 0) {
