@@ -27,15 +27,18 @@
 // next (1-2 times a ray).  Samples live in voxel-centre coordinates
 // q = (x - origin)/voxel - 1/2, where the 8 voxels around a sample are
 // floor(q) + {0,1}^3.  When a step finds nothing and its last sample lies in a
-// block without cells where a bracket can end, the group jumps past it, or past
-// the largest empty aligned group of 4^3 or 16^3 blocks around it.
+// largest empty aligned group of 4^3 or 16^3 blocks, the group jumps past it
+// (past a single block without cells where a bracket can end only if its step
+// is shorter than 32 samples).
 //
 // What bounds it: instruction issue and the chains of dependent loads (the
 // march's two per step), not bytes.  Evaluating F at every sample of the band
 // kept the vector units 80 % busy on the 640x480 orbit (1 mm); with the
-// records, and the refinement finishing on the ray's cubic inside a cell:
-// 263 -> 195 us there (8 lanes per ray), 128 -> 109 us on the 1280x960 hand
-// (0.15 mm, 4 lanes), 188 -> 90 us with the hash only (4 mm, FP16).
+// records, the refinement finishing on the ray's cubic inside a cell, in one
+// pass after the sampled steps, and a ray's setup without divisions and square
+// roots in the library's form: 263 -> 169 us there (8 lanes per ray, a step of
+// 32 samples), 20 -> 15 us at 160x120, 128 -> 108 us on the 1280x960 hand
+// (0.15 mm, 4 lanes), 188 -> 88 us with the hash only (4 mm, FP16).
 #include "raycast_device.h"
 
 namespace tsdf {

@@ -357,6 +357,21 @@ struct Ray {
     double dq[3];    // dq/ds: the unit world direction over the voxel size
 };
 
+// Reciprocal and reciprocal square root to about an ulp: the hardware
+// estimate and two Newton steps.
+__device__ __forceinline__ double fast_rcp(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ double fast_rsqrt(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = y * fma(-0.5 * x * y, y, 1.5);
+    return y * fma(-0.5 * x * y, y, 1.5);
+}
+
 template <typename S>
 __device__ __forceinline__ float ld(const S *p);
 template <>
@@ -480,12 +495,8 @@ __device__ __forceinline__ int cell_exit_sample(const Ray &r, const int B[3], in
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int lo = (B[a] >> sh) << (sh + 3);
-        // (a reciprocal to about an ulp, which the test below allows for)
-        double inv = __builtin_amdgcn_rcp(r.dq[a]);
-        inv = fma(inv, fma(-r.dq[a], inv, 1.0), inv);
-        inv = fma(inv, fma(-r.dq[a], inv, 1.0), inv);
         const double face = (double)(r.dq[a] > 0.0 ? lo + (8 << sh) : lo);
-        if (r.dq[a] != 0.0) s_exit = fmin(s_exit, (face - r.q0[a]) * inv);
+        if (r.dq[a] != 0.0) s_exit = fmin(s_exit, (face - r.q0[a]) * fast_rcp(r.dq[a]));
     }
     const int m = (int)fmin(floor(s_exit * inv_h), 2.0e9);
     double qm[3];
@@ -521,7 +532,7 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     const int cq = within >> 4, k16 = within & 15;
     const int i = ti * kRT + (cq & 1) * 4 + (k16 & 3), jpix = tj * kRT + (cq >> 1) * 4 + (k16 >> 2);
     const bool active = tj < tiles_y && i < cam.width && jpix < cam.height;
-    const double h = 0.5 * v.vs;
+    const double h = 0.5 * v.vs, inv_h = 2.0 * v.inv_vs;
 
     Ray r;
     r.q0 = cam.q0;
@@ -543,13 +554,14 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     // a ray with an empty span (and no block at the camera plane) misses
     // without a sample: the ray itself is only set up for the others
     if (active && (near || zmin_t <= zmax_t)) {
-        const double dc0 = (i - cam.cx) / cam.fx, dc1 = (jpix - cam.cy) / cam.fy;
-        const double len = sqrt(dc0 * dc0 + dc1 * dc1 + 1.0);
+        const double dc0 = (i - cam.cx) * cam.inv_fx, dc1 = (jpix - cam.cy) * cam.inv_fy;
+        const double len2 = dc0 * dc0 + dc1 * dc1 + 1.0;
+        const double inv_len = fast_rsqrt(len2), len = len2 * inv_len;
         double inv[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            r.dq[a] = (cam.R[3 * a] * dc0 + cam.R[3 * a + 1] * dc1 + cam.R[3 * a + 2]) / len * v.inv_vs;
-            inv[a] = r.dq[a] != 0.0 ? 1.0 / r.dq[a] : 0.0;
+            r.dq[a] = (cam.R[3 * a] * dc0 + cam.R[3 * a + 1] * dc1 + cam.R[3 * a + 2]) * inv_len * v.inv_vs;
+            inv[a] = r.dq[a] != 0.0 ? fast_rcp(r.dq[a]) : 0.0;
         }
         // valid samples need every stencil voxel in the grid: q in [0, G-1]
         double s_in = 0.0, s_out = 1e300;
@@ -570,8 +582,10 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             s_out = fmin(s_out, (double)zmax_t * len);
         }
         if (!miss && s_in <= s_out) {
-            n_lo = max((int)fmin(floor(s_in / h) - 1.0, 2.0e9), 1);
-            n_end = (int)fmin(ceil(s_out / h) + 1.0, 2.0e9);
+            // (a sample more at either end than the span needs: s_in and s_out
+            // are products with reciprocals good to a few ulp)
+            n_lo = max((int)fmin(floor(s_in * inv_h) - 1.0, 2.0e9), 1);
+            n_end = (int)fmin(ceil(s_out * inv_h) + 1.0, 2.0e9);
         }
     }
 
@@ -588,12 +602,14 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     // kPerLane samples a lane make the steps fewer.
     constexpr int kPerLane = G >= 16 ? 2 : G == 8 ? 4 : 8;
     constexpr int kSpan = G * kPerLane;   // at most 32: a bit each
+    // a step of 32 samples (16 voxels) is longer than the way through a block:
+    // only larger empty groups of blocks are worth a jump then
+    constexpr bool kJumpBlock = kSpan < 32;
     const float kNaN = __builtin_nanf("");
     BlockCache cache;
     cache.key = kEmptyKey;
 #pragma unroll
     for (int k = 0; k < 8; ++k) cache.base[k] = v.capacity * (uint32_t)kBlockVoxels;
-    const double inv_h = 2.0 * v.inv_vs;
     int n_base = n_lo;
     bool done = !(active && n_lo <= n_end);
     bool hit = false;
@@ -642,7 +658,7 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
                     const uint32_t w = (uint32_t)rec->cell[cell[k] & 63u] >> (cell[k] >> 8);
                     ends |= (w & 1u) << (k * G + j);
                     begins |= ((w >> 8) & 1u) << (k * G + j);
-                    if (k == kPerLane - 1 && j == G - 1) box = rec->box;
+                    if (kJumpBlock && k == kPerLane - 1 && j == G - 1) box = rec->box;
                 }
 #pragma unroll
             for (int off = 1; off < G; off <<= 1) {
@@ -654,7 +670,8 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             // the group's last sample decides a jump past the cells of its block
             // when no bracket can end there, or of the largest aligned group of
             // blocks around it that is empty (bits 30-31: log4 of its edge)
-            const uint32_t skip = inside && !box ? last_key | (occ0 ? 0u : occ1 ? 1u << 30 : 2u << 30) : kEmptyKey;
+            const uint32_t skip = inside && (kJumpBlock ? !box : !occ0)
+                                      ? last_key | (occ0 ? 0u : occ1 ? 1u << 30 : 2u << 30) : kEmptyKey;
             const uint32_t jump = (uint32_t)__shfl((int)skip, group_lane<G>(lane, G - 1));
             if (!found) {
                 if (cand) {
@@ -738,16 +755,19 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     }
 
     // ---- refinement: quaternary search inside [s_lo, s_hi] (F_lo > 0 >= F_hi),
-    // six steps that shrink the bracket 4096-fold.  Each looks at the 3 inner
-    // quarter points (point m by lane m % G of the group, in ceil(3 / G)
+    // up to six steps that shrink the bracket 4096-fold.  Each looks at the 3
+    // inner quarter points (point m by lane m % G of the group, in ceil(3 / G)
     // rounds), so the points and hence the result do not depend on the group
     // size.  Inside one cell F along the ray is a cubic: once a step's bracket
-    // lies in one, the steps after it evaluate the cubic through the step's
-    // points instead of the volume (most rays: after the second step).
+    // lies in one (most rays: the second step's), the cubic through the step's
+    // points stands in for the volume, and the search goes on in registers.
     constexpr int kPts = 3, kSteps = 6, kRounds = (kPts + G - 1) / G;
     double a = s_lo, b = s_hi;
     float Fa = F_lo, Fb = F_hi;
-    bool refine = hit;
+    bool refine = hit, cubic = false;
+    // the cubic through f0.. at u = 0..3 (Newton's forward differences); the
+    // bracket [a, b] is [u0, u0 + 1]
+    float f0 = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f, u0 = 0.0f;
     for (int it = 0; it < kSteps; ++it) {
         if (!__ballot(refine)) break;
         float Fp[kPts];
@@ -765,60 +785,59 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
                 Fp[mm] = __shfl(Fm, group_lane<G>(lane, mm - rd * G));
         }
         if (refine) {
-            bool bad = false;
-            int k = kPts;   // first non-positive point: the root lies in (point k-1, point k]
-#pragma unroll
-            for (int mm = kPts - 1; mm >= 0; --mm) {
-                bad |= Fp[mm] != Fp[mm];   // NaN: invalid
-                if (Fp[mm] <= 0.0f) k = mm;
-            }
-            if (bad) {
-                refine = false;   // an invalid point inside the bracket: keep the bracket
+            // an invalid point inside the bracket: keep the bracket
+            if (Fp[0] != Fp[0] || Fp[1] != Fp[1] || Fp[2] != Fp[2]) {
+                refine = false;
             } else {
+                // first non-positive point: the root lies in (point k - 1, point k]
+                const bool n0 = Fp[0] <= 0.0f, n1 = Fp[1] <= 0.0f, n2 = Fp[2] <= 0.0f;
+                const int k = n0 ? 0 : n1 ? 1 : n2 ? 2 : 3;
                 double qa[3], qb[3];
                 q_at(r, a, qa);
                 q_at(r, b, qb);
-                const bool one_cell = floor(qa[0]) == floor(qb[0]) && floor(qa[1]) == floor(qb[1]) &&
-                                      floor(qa[2]) == floor(qb[2]);
+                cubic = floor(qa[0]) == floor(qb[0]) && floor(qa[1]) == floor(qb[1]) && floor(qa[2]) == floor(qb[2]);
+                refine = !cubic;
                 // the four of the five points around the root's quarter
                 const bool upper = k >= 2;
-                const float f0 = upper ? Fp[0] : Fa, f1 = upper ? Fp[1] : Fp[0], f2 = upper ? Fp[2] : Fp[1],
-                            f3 = upper ? Fb : Fp[2];
-                float lo = k == 0 ? Fa : k == 1 ? Fp[0] : k == 2 ? Fp[1] : Fp[2];
-                float hi = k == 0 ? Fp[0] : k == 1 ? Fp[1] : k == 2 ? Fp[2] : Fb;
-                const double na = k == 0 ? a : a + (b - a) * (double)k * 0.25;
-                const double nb = k == kPts ? b : a + (b - a) * (double)(k + 1) * 0.25;
-                if (one_cell) {
-                    // P(u) through f0..f3 at u = 0..3 (Newton's forward differences)
-                    const float d1 = f1 - f0, e1 = f2 - f1, e2 = f3 - f2;
-                    const float d2 = 0.5f * (e1 - d1), d3 = ((e2 - e1) - (e1 - d1)) * (1.0f / 6.0f);
-                    const float u0 = (float)(k - (upper ? 1 : 0));
-                    float t = 0.0f, dt = 1.0f;   // the bracket is u0 + [t, t + dt]
-                    for (int st = it + 1; st < kSteps; ++st) {
-                        dt *= 0.25f;
-                        float p[kPts];
-#pragma unroll
-                        for (int m = 0; m < kPts; ++m) {
-                            const float u = u0 + (t + (float)(m + 1) * dt);
-                            p[m] = fmaf(u, fmaf(u - 1.0f, fmaf(u - 2.0f, d3, d2), d1), f0);
-                        }
-                        const float l = lo, u = hi;
-                        const int kk = p[0] <= 0.0f ? 0 : p[1] <= 0.0f ? 1 : p[2] <= 0.0f ? 2 : 3;
-                        lo = kk == 0 ? l : kk == 1 ? p[0] : kk == 2 ? p[1] : p[2];
-                        hi = kk == 0 ? p[0] : kk == 1 ? p[1] : kk == 2 ? p[2] : u;
-                        t = fmaf((float)kk, dt, t);
-                    }
-                    const double w = nb - na;
-                    a = na + w * (double)t;
-                    b = na + w * (double)(t + dt);
-                    refine = false;
-                } else {
-                    a = na;
-                    b = nb;
-                }
-                Fa = lo;
-                Fb = hi;
+                const float g1 = upper ? Fp[1] : Fp[0], g2 = upper ? Fp[2] : Fp[1], g3 = upper ? Fb : Fp[2];
+                f0 = upper ? Fp[0] : Fa;
+                d1 = g1 - f0;
+                const float e1 = g2 - g1, e2 = g3 - g2, c1 = e1 - d1;
+                d2 = 0.5f * c1;
+                d3 = ((e2 - e1) - c1) * (1.0f / 6.0f);
+                u0 = k == 0 || k == 2 ? (upper ? 1.0f : 0.0f) : (upper ? 2.0f : 1.0f);
+                Fb = n0 ? Fp[0] : n1 ? Fp[1] : n2 ? Fp[2] : Fb;
+                Fa = n0 ? Fa : n1 ? Fp[0] : n2 ? Fp[1] : Fp[2];
+                const double w = (b - a) * 0.25;
+                a += w * (double)k;
+                b = a + w;
             }
+        }
+    }
+    if (__ballot(cubic)) {
+        // four more steps on the cubic: the bracket is then at most a 2048th of
+        // a voxel
+        float t = 0.0f, dt = 1.0f;   // the bracket is u0 + [t, t + dt]
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            dt *= 0.25f;
+            float p[kPts];
+#pragma unroll
+            for (int m = 0; m < kPts; ++m) {
+                const float u = u0 + (t + (float)(m + 1) * dt);
+                p[m] = fmaf(u, fmaf(u - 1.0f, fmaf(u - 2.0f, d3, d2), d1), f0);
+            }
+            const bool n0 = p[0] <= 0.0f, n1 = p[1] <= 0.0f, n2 = p[2] <= 0.0f;
+            if (cubic) {
+                Fb = n0 ? p[0] : n1 ? p[1] : n2 ? p[2] : Fb;
+                Fa = n0 ? Fa : n1 ? p[0] : n2 ? p[1] : p[2];
+            }
+            t = fmaf(n0 ? 0.0f : n1 ? 1.0f : n2 ? 2.0f : 3.0f, dt, t);
+        }
+        if (cubic) {
+            const double w = b - a;
+            a += w * (double)t;
+            b = a + w * (double)dt;
         }
     }
     const double sh = hit ? ((Fa - Fb) > 0.0f ? a + (b - a) * ((double)Fa / ((double)Fa - (double)Fb)) : 0.5 * (a + b))

@@ -101,7 +101,8 @@ struct Camera {
     double R[9];      // row-major camera-to-world rotation
     double t[3];
     double fx, fy, cx, cy;
-    double q0[3];     // camera centre in voxel-centre coordinates (t - origin) / voxel - 1/2 (set_ray_origin)
+    double q0[3];     // camera centre in voxel-centre coordinates (t - origin) / voxel - 1/2, and 1 / fx, 1 / fy
+    double inv_fx, inv_fy;   // (set_ray_origin)
     int32_t width, height;
 };
 
@@ -114,6 +115,8 @@ struct NoiseParams {
 inline void set_ray_origin(Camera &cam, const VolumeView &v)
 {
     for (int a = 0; a < 3; ++a) cam.q0[a] = fma(cam.t[a] - v.origin[a], v.inv_vs, -0.5);
+    cam.inv_fx = 1.0 / cam.fx;
+    cam.inv_fy = 1.0 / cam.fy;
 }
 
 // Block key: 10 bits per axis.
