@@ -76,7 +76,7 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
 {
     using Lds = typename std::conditional<kMlp, PrepMlpLds, PrepCandLds>::type;
     __shared__ Lds lds;
-    __shared__ uint32_t n_list;
+    __shared__ uint32_t n_list, n_fresh, base;
     const int tid = threadIdx.x;
     const int i = tx * kTile + (tid & (kTile - 1));
     const int j = ty * kTile + (tid / kTile);
@@ -112,10 +112,13 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
     uint32_t *set = cand->set;
     uint32_t *list = cand->list;
     for (int k = tid; k < kLdsSet; k += 256) set[k] = kEmptyKey;
-    if (tid == 0) n_list = 0;
+    if (tid == 0) n_list = n_fresh = 0;
     if (in_image) v.pixmap[(size_t)j * cam.width + i] = make_float2(valid ? D : 0.0f, ph);
     __syncthreads();
 
+    uint32_t lo[kSubRanges], hi[kSubRanges];   // boxes of blocks, first and last (kEmptyKey: none)
+#pragma unroll
+    for (int sr = 0; sr < kSubRanges; ++sr) lo[sr] = hi[sr] = kEmptyKey;
     if (valid) {
         // The frustum cell (pixel square x [D - delta, D + delta]) is cut into
         // kSubRanges depth slices; each slice's world box gives candidate
@@ -139,6 +142,7 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
             cmin[a] = (cam.t[a] - pad - v.origin[a]) * v.inv_vs - 0.5;
             cmax[a] = (cam.t[a] + pad - v.origin[a]) * v.inv_vs - 0.5;
         }
+#pragma unroll
         for (int sr = 0; sr < kSubRanges; ++sr) {
             const double za = z0 + (z1 - z0) * sr / kSubRanges;
             const double zb = (sr == kSubRanges - 1) ? z1 : z0 + (z1 - z0) * (sr + 1) / kSubRanges;
@@ -155,65 +159,108 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
                 b1[a] = empty ? -1 : (int)g1 >> 3;
             }
             if (empty) continue;
-            for (int bz = b0[2]; bz <= b1[2]; ++bz)
-                for (int by = b0[1]; by <= b1[1]; ++by)
-                    for (int bx = b0[0]; bx <= b1[0]; ++bx) {
-                        const uint32_t key = pack_key(bx, by, bz);
-                        uint32_t h = hash_key(key) & (kLdsSet - 1);
-                        bool placed = false;
-                        for (int p = 0; p < 64; ++p) {
-                            uint32_t prev = atomicCAS(&set[h], kEmptyKey, key);
-                            if (prev == kEmptyKey) {
-                                uint32_t slot = atomicAdd(&n_list, 1u);
-                                if (slot < (uint32_t)kLdsList) {
-                                    list[slot] = key;
-                                    placed = true;
-                                }
-                                break;
-                            }
-                            if (prev == key) {
-                                placed = true;
-                                break;
-                            }
-                            h = (h + 1) & (kLdsSet - 1);
-                        }
-                        // LDS set or list exhausted: go straight to the frame-wide dedup
-                        if (!placed) global_candidate_lane(v, key, bx, by, bz);
+            lo[sr] = pack_key(b0[0], b0[1], b0[2]);
+            hi[sr] = pack_key(b1[0], b1[1], b1[2]);
+        }
+    }
+
+    // Rounds: every lane enters the blocks of its boxes until the tile's list is
+    // full or all are in, then the list goes out.  One round for most tiles.  A
+    // tile whose pixels are wider than a block has more blocks than the list
+    // holds (1500 at 320x240 and 1 mm): sending each block past a full list
+    // from its lane, a round trip to the frame's bitmap at a time, kept such a
+    // tile busy for 0.5 ms, and the launch with it (16 scenes from 320x240 to
+    // 640x480: 647 -> 220 us).
+    static_assert(kSubRanges == 2, "a lane's boxes: the current one and the next");
+    uint32_t cur_lo = lo[0] != kEmptyKey ? lo[0] : lo[1], cur_hi = lo[0] != kEmptyKey ? hi[0] : hi[1];
+    uint32_t next_lo = lo[0] != kEmptyKey ? lo[1] : kEmptyKey;
+    const uint32_t next_hi = hi[1];
+    int bx, by, bz;
+    unpack_key(cur_lo, bx, by, bz);
+    for (;;) {
+        while (cur_lo != kEmptyKey) {
+            const uint32_t key = pack_key(bx, by, bz);
+            uint32_t h = hash_key(key) & (kLdsSet - 1);
+            bool placed = false, full = false;
+            for (int p = 0; p < 64; ++p) {
+                uint32_t prev = atomicCAS(&set[h], kEmptyKey, key);
+                if (prev == kEmptyKey) {
+                    uint32_t slot = atomicAdd(&n_list, 1u);
+                    full = slot >= (uint32_t)kLdsList;
+                    if (!full) list[slot] = key;
+                    placed = true;
+                    break;
+                }
+                if (prev == key) {
+                    placed = true;   // (if it found the list full: its lane enters it in the next round)
+                    break;
+                }
+                h = (h + 1) & (kLdsSet - 1);
+            }
+            if (full) break;
+            if (!placed) global_candidate_lane(v, key, bx, by, bz);   // a crowded stretch of the set
+            int x0, y0, z0, x1, y1, z1;
+            unpack_key(cur_lo, x0, y0, z0);
+            unpack_key(cur_hi, x1, y1, z1);
+            if (++bx > x1) {
+                bx = x0;
+                if (++by > y1) {
+                    by = y0;
+                    if (++bz > z1) {
+                        cur_lo = next_lo;
+                        cur_hi = next_hi;
+                        next_lo = kEmptyKey;
+                        unpack_key(cur_lo, bx, by, bz);
                     }
+                }
+            }
         }
-    }
-    __syncthreads();
-    const uint32_t n = min(n_list, (uint32_t)kLdsList);
-    if (n == 0) return;
-    // Keys this tile is first to mark are compacted into the (now unused)
-    // set and appended with one counter update per tile: a counter update
-    // per wavefront makes every tile of the frame queue on one address.
-    __shared__ uint32_t n_fresh, base;
-    if (tid == 0) n_fresh = 0;
-    __syncthreads();
-    for (uint32_t k = tid; k < n; k += 256) {
-        const uint32_t key = list[k];
-        int bx, by, bz;
-        unpack_key(key, bx, by, bz);
-        const uint64_t b = block_linear(v, bx, by, bz);
-        const uint32_t bit = 1u << (b & 31);
-        if (!(atomicOr(&v.cand_bits[b >> 5], bit) & bit)) set[atomicAdd(&n_fresh, 1u)] = key;
-    }
-    __syncthreads();
-    if (tid == 0 && n_fresh) base = atomicAdd(&v.state->cand_count, n_fresh);
-    __syncthreads();
-    for (uint32_t k = tid; k < n_fresh; k += 256) {
-        const uint32_t key = set[k];
-        const uint32_t idx = base + k;
-        if (idx < v.max_candidates) {
-            v.cand_list[idx] = key;
-        } else {
-            int bx, by, bz;
-            unpack_key(key, bx, by, bz);
-            const uint64_t b = block_linear(v, bx, by, bz);
-            atomicOr(&v.state->status, (uint32_t)TSDF_FLAG_CAND_FULL);
-            atomicAnd(&v.cand_bits[b >> 5], ~(1u << (b & 31)));
+        __syncthreads();
+        const uint32_t n = min(n_list, (uint32_t)kLdsList);
+        if (n == 0) return;   // the whole workgroup: no block at all
+        // Keys this tile is first to mark are compacted into the (now unused)
+        // set and appended with one counter update per round: a counter update
+        // per wavefront makes every tile of the frame queue on one address.
+        // All of a thread's marks are in flight before it looks at the first.
+        constexpr int kMarks = kLdsList / 256;
+        uint32_t keys[kMarks], old[kMarks], bit[kMarks];
+#pragma unroll
+        for (int q = 0; q < kMarks; ++q) {
+            const uint32_t k = tid + 256u * q;
+            old[q] = bit[q] = 1u;
+            if (k < n) {
+                keys[q] = list[k];
+                int kx, ky, kz;
+                unpack_key(keys[q], kx, ky, kz);
+                const uint64_t b = block_linear(v, kx, ky, kz);
+                bit[q] = 1u << (b & 31);
+                old[q] = atomicOr(&v.cand_bits[b >> 5], bit[q]);
+            }
         }
+#pragma unroll
+        for (int q = 0; q < kMarks; ++q)
+            if (!(old[q] & bit[q])) set[atomicAdd(&n_fresh, 1u)] = keys[q];
+        __syncthreads();
+        if (tid == 0 && n_fresh) base = atomicAdd(&v.state->cand_count, n_fresh);
+        const bool more = __syncthreads_or(cur_lo != kEmptyKey);
+        for (uint32_t k = tid; k < n_fresh; k += 256) {
+            const uint32_t key = set[k];
+            const uint32_t idx = base + k;
+            if (idx < v.max_candidates) {
+                v.cand_list[idx] = key;
+            } else {
+                int kx, ky, kz;
+                unpack_key(key, kx, ky, kz);
+                const uint64_t b = block_linear(v, kx, ky, kz);
+                atomicOr(&v.state->status, (uint32_t)TSDF_FLAG_CAND_FULL);
+                atomicAnd(&v.cand_bits[b >> 5], ~(1u << (b & 31)));
+            }
+        }
+        if (!more) return;
+        __syncthreads();
+        for (int k = tid; k < kLdsSet; k += 256) set[k] = kEmptyKey;
+        if (tid == 0) n_list = n_fresh = 0;
+        __syncthreads();
     }
 }
 

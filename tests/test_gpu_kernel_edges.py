@@ -9,7 +9,9 @@ import pytest
 import torch
 
 import oracle
+from synthetic.configs import sequence_frame, small_orbit
 from synthetic.scenes import Intrinsics, look_at
+from tests.parity import CHI, Kvec, compare_raycast, compare_volumes, gpu_volume_for, oracle_volume_for
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +77,94 @@ def test_samples_are_collected_in_pixel_order(mlp, W, H):
     m = len(r)
     assert m == max(2 * n - 3, 1) or n < 2
     assert np.array_equal(x, np.concatenate([ef, ef])[:m]) and np.array_equal(r, np.concatenate([er, er])[:m])
+
+
+@pytest.fixture(scope="module")
+def tsdf():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1311_7194_amd as m
+
+    m.lib()
+    return m
+
+
+@pytest.mark.parametrize("W,H", [(60, 45), (24, 18), (13, 9)])
+def test_tiles_with_more_blocks_than_their_list(tsdf, W, H):
+    """Frames whose pixels are up to four blocks wide: a 16x16-pixel tile
+    reaches from some hundred blocks to several times the 1024 its list holds
+    (and its last round holds any number)."""
+    spec = small_orbit(width=W, height=H, n_frames=2, G=512, vs=0.004)
+    gv, ov = gpu_volume_for(spec), oracle_volume_for(spec)
+    for k in range(2):
+        d, p = sequence_frame(spec, k)
+        st = ov.integrate(d.numpy(), Kvec(spec.K), p)
+        gv.integrate(d.cuda(), spec.K, p)
+        gst = gv.stats()
+        assert gst["frame_updates"] == st["updates"] and gst["frame_new_blocks"] == st["new_blocks"]
+        assert gst["status_flags"] == 0
+    stats = compare_volumes(gv, ov)
+    assert stats["blocks"] > 800
+
+
+@pytest.mark.parametrize("z", [0.125, 1.0])
+@pytest.mark.parametrize("shift", [0.0, 0.5])
+def test_voxel_centres_on_pixel_borders(tsdf, z, shift):
+    """A camera for which whole planes of voxel centres project exactly onto
+    the borders between pixels (dyadic sizes: the projection is exact), each
+    pixel with its own depth: the oracle's pixel in every case."""
+    W, H, vs = 97, 61, z / 128
+    K = Intrinsics(64.0, 64.0, 48.0 + shift, 30.0 + shift, W, H)
+    rng = np.random.default_rng(int(8 * z))
+    d = (z * (1 + 0.02 * rng.uniform(-1, 1, (H, W)))).astype(np.float32)
+    # the camera centre is a voxel centre
+    pose = np.hstack([np.eye(3), np.array([[0.5 * vs], [0.5 * vs], [0.5 * vs]])])
+    origin, dims = (-128 * vs, -128 * vs, 0.0), (256, 256, 256)
+    gv = tsdf.Volume(dims, vs, origin, 4.0, 1 << 13, 1 << 14, 0, 1e-4, W, H)
+    ov = oracle.OracleVolume(dims, vs, origin, 4.0, capacity_blocks=1 << 13)
+    coeff = 0.0015 / z
+    st = ov.integrate(d, Kvec(K), pose, coeff=coeff)
+    gv.integrate(torch.from_numpy(d).cuda(), K, pose, coeff=coeff)
+    gst = gv.stats()
+    assert st["updates"] > 20000 and gst["frame_updates"] == st["updates"]
+    assert gst["frame_new_blocks"] == st["new_blocks"]
+    compare_volumes(gv, ov)
+
+
+@pytest.fixture(scope="module")
+def gyroid():
+    """Blocks of a gyroid's truncated distance, every seventh or so missing,
+    and the oracle's raycast of them: brackets, stencils and empty stretches at
+    every place of a block and across its borders."""
+    n, vs = 96, 0.01
+    q = (np.arange(n) + 0.5) * (2 * math.pi / 29.3)
+    x, y, z = np.meshgrid(q, q, q, indexing="ij")
+    g = np.sin(x) * np.cos(y) + np.sin(y) * np.cos(z) + np.sin(z) * np.cos(x)
+    T = g / (1.2 * 2 * math.pi / 29.3) / 4.0      # about the distance in truncation widths of 4 voxels
+    T[np.abs(T) > 1] = CHI
+    T = T.astype(np.float32).astype(np.float64)
+    ov = oracle.OracleVolume((n, n, n), vs, (0.0, 0.0, 0.0), 4.0, capacity_blocks=2048)
+    rng = np.random.default_rng(3)
+    for bz in range(n // 8):
+        for by in range(n // 8):
+            for bx in range(n // 8):
+                if rng.random() < 0.15:
+                    continue
+                t = T[8 * bx:8 * bx + 8, 8 * by:8 * by + 8, 8 * bz:8 * bz + 8].transpose(2, 1, 0)   # x fastest
+                if (t <= 1).any():
+                    ov.set_block((bx, by, bz), np.ascontiguousarray(t).reshape(-1), np.full(512, 1e-3))
+    K = Intrinsics(70.0, 70.0, 40.2, 29.6, 83, 59)
+    pose = look_at((-0.35, 0.7, -0.25), (0.5, 0.45, 0.5))
+    return n, vs, K, pose, ov.export(), ov.raycast(Kvec(K), pose, K.width, K.height, n_threads=8)
+
+
+@pytest.mark.parametrize("group,dense", [(1, True), (2, False), (4, True), (8, True), (8, False), (16, False)])
+def test_raycast_of_cells_at_block_borders(tsdf, gyroid, group, dense):
+    n, vs, K, pose, (keys, T, P), (ov, on, flags) = gyroid
+    gv = tsdf.Volume((n, n, n), vs, (0.0, 0.0, 0.0), 4.0, 2048, 4096, 0, 1e-4, K.width, K.height, dense_index=dense)
+    gv.set_raycast_group(group)
+    gv.import_blocks(torch.from_numpy(keys), torch.from_numpy(T).float(), torch.from_numpy(P).float())
+    vert, nrm = gv.raycast(K, pose)
+    torch.cuda.synchronize()
+    rs = compare_raycast(vert.cpu().numpy(), nrm.cpu().numpy(), ov, on, flags, pose, vs)
+    assert rs["hits"] > 1000, rs
