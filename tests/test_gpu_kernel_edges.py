@@ -11,6 +11,7 @@ import torch
 import oracle
 from synthetic.configs import sequence_frame, small_orbit
 from synthetic.scenes import Intrinsics, look_at
+from tests.test_gpu_mesh import compare_meshes, gpu_mesh, load_both
 from tests.parity import CHI, Kvec, compare_raycast, compare_volumes, gpu_volume_for, oracle_volume_for
 
 pytestmark = pytest.mark.gpu
@@ -168,3 +169,31 @@ def test_raycast_of_cells_at_block_borders(tsdf, gyroid, group, dense):
     torch.cuda.synchronize()
     rs = compare_raycast(vert.cpu().numpy(), nrm.cpu().numpy(), ov, on, flags, pose, vs)
     assert rs["hits"] > 1000, rs
+
+
+@pytest.mark.parametrize("storage,dense,missing", [(0, True, 0.1), (0, False, 0.0), (1, True, 0.0)])
+def test_mesh_of_blocks_with_several_rounds_of_triangles(tsdf, storage, dense, missing):
+    """Random signs: about 1400 triangles a block, placed 512 at a time, every
+    case of a cell at every place of a block; some voxels without a distance,
+    some exactly zero, some neighbour blocks missing; and the same with room
+    for part of the triangles, ending inside a round."""
+    rng = np.random.default_rng(17 + storage)
+    keys = [(x, y, z) for x in range(3) for y in range(3) for z in range(3) if rng.random() >= missing]
+    T = rng.uniform(-1, 1, (len(keys), 512))
+    T[rng.random(T.shape) < 0.02] = CHI
+    T[rng.random(T.shape) < 0.02] = 0.0
+    T = T.astype(np.float16 if storage else np.float32).astype(np.float64)
+    ov, gv = load_both(tsdf, (24, 24, 24), 0.01, (-0.1, 0.0, 0.05), np.array(keys, np.int32), T, storage, dense,
+                       capacity=64)
+    mesh = gpu_mesh(gv)
+    assert compare_meshes(mesh, ov.marching_cubes(), 0.01)["triangles"] > 20000
+    n = len(mesh[0])
+    cap = n - 700
+    vid, t, xyz = (torch.full((cap, *s), -7, dtype=d, device="cuda")
+                   for s, d in (((3,), torch.int64), ((3,), torch.float32), ((3, 3), torch.float32)))
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    gv.extract_mesh_into(vid, t, xyz, count, gv.mesh_workspace())
+    torch.cuda.synchronize()
+    assert int(count) == n
+    for got, want in zip((vid, t, xyz), mesh):
+        assert np.array_equal(got.cpu().numpy(), want[:cap])
