@@ -38,7 +38,8 @@
 // pass after the sampled steps, and a ray's setup without divisions and square
 // roots in the library's form: 263 -> 169 us there (8 lanes per ray, a step of
 // 32 samples), 20 -> 15 us at 160x120, 128 -> 108 us on the 1280x960 hand
-// (0.15 mm, 4 lanes), 188 -> 88 us with the hash only (4 mm, FP16).
+// (0.15 mm, 4 lanes; 79 us from a list of its tiles, see kListTiles), 188 ->
+// 88 us with the hash only (4 mm, FP16).
 #include "raycast_device.h"
 
 namespace tsdf {
@@ -54,6 +55,7 @@ __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, ui
 {
     __shared__ RangeLds L;
     const uint32_t n = min(v.state->pool_count, v.capacity);
+    if (blockIdx.x == 0 && threadIdx.x == 0) v.state->long_tiles = v.state->short_tiles = 0;   // for tiles_kernel
     if (blockIdx.x * (uint32_t)kRangeChunk >= n) return;   // (the whole workgroup)
     span_lds_init(L);
     const int cw = (cam.width + kCell - 1) / kCell, ch = (cam.height + kCell - 1) / kCell;
@@ -74,6 +76,73 @@ __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, ui
     }
 }
 
+// Sorts the frame's 8x8-pixel tiles, kTilesPerGroup to a workgroup: a tile without a depth
+// span is background, and its part of the maps is cleared here; the others go to
+// the tile list, those with a long span at its front (their rays march longest
+// and must not start last), the rest from its back.
+constexpr int kTilesPerGroup = 16;
+constexpr float kLongSpan = 80.0f;   // voxels
+
+__global__ __launch_bounds__(256) void tiles_kernel(VolumeView v, int width, int height, uint32_t stamp, int tiles_x,
+                                                    int n_tiles, float4 *__restrict__ vertex,
+                                                    float4 *__restrict__ normal)
+{
+    __shared__ unsigned long long empty;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int first = blockIdx.x * kTilesPerGroup;
+    if (tid < kTilesPerGroup) {   // in one wavefront
+        const int tile = first + lane;
+        const bool valid = tile < n_tiles;
+        bool any = false, is_long = false;
+        if (valid) {
+            const bool near = v.state->near_stamp == stamp;
+            const int cw = (width + kCell - 1) / kCell, ch = (height + kCell - 1) / kCell;
+            const int ci = (tile % tiles_x) * kCellsPerTile, cj = (tile / tiles_x) * kCellsPerTile;
+            const uint32_t tlo = v.tile_range[tile], thi = v.tile_range[(size_t)n_tiles + tile];
+            any = is_long = near;
+#pragma unroll
+            for (int q = 0; q < kCellsPerTile * kCellsPerTile; ++q) {
+                // (a border tile's missing cells: its last ones again)
+                const size_t c = (size_t)min(cj + q / kCellsPerTile, ch - 1) * cw +
+                                 (size_t)min(ci + q % kCellsPerTile, cw - 1);
+                const float lo = __uint_as_float(min(tlo, v.pix_range[c]));
+                const float hi = __uint_as_float(max(thi, v.pix_range[(size_t)cw * ch + c]));
+                any |= lo <= hi;
+                is_long |= hi - lo > kLongSpan * (float)v.vs;
+            }
+        }
+        const unsigned long long ml = __ballot(any && is_long), ms = __ballot(any && !is_long),
+                                 me = __ballot(valid && !any);
+        uint32_t bl = 0, bs = 0;
+        if (lane == 0) {
+            if (ml) bl = atomicAdd(&v.state->long_tiles, (uint32_t)__popcll(ml));
+            if (ms) bs = atomicAdd(&v.state->short_tiles, (uint32_t)__popcll(ms));
+            empty = me;
+        }
+        bl = (uint32_t)__shfl((int)bl, 0);
+        bs = (uint32_t)__shfl((int)bs, 0);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        const uint32_t at = is_long ? bl + (uint32_t)__popcll(ml & below)
+                                    : (uint32_t)n_tiles - 1u - (bs + (uint32_t)__popcll(ms & below));
+        // (in range unless two raycasts of one volume run at once, which is the caller's error)
+        if (any && at < (uint32_t)n_tiles) v.tile_list[at] = (uint32_t)tile;
+    }
+    __syncthreads();
+    // background: a wavefront per tile, a lane per pixel
+    unsigned long long rest = empty;
+    for (int k = 0; rest; ++k) {
+        const int tile = first + __builtin_ctzll(rest);
+        rest &= rest - 1ull;
+        if ((k & 3) != (tid >> 6)) continue;
+        const int i = (tile % tiles_x) * kRT + (lane & 7), jpix = (tile / tiles_x) * kRT + (lane >> 3);
+        if (i < width && jpix < height) {
+            const size_t pix = (size_t)jpix * width + i;
+            vertex[pix] = make_float4(0.f, 0.f, 0.f, 0.f);
+            normal[pix] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+}
+
 // One wavefront per workgroup: march lengths differ widely between
 // wavefronts (most rays of a frame march little or not at all), and a CU
 // takes a new workgroup only where all of its wavefronts fit, so single-wave
@@ -81,10 +150,21 @@ __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, ui
 // at 4 lanes per ray; 640x480 orbit: 284 -> 246 us, now at 8 lanes per ray).
 constexpr int kRayWG = 64;
 
-template <typename S, int G, bool kDense, bool kMark = false>
-__global__ __launch_bounds__(kRayWG) void raycast_kernel(VolumeView v, Camera cam, uint32_t stamp, int tiles_x,
-                                                      int tiles_y, float4 *__restrict__ vertex,
-                                                      float4 *__restrict__ normal)
+// Frames of at least this many tiles march from a tile list: a wavefront takes
+// 1.2 us to find that its tile is background, G of them a tile, and where a
+// large frame shows one object most of it is.  1280x960 hand (19200 tiles, nine
+// in ten background, 4 lanes): 108 -> 79 us, and 10 us for the list; a 640x480
+// orbit frame (4800 tiles, all with something) 169 -> 174 us, and 9 us, so
+// smaller frames keep a wavefront for each G-th of every tile.
+constexpr int kListTiles = 8192;
+constexpr uint32_t kListGrid = 16384;   // workgroups striding over the list; a multiple of 8 * 16
+
+enum MarchMode { kMarchAll, kMarchMark, kMarchList };
+
+template <typename S, int G, bool kDense, MarchMode kMode>
+__global__ __launch_bounds__(kRayWG) __attribute__((amdgpu_waves_per_eu(kMode == kMarchList ? 4 : 1))) void raycast_kernel(
+    VolumeView v, Camera cam, uint32_t stamp, int tiles_x, int tiles_y, float4 *__restrict__ vertex,
+    float4 *__restrict__ normal)
 {
     // Workgroups are dealt to the 8 XCDs in turn.  With up to 4 lanes per ray
     // the G wavefronts of a tile go to one XCD, where they read the same
@@ -96,29 +176,40 @@ __global__ __launch_bounds__(kRayWG) void raycast_kernel(VolumeView v, Camera ca
         const uint32_t grp = blockIdx.x / (8u * G), r = blockIdx.x % (8u * G);
         wg = grp * (8u * G) + (r & 7u) * G + (r >> 3);
     }
-    raycast_body<S, G, kDense, kMark>(v, cam, stamp, tiles_x, tiles_y, vertex, normal,
-                               (long long)wg * kRayWG + threadIdx.x);
+    if constexpr (kMode == kMarchList) {
+        const uint32_t n_tiles = (uint32_t)(tiles_x * tiles_y), n_long = min(v.state->long_tiles, n_tiles);
+        const uint32_t n = min(n_long + v.state->short_tiles, n_tiles);
+        for (uint32_t t = wg / G; t < n; t += gridDim.x / G) {
+            const uint32_t tile = v.tile_list[t < n_long ? t : n_tiles - 1u - (t - n_long)];
+            raycast_body<S, G, kDense, false>(v, cam, stamp, tiles_x, tiles_y, vertex, normal,
+                                              ((long long)tile * G + wg % G) * kRayWG + threadIdx.x);
+        }
+    } else {
+        raycast_body<S, G, kDense, kMode == kMarchMark>(v, cam, stamp, tiles_x, tiles_y, vertex, normal,
+                                                        (long long)wg * kRayWG + threadIdx.x);
+    }
 }
 
-template <typename S, bool kDense, bool kMark>
+template <typename S, bool kDense, MarchMode kMode>
 static void launch_group(int G, dim3 grid, hipStream_t s, const VolumeView &v, const Camera &cam, uint32_t stamp,
                          int tx, int ty, float4 *vertex, float4 *normal)
 {
     switch (G) {
-    case 1: hipLaunchKernelGGL((raycast_kernel<S, 1, kDense, kMark>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
-    case 2: hipLaunchKernelGGL((raycast_kernel<S, 2, kDense, kMark>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
-    case 4: hipLaunchKernelGGL((raycast_kernel<S, 4, kDense, kMark>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
-    case 16: hipLaunchKernelGGL((raycast_kernel<S, 16, kDense, kMark>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
-    default: hipLaunchKernelGGL((raycast_kernel<S, 8, kDense, kMark>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
+    case 1: hipLaunchKernelGGL((raycast_kernel<S, 1, kDense, kMode>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
+    case 2: hipLaunchKernelGGL((raycast_kernel<S, 2, kDense, kMode>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
+    case 4: hipLaunchKernelGGL((raycast_kernel<S, 4, kDense, kMode>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
+    case 16: hipLaunchKernelGGL((raycast_kernel<S, 16, kDense, kMode>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
+    default: hipLaunchKernelGGL((raycast_kernel<S, 8, kDense, kMode>), grid, dim3(kRayWG), 0, s, v, cam, stamp, tx, ty, vertex, normal); break;
     }
 }
 
 template <typename S, bool kDense>
-static void launch_group(bool mark, int G, dim3 grid, hipStream_t s, const VolumeView &v, const Camera &cam,
+static void launch_group(MarchMode mode, int G, dim3 grid, hipStream_t s, const VolumeView &v, const Camera &cam,
                          uint32_t stamp, int tx, int ty, float4 *vertex, float4 *normal)
 {
-    if (mark) launch_group<S, kDense, true>(G, grid, s, v, cam, stamp, tx, ty, vertex, normal);
-    else launch_group<S, kDense, false>(G, grid, s, v, cam, stamp, tx, ty, vertex, normal);
+    if (mode == kMarchMark) launch_group<S, kDense, kMarchMark>(G, grid, s, v, cam, stamp, tx, ty, vertex, normal);
+    else if (mode == kMarchList) launch_group<S, kDense, kMarchList>(G, grid, s, v, cam, stamp, tx, ty, vertex, normal);
+    else launch_group<S, kDense, kMarchAll>(G, grid, s, v, cam, stamp, tx, ty, vertex, normal);
 }
 
 hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, hipStream_t s)
@@ -145,13 +236,21 @@ hipError_t launch_march(const VolumeView &v, const Camera &camera, uint32_t stam
     const long long threads = (long long)tiles_x * tiles_y * 64 * G;
     const long long unit = (G <= 4 ? 8LL * G : 1LL) * kRayWG;   // whole groups of 8 tiles' wavefronts
     dim3 grid((unsigned)((threads + unit - 1) / unit * (unit / kRayWG)));
+    MarchMode mode = mark ? kMarchMark : kMarchAll;
+    const int n_tiles = tiles_x * tiles_y;
+    if (!mark && n_tiles >= kListTiles) {
+        mode = kMarchList;
+        grid = dim3(grid.x < kListGrid ? grid.x : kListGrid);
+        hipLaunchKernelGGL(tiles_kernel, dim3((n_tiles + kTilesPerGroup - 1) / kTilesPerGroup), dim3(256), 0, s, v,
+                           cam.width, cam.height, stamp, tiles_x, n_tiles, vertex, normal);
+    }
     const bool dense = v.block_index != nullptr;
     if (v.storage == TSDF_F16) {
-        if (dense) launch_group<__half, true>(mark, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
-        else launch_group<__half, false>(mark, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
+        if (dense) launch_group<__half, true>(mode, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
+        else launch_group<__half, false>(mode, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
     } else {
-        if (dense) launch_group<float, true>(mark, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
-        else launch_group<float, false>(mark, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
+        if (dense) launch_group<float, true>(mode, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
+        else launch_group<float, false>(mode, G, grid, s, v, cam, stamp, tiles_x, tiles_y, vertex, normal);
     }
     return hipGetLastError();
 }

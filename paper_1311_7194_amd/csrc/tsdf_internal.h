@@ -27,7 +27,8 @@ struct DeviceState {
     unsigned long long frames;
     unsigned long long total_candidates;
     unsigned long long footprint;   // blocks counted by the last raycast footprint query
-    uint32_t pad[54];
+    uint32_t long_tiles, short_tiles;   // raycast: entries of the tile list at its front and at its back
+    uint32_t pad[52];
 };
 static_assert(sizeof(DeviceState) == 256, "state line");
 
@@ -69,6 +70,7 @@ struct VolumeView {
     uint32_t *pool_keys;        // capacity entries: key of the block in each pool slot
     VoxelMasks *masks;          // capacity entries: inside and non-chi voxels of each block
     BlockRec *recs;             // capacity entries: the raycast's record of each block in view
+    uint32_t *tile_list;        // raycast: the frame's tiles with something to march
     uint32_t *tile_range;       // raycast: per 8x8 pixel tile (min depth bits, max depth bits)
     uint32_t *pix_range;        // raycast: per kCell x kCell pixel cell (min depth bits, max depth bits)
     uint32_t *mark_bits;        // one bit per virtual block: blocks a footprint query's rays read

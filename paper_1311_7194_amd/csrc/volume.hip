@@ -116,7 +116,7 @@ hipError_t launch_import(const VolumeView &v, const int32_t *keys, const void *T
 // ------------------------------------------------------------ layout
 
 struct Layout {
-    uint64_t state, ctr, hash, occupancy, block_index, cand_bits, cand_list, pixmap, pool_keys, masks, recs, tile_range, pix_range, mark_bits,
+    uint64_t state, ctr, hash, occupancy, block_index, cand_bits, cand_list, pixmap, pool_keys, masks, recs, tile_list, tile_range, pix_range, mark_bits,
         poolT, poolP, total;
     uint64_t bitmap_words, occ_words, tile_words, nblocks;
 };
@@ -180,6 +180,8 @@ static Layout layout_of(const tsdf_volume_desc *d)
     L.recs = off;
     off = align256(off + sizeof(BlockRec) * (uint64_t)d->capacity_blocks);
     L.tile_words = (uint64_t)((d->max_width + 7) / 8) * (uint64_t)((d->max_height + 7) / 8);
+    L.tile_list = off;
+    off = align256(off + 4ull * L.tile_words);
     L.tile_range = off;
     off = align256(off + 8ull * L.tile_words);
     L.pix_range = off;
@@ -397,6 +399,7 @@ tsdf_status tsdf_create_volume(const tsdf_volume_desc *desc, void *dev_buf, uint
     w.ctr = (Counters *)(v->base + L.ctr);
     w.pool_keys = (uint32_t *)(v->base + L.pool_keys);
     w.masks = (VoxelMasks *)(v->base + L.masks);
+    w.tile_list = (uint32_t *)(v->base + L.tile_list);
     w.tile_range = (uint32_t *)(v->base + L.tile_range);
     w.pix_range = (uint32_t *)(v->base + L.pix_range);
     w.recs = (BlockRec *)(v->base + L.recs);

@@ -197,3 +197,30 @@ def test_mesh_of_blocks_with_several_rounds_of_triangles(tsdf, storage, dense, m
     assert int(count) == n
     for got, want in zip((vid, t, xyz), mesh):
         assert np.array_equal(got.cpu().numpy(), want[:cap])
+
+
+@pytest.mark.parametrize("group,dense,close", [(1, True, False), (2, False, False), (4, True, True), (8, True, False),
+                                               (8, False, True), (16, True, False)])
+def test_large_frames_march_a_list_of_tiles(tsdf, gyroid, group, dense, close):
+    """A ragged frame large enough to march from a list of its tiles gives
+    bitwise the maps of the two half frames, which march every tile; with a
+    camera that sees mostly background, and one with blocks at its plane.
+    Every element is written (the maps start as NaN)."""
+    n, vs, _, _, (keys, T, P), _ = gyroid
+    W, H, cut = 1037, 509, 520
+    gv = tsdf.Volume((n, n, n), vs, (0.0, 0.0, 0.0), 4.0, 2048, 4096, 0, 1e-4, W, H, dense_index=dense)
+    gv.set_raycast_group(group)
+    gv.import_blocks(torch.from_numpy(keys), torch.from_numpy(T).float(), torch.from_numpy(P).float())
+    pose = look_at((0.5, 0.52, -0.02) if close else (-1.5, 2.0, -1.2), (0.5, 0.45, 0.5))
+    out = {}
+    for x0, x1 in ((0, W), (0, cut), (cut, W)):
+        K = Intrinsics(700.0, 700.0, 500.25 - x0, 250.5, x1 - x0, H)
+        maps = [torch.full((H, x1 - x0, 4), float("nan"), device="cuda") for _ in range(2)]
+        gv.raycast(K, pose, *maps)
+        torch.cuda.synchronize()
+        out[x0, x1] = maps
+    hits = int((out[0, W][0][..., 3] > 0).sum())
+    assert hits > 20000
+    assert close or hits < 0.9 * W * H
+    for m in range(2):
+        assert torch.equal(out[0, W][m], torch.cat((out[0, cut][m], out[cut, W][m]), 1))
