@@ -146,10 +146,11 @@ __constant__ McCases kMcCases = make_mc_cases();
 
 constexpr int kMcLanes = 64;         // one wavefront per block: lane (x, y) takes the cells of its z column
 constexpr int kTile = 9;             // corner tile edge
-// Single-wavefront workgroups striding over the pool, at most this many: blocks
-// differ in work, and a workgroup that gets few of them leaves the rest to the
-// dispatcher (56,000 blocks: 16384 workgroups 47 + 109 us, 32768 44 + 98 us,
-// 65536 the same), but an empty one costs too.
+// Single-wavefront workgroups striding over the pool: blocks differ in work, and
+// a workgroup that gets few of them leaves the rest to the dispatcher (56,000
+// blocks: 16384 workgroups 47 + 109 us, 32768 44 + 98 us, 65536 the same), but
+// an empty one costs too, so a small pool gets a quarter of its capacity (pools
+// are rarely full), or one round of resident wavefronts (8192).
 constexpr uint32_t kMcGrid = 32768;
 constexpr uint32_t kScanTile = 1024; // slots per first-level scan tile
 constexpr int kOwnerChunk = 512;     // output triangles of a block placed per round
@@ -531,7 +532,9 @@ tsdf_status tsdf_extract_mesh(tsdf_volume *vol, int64_t *vertex_id_dev, float *t
     const VolumeView v = volume_view(vol);
     const MeshWork w = mesh_work(v, work_dev);
     const uint32_t tiles = (v.capacity + kScanTile - 1) / kScanTile;
-    const dim3 grid(v.capacity < kMcGrid ? v.capacity : kMcGrid);
+    const uint32_t round = v.capacity < 8192u ? v.capacity : 8192u;
+    const uint32_t want = v.capacity / 4 > round ? v.capacity / 4 : round;
+    const dim3 grid(want < kMcGrid ? want : kMcGrid);
     const bool f16 = v.storage == TSDF_F16;
     if (f16)
         hipLaunchKernelGGL(mc_count_kernel<__half>, grid, dim3(kMcLanes), 0, stream, v, w.counts);
