@@ -164,14 +164,17 @@ tsdf_status tsdf_integrate_frame(tsdf_volume *vol, const float *depth_dev, const
  * no front-facing zero crossing or the normal is undefined.  The ray through
  * each pixel centre is sampled every half voxel from the camera centre; the
  * first bracket with F > 0 >= F over valid trilinear samples is refined by
- * six quaternary search steps and a final linear interpolation; the normal is the central difference of F one voxel apart
- * along the world axes. */
+ * quaternary search steps, on the ray's cubic once the bracket lies in one
+ * cell, and a final linear interpolation; the normal is the central difference
+ * of F one voxel apart along the world axes. */
 tsdf_status tsdf_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, const double pose_c2w[12],
                          float *vertex_dev, float *normal_dev, hipStream_t stream);
 
-/* The raycast above, also counting the blocks whose voxels the rays' march
- * samples are based in (each block once, however many rays read it).  This
- * is the data the raycast must read from the pool: the measure of its
+/* The raycast above, also counting the blocks that the samples it evaluates
+ * are based in (each block once, however many rays read it; samples decided
+ * from the blocks' bit records alone are not evaluated, and a group of lanes
+ * evaluates a step's together, so the count depends a little on the group
+ * size).  This is the data the raycast reads from the pool: the measure of its
  * algorithmic traffic.  The maps are bitwise those of tsdf_raycast.  Runs an
  * instrumented copy of the march (not the one tsdf_raycast times) and
  * synchronises `stream` to return *blocks_out. */
