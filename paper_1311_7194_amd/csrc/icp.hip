@@ -528,14 +528,26 @@ __global__ __launch_bounds__(kIcpThreads) void icp_solve_kernel(const double *__
         }
         res->pose[lane] = P;   // (may be the current pose's own record: read before)
     }
-    // eigenvalues per pair, ascending
+    // eigenvalues per pair, ascending, by an insertion sort in every lane: all six
+    // are written whatever they are (a rank by comparisons has gaps with NaN)
+    if (lane < 6) L.lam[e] = N > 0.0 ? lam / N : 0.0;
+    wave_sync();
     if (lane < 6) {
-        int rank = 0;
-        for (int q = 0; q < 6; ++q) {
-            const double o = N > 0.0 ? L.lam[q] : 0.0;
-            rank += o < lam || (o == lam && q < lane);
-        }
-        res->lambda[rank] = N > 0.0 ? lam / N : 0.0;
+        double o[6], mine = 0.0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) o[q] = L.lam[q];
+#pragma unroll
+        for (int q = 1; q < 6; ++q)
+#pragma unroll
+            for (int f = q; f > 0; --f) {
+                const bool swap = o[f - 1] > o[f];
+                const double lo = swap ? o[f] : o[f - 1], hi = swap ? o[f - 1] : o[f];
+                o[f - 1] = lo;
+                o[f] = hi;
+            }
+#pragma unroll
+        for (int q = 0; q < 6; ++q) mine = q == lane ? o[q] : mine;
+        res->lambda[lane] = mine;
         res->b[lane] = L.b[lane];
         res->x[lane] = lane < 3 ? at3(x, lane) : at3(x + 3, lane - 3);
     }

@@ -49,3 +49,41 @@ def test_solution_residual_over_random_systems(tsdf):
     print(f"[icp] solution residual: median {np.median(res):.2e}, 90 % {np.quantile(res, 0.9):.2e}, "
           f"largest {max(res):.2e}", flush=True)
     assert np.median(res) <= 5e-16
+
+
+@pytest.mark.parametrize("shrink", [False, True])
+@pytest.mark.parametrize("at", [5, -1])
+@pytest.mark.parametrize("normal", [(1.0, 0.0, 0.0), (1.0, 1.0, 0.0), (0.0, 1.0, -1.0)])
+def test_infinite_model_normal(tsdf, normal, at, shrink):
+    """A model normal with infinite components passes the rejection (inf >= inf).
+    All six eigenvalues are written: the sweeps cannot start, so they are the
+    system's diagonal, in the order of an insertion sort."""
+    K = Intrinsics(20.0, 20.0, 7.5, 3.5, 16, 8)
+    rng = np.random.default_rng(3)
+    depth = (1.0 + 0.01 * rng.random((8, 16))).astype(np.float32)
+    v, n, ok = O.live_points(depth, K.as_tuple())
+    MV, MN = np.ones((8, 16, 4), np.float32), np.ones((8, 16, 4), np.float32)
+    MV[..., :3] = v + 0.01 * rng.normal(size=v.shape)
+    with np.errstate(invalid="ignore"):
+        MN[..., :3] = n / np.linalg.norm(n, axis=-1, keepdims=True)
+    agrees = ((n * np.array(normal) > 0) | (np.array(normal) == 0)).all(-1)
+    one = np.argwhere(ok & agrees)[at]   # a pixel whose normal agrees with it
+    MN[one[0], one[1], :3] = [x * np.inf if x else 0.0 for x in normal]
+    params = O.IcpParams(dist_max=1.0, cos_min=0.5, theta=-1.0, shrink=shrink)
+    with np.errstate(invalid="ignore"):
+        p, _, _, _ = O.associate(depth, K.as_tuple(), MV, MN, IDENTITY, IDENTITY, params)
+    assert len(p) > 50
+    icp = tsdf.Icp(K, 1.0, 0.5, -1.0, shrink)
+    icp.results.fill_(-7.0)
+    icp.run(torch.from_numpy(depth).cuda(), torch.from_numpy(MV).cuda(), torch.from_numpy(MN).cuda(), IDENTITY,
+            IDENTITY, 1)
+    torch.cuda.synchronize()
+    r = icp.result(0)
+    assert r["N"] == len(p)
+    want = [float(x) for x in np.diag(r["C"]) / r["N"]]
+    for e in range(1, 6):
+        f = e
+        while f > 0 and want[f - 1] > want[f]:
+            want[f - 1], want[f] = want[f], want[f - 1]
+            f -= 1
+    assert np.array_equal(r["lam"], np.array(want), equal_nan=True)
