@@ -447,14 +447,17 @@ __global__ __launch_bounds__(kIcpThreads) void icp_solve_kernel(const double *__
     row(r, ri, rw);
     row(c, ci, cw);
     const double Sr = r < 3 ? at3(S, r) : 1.0, Sc = c < 3 ? at3(S, c) : 1.0;
+    // (the terms in M are left out where there is no M, not multiplied by zero:
+    // an infinite normal makes some sums infinite and must not reach the others)
+    const bool rm = scaled && r < 3, cm = scaled && c < 3;
     double A = 0.0, b = 0.0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         double x = 0.0;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) x += cw[j] * sum_gg(L.tot, ri[i], ci[j]);
-        A += rw[i] * x;
-        b += rw[i] * L.tot[21 + ri[i]];
+        for (int j = 0; j < 3; ++j) x += j == 0 || cm ? cw[j] * sum_gg(L.tot, ri[i], ci[j]) : 0.0;
+        A += i == 0 || rm ? rw[i] * x : 0.0;
+        b += i == 0 || rm ? rw[i] * L.tot[21 + ri[i]] : 0.0;
     }
     A /= Sr * Sc;
     b = -b / Sr;

@@ -56,8 +56,11 @@ def test_solution_residual_over_random_systems(tsdf):
 @pytest.mark.parametrize("normal", [(1.0, 0.0, 0.0), (1.0, 1.0, 0.0), (0.0, 1.0, -1.0)])
 def test_infinite_model_normal(tsdf, normal, at, shrink):
     """A model normal with infinite components passes the rejection (inf >= inf).
-    All six eigenvalues are written: the sweeps cannot start, so they are the
-    system's diagonal, in the order of an insertion sort."""
+    Without scaling, every entry of the system that does not hold one of its
+    infinite terms stays the finite sum, and all six eigenvalues are written:
+    the sweeps cannot start, so they are the system's diagonal, in the order of
+    an insertion sort.  With scaling the matrix has no entry left to rely on, but
+    the eigenvalues are still its diagonal."""
     K = Intrinsics(20.0, 20.0, 7.5, 3.5, 16, 8)
     rng = np.random.default_rng(3)
     depth = (1.0 + 0.01 * rng.random((8, 16))).astype(np.float32)
@@ -71,8 +74,11 @@ def test_infinite_model_normal(tsdf, normal, at, shrink):
     MN[one[0], one[1], :3] = [x * np.inf if x else 0.0 for x in normal]
     params = O.IcpParams(dist_max=1.0, cos_min=0.5, theta=-1.0, shrink=shrink)
     with np.errstate(invalid="ignore"):
-        p, _, _, _ = O.associate(depth, K.as_tuple(), MV, MN, IDENTITY, IDENTITY, params)
-    assert len(p) > 50
+        p, q, nn, _ = O.associate(depth, K.as_tuple(), MV, MN, IDENTITY, IDENTITY, params)
+        g = np.concatenate([O._cross(p, nn), nn], 1)
+        C = np.array([[(g[:, a] * g[:, b]).sum() for b in range(6)] for a in range(6)])
+        b = -np.array([(g[:, a] * O._dot(p - q, nn)).sum() for a in range(6)])
+    assert len(p) > 50 and not np.isfinite(C).all()
     icp = tsdf.Icp(K, 1.0, 0.5, -1.0, shrink)
     icp.results.fill_(-7.0)
     icp.run(torch.from_numpy(depth).cuda(), torch.from_numpy(MV).cuda(), torch.from_numpy(MN).cuda(), IDENTITY,
@@ -80,6 +86,12 @@ def test_infinite_model_normal(tsdf, normal, at, shrink):
     torch.cuda.synchronize()
     r = icp.result(0)
     assert r["N"] == len(p)
+    if not shrink:
+        for got, want in ((r["C"], C), (r["b"], b)):
+            fin = np.isfinite(want)
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            assert np.abs(got[fin] - want[fin]).max(initial=0.0) <= 1e-9 * np.abs(want[fin]).max(initial=1.0)
+            assert np.array_equal(got[~fin & ~np.isnan(want)], want[~fin & ~np.isnan(want)])
     want = [float(x) for x in np.diag(r["C"]) / r["N"]]
     for e in range(1, 6):
         f = e
