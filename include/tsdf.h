@@ -164,9 +164,8 @@ tsdf_status tsdf_integrate_frame(tsdf_volume *vol, const float *depth_dev, const
  * no front-facing zero crossing or the normal is undefined.  The ray through
  * each pixel centre is sampled every half voxel from the camera centre; the
  * first bracket with F > 0 >= F over valid trilinear samples is refined by
- * quaternary search steps, on the ray's cubic once the bracket lies in one
- * cell, and a final linear interpolation; the normal is the central difference
- * of F one voxel apart along the world axes. */
+ * six quaternary search steps and a final linear interpolation; the normal is
+ * the central difference of F one voxel apart along the world axes. */
 tsdf_status tsdf_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, const double pose_c2w[12],
                          float *vertex_dev, float *normal_dev, hipStream_t stream);
 

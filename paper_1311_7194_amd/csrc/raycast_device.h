@@ -755,106 +755,109 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     }
 
     // ---- refinement: quaternary search inside [s_lo, s_hi] (F_lo > 0 >= F_hi),
-    // up to six steps that shrink the bracket 4096-fold.  Each looks at the 3
-    // inner quarter points (point m by lane m % G of the group, in ceil(3 / G)
-    // rounds), so the points and hence the result do not depend on the group
-    // size.  Inside one cell F along the ray is a cubic: once a step's bracket
-    // lies in one (most rays: the second step's), the cubic through the step's
-    // points stands in for the volume, and the search goes on in registers.
+    // six steps that shrink the bracket 4096-fold.  Each looks at the 3 inner
+    // quarter points (point m by lane m % G of the group, in ceil(3 / G) rounds),
+    // so the points and hence the result do not depend on the group size.  Inside
+    // one cell F along the ray is a cubic: once a step's bracket lies in one (most
+    // rays: the second step's), the steps that are left are taken on the cubic
+    // through its points, in registers, by all of the wavefront's rays at once.
+    // The cubic only says where to look: F is then evaluated at both ends of its
+    // bracket, along with the normal's samples, and where they do not enclose the
+    // crossing (a root within rounding of an end) the ray goes on with sampled
+    // steps.  The crossing is that of six sampled steps, whatever the cubic's
+    // rounding (taken from the cubic, it was off by 1.2 times as much).
     constexpr int kPts = 3, kSteps = 6, kRounds = (kPts + G - 1) / G;
     double a = s_lo, b = s_hi;
     float Fa = F_lo, Fb = F_hi;
-    bool refine = hit, cubic = false;
-    // the cubic through f0.. at u = 0..3 (Newton's forward differences); the
-    // bracket [a, b] is [u0, u0 + 1]
-    float f0 = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f, u0 = 0.0f;
-    for (int it = 0; it < kSteps; ++it) {
-        if (!__ballot(refine)) break;
-        float Fp[kPts];
+    bool refine = hit;                        // takes sampled steps
+    bool cubic = false, sampled = false;      // has a cubic to check; does without one
+    int left = kSteps;
+    // ---- normal: central differences one voxel apart, lanes share the 6 samples
+    float g[3] = {0.f, 0.f, 0.f};
+    bool ok = false, fresh = hit;             // fresh: its normal is still to be taken
+    while (__ballot(fresh)) {
+        // the cubic through f0.. at u = 0..3 (Newton's forward differences); the
+        // bracket [a, b] is [u0, u0 + 1]
+        float f0 = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f, u0 = 0.0f;
+        while (__ballot(refine)) {
+            float Fp[kPts];
 #pragma unroll
-        for (int rd = 0; rd < kRounds; ++rd) {
-            const int m = rd * G + j;
-            float Fm = kNaN;
-            if (refine && m < kPts) {
-                double qm[3];
-                q_at(r, a + (b - a) * (double)(m + 1) * 0.25, qm);
-                Fm = sample<S, kDense>(v, cache, qm);
+            for (int rd = 0; rd < kRounds; ++rd) {
+                const int m = rd * G + j;
+                float Fm = kNaN;
+                if (refine && m < kPts) {
+                    double qm[3];
+                    q_at(r, a + (b - a) * (double)(m + 1) * 0.25, qm);
+                    Fm = sample<S, kDense>(v, cache, qm);
+                }
+#pragma unroll
+                for (int mm = rd * G; mm < (rd + 1) * G && mm < kPts; ++mm)
+                    Fp[mm] = __shfl(Fm, group_lane<G>(lane, mm - rd * G));
             }
-#pragma unroll
-            for (int mm = rd * G; mm < (rd + 1) * G && mm < kPts; ++mm)
-                Fp[mm] = __shfl(Fm, group_lane<G>(lane, mm - rd * G));
-        }
-        if (refine) {
+            if (!refine) continue;
             // an invalid point inside the bracket: keep the bracket
             if (Fp[0] != Fp[0] || Fp[1] != Fp[1] || Fp[2] != Fp[2]) {
                 refine = false;
-            } else {
-                // first non-positive point: the root lies in (point k - 1, point k]
-                const bool n0 = Fp[0] <= 0.0f, n1 = Fp[1] <= 0.0f, n2 = Fp[2] <= 0.0f;
-                const int k = n0 ? 0 : n1 ? 1 : n2 ? 2 : 3;
-                double qa[3], qb[3];
-                q_at(r, a, qa);
-                q_at(r, b, qb);
-                cubic = floor(qa[0]) == floor(qb[0]) && floor(qa[1]) == floor(qb[1]) && floor(qa[2]) == floor(qb[2]);
-                refine = !cubic;
-                // the four of the five points around the root's quarter
-                const bool upper = k >= 2;
-                const float g1 = upper ? Fp[1] : Fp[0], g2 = upper ? Fp[2] : Fp[1], g3 = upper ? Fb : Fp[2];
-                f0 = upper ? Fp[0] : Fa;
-                d1 = g1 - f0;
-                const float e1 = g2 - g1, e2 = g3 - g2, c1 = e1 - d1;
-                d2 = 0.5f * c1;
-                d3 = ((e2 - e1) - c1) * (1.0f / 6.0f);
-                u0 = k == 0 || k == 2 ? (upper ? 1.0f : 0.0f) : (upper ? 2.0f : 1.0f);
-                Fb = n0 ? Fp[0] : n1 ? Fp[1] : n2 ? Fp[2] : Fb;
-                Fa = n0 ? Fa : n1 ? Fp[0] : n2 ? Fp[1] : Fp[2];
-                const double w = (b - a) * 0.25;
-                a += w * (double)k;
-                b = a + w;
+                continue;
             }
+            // first non-positive point: the root lies in (point k - 1, point k]
+            const bool n0 = Fp[0] <= 0.0f, n1 = Fp[1] <= 0.0f, n2 = Fp[2] <= 0.0f;
+            const int k = n0 ? 0 : n1 ? 1 : n2 ? 2 : 3;
+            double qa[3], qb[3];
+            q_at(r, a, qa);
+            q_at(r, b, qb);
+            --left;
+            cubic = !sampled && left > 0 && floor(qa[0]) == floor(qb[0]) && floor(qa[1]) == floor(qb[1]) &&
+                    floor(qa[2]) == floor(qb[2]);
+            refine = !cubic && left > 0;
+            // the four of the five points around the root's quarter
+            const bool upper = k >= 2;
+            const float g1 = upper ? Fp[1] : Fp[0], g2 = upper ? Fp[2] : Fp[1], g3 = upper ? Fb : Fp[2];
+            f0 = upper ? Fp[0] : Fa;
+            d1 = g1 - f0;
+            const float e1 = g2 - g1, e2 = g3 - g2, c1 = e1 - d1;
+            d2 = 0.5f * c1;
+            d3 = ((e2 - e1) - c1) * (1.0f / 6.0f);
+            u0 = k == 0 || k == 2 ? (upper ? 1.0f : 0.0f) : (upper ? 2.0f : 1.0f);
+            Fb = n0 ? Fp[0] : n1 ? Fp[1] : n2 ? Fp[2] : Fb;
+            Fa = n0 ? Fa : n1 ? Fp[0] : n2 ? Fp[1] : Fp[2];
+            const double w = (b - a) * 0.25;
+            a += w * (double)k;
+            b = a + w;
         }
-    }
-    if (__ballot(cubic)) {
-        // four more steps on the cubic: the bracket is then at most a 2048th of
-        // a voxel
-        float t = 0.0f, dt = 1.0f;   // the bracket is u0 + [t, t + dt]
+        double ca = a, cb = b;
+        float cFa = Fa, cFb = Fb;
+        if (__ballot(cubic)) {
+            float t = 0.0f, dt = 1.0f;   // the bracket is u0 + [t, t + dt]
+            auto P = [&](float u) { return fmaf(u, fmaf(u - 1.0f, fmaf(u - 2.0f, d3, d2), d1), f0); };
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            dt *= 0.25f;
-            float p[kPts];
-#pragma unroll
-            for (int m = 0; m < kPts; ++m) {
-                const float u = u0 + (t + (float)(m + 1) * dt);
-                p[m] = fmaf(u, fmaf(u - 1.0f, fmaf(u - 2.0f, d3, d2), d1), f0);
+            for (int st = 0; st < kSteps - 1; ++st) {
+                const float q = 0.25f * dt;
+                const float p0 = P(u0 + (t + q)), p1 = P(u0 + (t + 2.0f * q)), p2 = P(u0 + (t + 3.0f * q));
+                if (st < left) {
+                    dt = q;
+                    t = fmaf(p0 <= 0.0f ? 0.0f : p1 <= 0.0f ? 1.0f : p2 <= 0.0f ? 2.0f : 3.0f, q, t);
+                }
             }
-            const bool n0 = p[0] <= 0.0f, n1 = p[1] <= 0.0f, n2 = p[2] <= 0.0f;
             if (cubic) {
-                Fb = n0 ? p[0] : n1 ? p[1] : n2 ? p[2] : Fb;
-                Fa = n0 ? Fa : n1 ? p[0] : n2 ? p[1] : p[2];
+                const double w = b - a;
+                ca = a + w * (double)t;
+                cb = ca + w * (double)dt;
+                cFa = P(u0 + t);
+                cFb = P(u0 + (t + dt));
             }
-            t = fmaf(n0 ? 0.0f : n1 ? 1.0f : n2 ? 2.0f : 3.0f, dt, t);
         }
-        if (cubic) {
-            const double w = b - a;
-            a += w * (double)t;
-            b = a + w * (double)dt;
-        }
-    }
-    const double sh = hit ? ((Fa - Fb) > 0.0f ? a + (b - a) * ((double)Fa / ((double)Fa - (double)Fb)) : 0.5 * (a + b))
-                          : 0.0;
-    // ---- normal: central differences one voxel apart, lanes share the 6 samples
-    float g[3] = {0.f, 0.f, 0.f};
-    bool ok = hit;
-    if (__ballot(hit)) {
         double qh[3];
-        q_at(r, sh, qh);
-        float Fs[6];
+        q_at(r, cFa - cFb > 0.0f ? ca + (cb - ca) * ((double)cFa / ((double)cFa - (double)cFb)) : 0.5 * (ca + cb), qh);
+        float Fs[8];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) Fs[e] = kNaN;
-        // sample e in {+x, -x, +y, -y, +z, -z} is taken by lane e % G of the
-        // group.  A lane taking several samples looks up every block before it
-        // reads a voxel, so the loads are all in flight together.
-        constexpr int kPer = (6 + G - 1) / G;
+        for (int e = 0; e < 8; ++e) Fs[e] = kNaN;
+        // samples {+x, -x, +y, -y, +z, -z} around the crossing and the two ends of
+        // the cubic's bracket, sample e by lane e % G of the group.  A lane taking
+        // several samples looks up every block before it reads a voxel, so the
+        // loads are all in flight together (with one or two lanes per ray the last
+        // two samples follow by themselves: 176 VGPRs otherwise).
+        constexpr int kFirst = G <= 2 ? 6 : 8, kPer = (kFirst + G - 1) / G;
         int nc[kPer][3];
         float nf[kPer][3];
         bool nin[kPer];
@@ -862,11 +865,17 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
             const int e = j + t * G;
-            nin[t] = hit && e < 6;
+            nin[t] = fresh && (e < 6 || (cubic && e < kFirst));
             ncache[t] = cache;
             if (nin[t]) {
-                double qe[3] = {qh[0], qh[1], qh[2]};
-                qe[e >> 1] += (e & 1) ? -1.0 : 1.0;
+                double qe[3];
+                if (e < 6) {
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) qe[x] = qh[x];
+                    qe[e >> 1] += (e & 1) ? -1.0 : 1.0;
+                } else {
+                    q_at(r, e == 6 ? ca : cb, qe);
+                }
                 nin[t] = stencil(v, qe, nc[t], nf[t]);
                 if (nin[t]) enter_block<kDense>(v, ncache[t], nc[t]);
             }
@@ -876,19 +885,41 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             float Fv;
             if (nin[t] && interp<S>(v, ncache[t], nc[t], nf[t], Fv)) {
 #pragma unroll
-                for (int e = 0; e < 6; ++e)
+                for (int e = 0; e < 8; ++e)
                     if (e == j + t * G) Fs[e] = Fv;
             }
         }
+        if constexpr (kFirst == 6) {
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            Fs[e] = __shfl(Fs[e], group_lane<G>(lane, e % G));
-            ok = ok && Fs[e] == Fs[e];   // NaN: invalid
+            for (int e = 6 + j; e < 8; e += G)
+                if (cubic) {
+                    double qe[3];
+                    q_at(r, e == 6 ? ca : cb, qe);
+                    Fs[e] = sample<S, kDense>(v, cache, qe);
+                }
         }
-        g[0] = Fs[0] - Fs[1];
-        g[1] = Fs[2] - Fs[3];
-        g[2] = Fs[4] - Fs[5];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Fs[e] = __shfl(Fs[e], group_lane<G>(lane, e % G));
+        if (fresh) {
+            refine = cubic && !(Fs[6] > 0.0f && Fs[7] <= 0.0f);
+            if (cubic && !refine) {
+                a = ca;
+                b = cb;
+                Fa = Fs[6];
+                Fb = Fs[7];
+            }
+            fresh = sampled = refine;
+            cubic = false;
+            ok = true;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) ok = ok && Fs[e] == Fs[e];   // NaN: invalid
+            g[0] = Fs[0] - Fs[1];
+            g[1] = Fs[2] - Fs[3];
+            g[2] = Fs[4] - Fs[5];
+        }
     }
+    const double sh = hit ? ((Fa - Fb) > 0.0f ? a + (b - a) * ((double)Fa / ((double)Fa - (double)Fb)) : 0.5 * (a + b))
+                          : 0.0;
     if (active && j == 0) {
         float4 vout = make_float4(0.f, 0.f, 0.f, 0.f), nout = vout;
         const float gl = sqrtf(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);

@@ -1,0 +1,105 @@
+"""The raycast where its shortcuts could show: the refinement inside a cell
+(needs an MI355X)."""
+
+import numpy as np
+import pytest
+import torch
+
+from synthetic import Intrinsics, look_at
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tsdf():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1311_7194_amd as m
+
+    m.lib()
+    return m
+
+
+def trilinear(T, q, dtype):
+    """F at the points q of one 8^3 block, every interpolation rounded once to dtype."""
+    c = np.minimum(np.floor(q).astype(int), 6)
+    fr = (q - c).astype(dtype)
+
+    def lerp(a, b, t):
+        return (a.astype(np.float64) + t.astype(np.float64) * (b - a).astype(dtype)).astype(dtype)
+
+    v = {k: T[c[:, 0] + (k & 1), c[:, 1] + (k >> 1 & 1), c[:, 2] + (k >> 2)].astype(dtype) for k in range(8)}
+    x = [lerp(v[k], v[k + 1], fr[:, 0]) for k in (0, 2, 4, 6)]
+    return lerp(lerp(x[0], x[1], fr[:, 1]), lerp(x[2], x[3], fr[:, 1]), fr[:, 2])
+
+
+def sampled_search(T, o, d):
+    """Crossings of the rays o + s d (voxel-centre coordinates) as tsdf_raycast
+    defines them, every point evaluated from the voxels in single precision."""
+    n, h = len(d), 0.5
+    lo, prev = np.full(n, np.nan), np.full(n, np.nan)
+    for k in range(1, 60):
+        q = o + k * h * d
+        ok = ((q >= 0) & (q < 7)).all(1)
+        F = np.full(n, np.nan)
+        F[ok] = trilinear(T, q[ok], np.float32)
+        lo[np.isnan(lo) & (prev > 0) & (F <= 0)] = (k - 1) * h
+        prev = F
+    hit = ~np.isnan(lo)
+    d, a = d[hit], lo[hit]
+    b = a + h
+    at = lambda s: trilinear(T, o + s[:, None] * d, np.float32)   # noqa: E731
+    Fa, Fb = at(a), at(b)
+    for _ in range(6):
+        p = [at(a + (b - a) * (m + 1) * 0.25) for m in range(3)]
+        k = np.where(p[0] <= 0, 0, np.where(p[1] <= 0, 1, np.where(p[2] <= 0, 2, 3)))
+        w = (b - a) * 0.25
+        Fa, Fb = np.choose(k, [Fa] + p), np.choose(k, p + [Fb])
+        a = a + w * k
+        b = a + w
+    return hit, a + (b - a) * (Fa.astype(np.float64) / (Fa.astype(np.float64) - Fb))
+
+
+@pytest.mark.parametrize("group,dense", [(1, True), (4, False), (8, True)])
+def test_refinement_is_the_search_over_sampled_points(tsdf, group, dense):
+    """Strongly curved cells around the world's origin, where a vertex is stored
+    to 6e-8 voxel: the crossings are those of the search over sampled points,
+    within that rounding (1.2e-7 along a ray) but for the rays whose root lies
+    so near a point that the sign there is rounding (under one in a hundred),
+    and |F| at them is no larger than at the search's own."""
+    W = H = 64
+    K = Intrinsics(360.0, 360.0, W / 2.0, H / 2.0, W, H)
+    gv = tsdf.Volume((8, 8, 8), 1.0, (-4.0, -4.0, -4.0), 4.0, 4, 8, 0, 1e-4, W, H, dense_index=dense)
+    gv.set_raycast_group(group)
+    c = np.arange(8) - 3.5
+    x, y, z = np.meshgrid(c, c, c, indexing="ij")
+    inner = (np.abs(x) < 2) & (np.abs(y) < 2) & (np.abs(z) < 2)
+    err, res, ref = [], [], []
+    for seed in range(16):
+        rng = np.random.default_rng(seed)
+        T = rng.uniform(0.2, 0.9, (8, 8, 8))
+        T[inner] = rng.uniform(-0.9, 0.9, inner.sum())
+        T = T.astype(np.float32)
+        gv.import_blocks(torch.zeros((1, 3), dtype=torch.int32),
+                         torch.from_numpy(np.ascontiguousarray(T.transpose(2, 1, 0))).reshape(1, 512),
+                         torch.full((1, 512), 1e-3))
+        pose = look_at(np.array([-8.0, 9.0, -10.0]) + rng.normal(size=3), (0.0, 0.0, 0.0))
+        vert, _ = gv.raycast(K, pose)
+        torch.cuda.synchronize()
+        vert = vert.cpu().numpy().reshape(-1, 4)
+        j, i = np.meshgrid(np.arange(H), np.arange(W), indexing="ij")
+        d = np.stack([(i - K.cx) / K.fx, (j - K.cy) / K.fy, np.ones((H, W))], -1).reshape(-1, 3) @ pose[:, :3].T
+        d /= np.linalg.norm(d, axis=1, keepdims=True)
+        hit, s = sampled_search(T, pose[:, 3] + 3.5, d)
+        want = np.full((W * H, 3), np.nan)
+        want[hit] = pose[:, 3] + s[:, None] * d[hit]
+        both = (vert[:, 3] > 0) & hit & (np.abs(want) < 1.4).all(1)
+        err.append(np.linalg.norm(vert[both, :3] - want[both], axis=1))
+        res.append(np.abs(trilinear(T, vert[both, :3] + 3.5, np.float64)))
+        ref.append(np.abs(trilinear(T, want[both].astype(np.float32) + 3.5, np.float64)))
+    err, res, ref = (np.concatenate(v) for v in (err, res, ref))
+    print(f"[raycast] {len(err)} crossings, {np.mean(err > 1.2e-7):.4f} further than 1.2e-7 voxel from the search's; "
+          f"mean |F| {res.mean():.3e}, at the search's {ref.mean():.3e}", flush=True)
+    assert len(err) > 5000
+    assert np.mean(err > 1.2e-7) <= 0.01
+    assert res.mean() <= 1.02 * ref.mean()
