@@ -1,5 +1,5 @@
-"""The raycast where its shortcuts could show: the refinement inside a cell
-(needs an MI355X)."""
+"""The raycast where its shortcuts could show: the refinement inside a cell, rays
+with many brackets that are none (needs an MI355X)."""
 
 import numpy as np
 import pytest
@@ -21,8 +21,8 @@ def tsdf():
 
 
 def trilinear(T, q, dtype):
-    """F at the points q of one 8^3 block, every interpolation rounded once to dtype."""
-    c = np.minimum(np.floor(q).astype(int), 6)
+    """F at the points q of a grid, every interpolation rounded once to dtype."""
+    c = np.minimum(np.floor(q).astype(int), np.array(T.shape) - 2)
     fr = (q - c).astype(dtype)
 
     def lerp(a, b, t):
@@ -36,11 +36,11 @@ def trilinear(T, q, dtype):
 def sampled_search(T, o, d):
     """Crossings of the rays o + s d (voxel-centre coordinates) as tsdf_raycast
     defines them, every point evaluated from the voxels in single precision."""
-    n, h = len(d), 0.5
+    n, h, last = len(d), 0.5, len(T) - 1
     lo, prev = np.full(n, np.nan), np.full(n, np.nan)
-    for k in range(1, 60):
+    for k in range(1, 160):
         q = o + k * h * d
-        ok = ((q >= 0) & (q < 7)).all(1)
+        ok = ((q >= 0) & (q < last)).all(1)
         F = np.full(n, np.nan)
         F[ok] = trilinear(T, q[ok], np.float32)
         lo[np.isnan(lo) & (prev > 0) & (F <= 0)] = (k - 1) * h
@@ -58,6 +58,12 @@ def sampled_search(T, o, d):
         a = a + w * k
         b = a + w
     return hit, a + (b - a) * (Fa.astype(np.float64) / (Fa.astype(np.float64) - Fb))
+
+
+def rays(K, pose):
+    j, i = np.meshgrid(np.arange(K.height), np.arange(K.width), indexing="ij")
+    d = np.stack([(i - K.cx) / K.fx, (j - K.cy) / K.fy, np.ones(i.shape)], -1).reshape(-1, 3) @ pose[:, :3].T
+    return d / np.linalg.norm(d, axis=1, keepdims=True)
 
 
 @pytest.mark.parametrize("group,dense", [(1, True), (4, False), (8, True)])
@@ -87,9 +93,7 @@ def test_refinement_is_the_search_over_sampled_points(tsdf, group, dense):
         vert, _ = gv.raycast(K, pose)
         torch.cuda.synchronize()
         vert = vert.cpu().numpy().reshape(-1, 4)
-        j, i = np.meshgrid(np.arange(H), np.arange(W), indexing="ij")
-        d = np.stack([(i - K.cx) / K.fx, (j - K.cy) / K.fy, np.ones((H, W))], -1).reshape(-1, 3) @ pose[:, :3].T
-        d /= np.linalg.norm(d, axis=1, keepdims=True)
+        d = rays(K, pose)
         hit, s = sampled_search(T, pose[:, 3] + 3.5, d)
         want = np.full((W * H, 3), np.nan)
         want[hit] = pose[:, 3] + s[:, None] * d[hit]
@@ -103,3 +107,37 @@ def test_refinement_is_the_search_over_sampled_points(tsdf, group, dense):
     assert len(err) > 5000
     assert np.mean(err > 1.2e-7) <= 0.01
     assert res.mean() <= 1.02 * ref.mean()
+
+
+def test_candidates_without_a_crossing(tsdf):
+    """Voxels of random values, one in twenty below zero: most steps of a ray
+    see cells where a bracket can begin and end, few of them have a crossing.
+    Every group size finds the crossings of the search over all samples and
+    gives bitwise the same maps (coordinates up to 16: rounding 1e-6 apart)."""
+    n, W, H = 32, 96, 80
+    K = Intrinsics(150.0, 150.0, 47.3, 39.6, W, H)
+    rng = np.random.default_rng(11)
+    T = rng.uniform(0.05, 0.95, (n, n, n)).astype(np.float32)
+    T[rng.random(T.shape) < 0.05] *= -1
+    gv = tsdf.Volume((n, n, n), 1.0, (-16.0, -16.0, -16.0), 4.0, 64, 128, 0, 1e-4, W, H)
+    m = n // 8
+    keys = [(x, y, z) for x in range(m) for y in range(m) for z in range(m)]
+    blocks = [T[8 * x:8 * x + 8, 8 * y:8 * y + 8, 8 * z:8 * z + 8].transpose(2, 1, 0).reshape(-1) for x, y, z in keys]
+    gv.import_blocks(torch.tensor(keys, dtype=torch.int32), torch.from_numpy(np.stack(blocks)),
+                     torch.full((len(keys), 512), 1e-3))
+    pose = look_at((-38.0, 21.0, -25.0), (0.0, 0.0, 0.0))
+    d = rays(K, pose)
+    hit, s = sampled_search(T, pose[:, 3] + 15.5, d)
+    want = pose[:, 3] + s[:, None] * d[hit]
+    inner = (np.abs(want) < 14.4).all(1)   # every sample of the normal in the grid
+    maps = []
+    for group in (1, 2, 4, 8, 16):
+        gv.set_raycast_group(group)
+        maps.append([t.cpu().numpy().reshape(-1, 4) for t in gv.raycast(K, pose)])
+        assert np.array_equal(maps[0][0], maps[-1][0]) and np.array_equal(maps[0][1], maps[-1][1]), group
+    vert = maps[0][0]
+    got = vert[hit, 3] > 0
+    assert inner.sum() > 3000 and not (vert[~hit, 3] > 0).any()
+    assert np.mean(got[inner]) > 0.999
+    assert np.linalg.norm(vert[hit, :3] - want, axis=1)[got].max() < 1e-4   # a bracket of the search
+    assert np.mean(np.linalg.norm(vert[hit, :3] - want, axis=1)[got] < 4e-6) > 0.99
