@@ -199,10 +199,13 @@ tsdf_status tsdf_set_update_rule(tsdf_volume *vol, int32_t rule, int32_t weight_
 tsdf_status tsdf_set_raycast_group(tsdf_volume *vol, int32_t group);
 int32_t tsdf_get_raycast_group(const tsdf_volume *vol);
 
-/* Autotuner: raycasts the current volume from pose_c2w with every group size
- * (`reps` timed launches each after one warm-up, HIP events on `stream`),
- * keeps the fastest for later raycasts and reports it with its mean time in
- * milliseconds.  Synchronises `stream`.  The outputs hold the last raycast. */
+/* Autotuner: raycasts the current volume from pose_c2w with every group size,
+ * over all tiles of the frame and (from 2048 tiles of 8x8 pixels on) from a list
+ * of those with something to march (`reps` timed launches each after one
+ * warm-up, HIP events on `stream`), keeps the fastest for later raycasts and
+ * reports its group size and mean time in milliseconds.  The choice of the list
+ * holds for frames of at least (or, where the list lost, at most) this size;
+ * untuned, frames of 8192 tiles and more take it.  Synchronises `stream`.  The outputs hold the last raycast. */
 tsdf_status tsdf_autotune_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, const double pose_c2w[12],
                                   float *vertex_dev, float *normal_dev, int32_t reps, hipStream_t stream,
                                   int32_t *best_group, float *best_ms);

@@ -80,6 +80,8 @@ __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, ui
 // span is background, and its part of the maps is cleared here; the others go to
 // the tile list, those with a long span at its front (their rays march longest
 // and must not start last), the rest from its back.
+// (hand at 1280x960, 8 lanes: 62 us with the line at 80 voxels, 75 at 20 or 320
+// and without one)
 constexpr int kTilesPerGroup = 16;
 constexpr float kLongSpan = 80.0f;   // voxels
 
@@ -150,19 +152,34 @@ __global__ __launch_bounds__(256) void tiles_kernel(VolumeView v, int width, int
 // at 4 lanes per ray; 640x480 orbit: 284 -> 246 us, now at 8 lanes per ray).
 constexpr int kRayWG = 64;
 
-// Frames of at least this many tiles march from a tile list: a wavefront takes
-// 1.2 us to find that its tile is background, G of them a tile, and where a
-// large frame shows one object most of it is.  1280x960 hand (19200 tiles, nine
-// in ten background, 4 lanes): 108 -> 79 us, and 10 us for the list; a 640x480
-// orbit frame (4800 tiles, all with something) 169 -> 174 us, and 9 us, so
-// smaller frames keep a wavefront for each G-th of every tile.
-constexpr int kListTiles = 8192;
-constexpr uint32_t kListGrid = 16384;   // workgroups striding over the list; a multiple of 8 * 16
+// March from a tile list.  A wavefront takes 1.2 us to find that its tile is
+// background, G of them a tile, and the list starts the tiles with long depth
+// spans first; it costs a launch of 9 us and wavefronts that take several tiles
+// each.  What it gives depends on the scene, which the host does not know, so a
+// frame of at least a volume's list_tiles takes it: kListTiles until
+// tsdf_autotune_raycast has timed both forms on a view.  Raycast with the list
+// and without, us (G lanes per ray; hand: nine tiles in ten background, orbit:
+// under half):
+//   1280x960 (19200 tiles)  hand    79 / 94 (G = 4)    62 / 95 (G = 8)
+//                           orbit  411 / 394, 332 / 310, 293 / 262 (1, 2, 4 mm, G = 4)
+//                                  499 / 481, 435 / 407, 396 / 366 (the same, G = 8)
+//   640x480 (4800 tiles)    hand    71 / 69            48 / 52
+//                           orbit  153 / 167, 119 / 121, 106 / 92 (1, 2, 4 mm, G = 4)
+//                                  162 / 166, 137 / 132, 126 / 112 (the same, G = 8)
+// Large frames lose up to 11 % one way and a third the other, so they take the
+// list by default; smaller ones gain or lose a tenth, and do not.
+//
+// kListGrid workgroups stride over the list: with 16384 the full frames took
+// 543 us (1 mm, G = 8) for 499, with one each the hand's took 67 for 62.
+constexpr uint32_t kListGrid = 65536;   // a multiple of 8 * 16
 
 enum MarchMode { kMarchAll, kMarchMark, kMarchList };
 
+// From the list four wavefronts a SIMD for the loop's few registers more (hand,
+// 8 lanes: 70 -> 62 us), but not with the 1 or 2 lanes per ray that would spill
+// for it (210 us, 188 without, at 1 lane).
 template <typename S, int G, bool kDense, MarchMode kMode>
-__global__ __launch_bounds__(kRayWG) __attribute__((amdgpu_waves_per_eu(kMode == kMarchList ? 4 : 1))) void raycast_kernel(
+__global__ __launch_bounds__(kRayWG) __attribute__((amdgpu_waves_per_eu(kMode == kMarchList && G >= 4 ? 4 : 1))) void raycast_kernel(
     VolumeView v, Camera cam, uint32_t stamp, int tiles_x, int tiles_y, float4 *__restrict__ vertex,
     float4 *__restrict__ normal)
 {
@@ -226,8 +243,8 @@ hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, 
     return hipGetLastError();
 }
 
-hipError_t launch_march(const VolumeView &v, const Camera &camera, uint32_t stamp, int group, float4 *vertex,
-                        float4 *normal, hipStream_t s, bool mark)
+hipError_t launch_march(const VolumeView &v, const Camera &camera, uint32_t stamp, int group, int list_tiles,
+                        float4 *vertex, float4 *normal, hipStream_t s, bool mark)
 {
     Camera cam = camera;
     set_ray_origin(cam, v);
@@ -238,7 +255,7 @@ hipError_t launch_march(const VolumeView &v, const Camera &camera, uint32_t stam
     dim3 grid((unsigned)((threads + unit - 1) / unit * (unit / kRayWG)));
     MarchMode mode = mark ? kMarchMark : kMarchAll;
     const int n_tiles = tiles_x * tiles_y;
-    if (!mark && n_tiles >= kListTiles) {
+    if (!mark && n_tiles >= list_tiles) {
         mode = kMarchList;
         grid = dim3(grid.x < kListGrid ? grid.x : kListGrid);
         hipLaunchKernelGGL(tiles_kernel, dim3((n_tiles + kTilesPerGroup - 1) / kTilesPerGroup), dim3(256), 0, s, v,

@@ -244,8 +244,11 @@ hipError_t launch_prep(const VolumeView &v, const float *depth, const Camera &ca
 hipError_t launch_fuse(const VolumeView &v, const Camera &cam, hipStream_t s);
 hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, hipStream_t s);
 hipError_t launch_count_bits(const uint32_t *bits, uint64_t words, unsigned long long *out, hipStream_t s);
-hipError_t launch_march(const VolumeView &v, const Camera &cam, uint32_t stamp, int group, float4 *vertex,
-                        float4 *normal, hipStream_t s, bool mark = false);
+// Frames of at least `list_tiles` 8x8-pixel tiles march from a list of them;
+// kListTiles is the default, kTuneListTiles the smallest frame worth timing both.
+constexpr int kListTiles = 8192, kTuneListTiles = 2048;
+hipError_t launch_march(const VolumeView &v, const Camera &cam, uint32_t stamp, int group, int list_tiles,
+                        float4 *vertex, float4 *normal, hipStream_t s, bool mark = false);
 hipError_t launch_export(const VolumeView &v, int32_t *keys, void *T, void *P, uint32_t cap, hipStream_t s);
 hipError_t launch_import(const VolumeView &v, const int32_t *keys, const void *T, const void *P, uint32_t n,
                          hipStream_t s);

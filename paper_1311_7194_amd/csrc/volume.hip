@@ -216,6 +216,7 @@ struct tsdf_volume {
     uint32_t host_flags;   // sticky flags seen by the last tsdf_query_stats
     uint32_t raycast_stamp;
     int32_t ray_group;     // lanes per ray in the raycast march (1, 2, 4, 8 or 16)
+    int32_t list_tiles;    // frames of at least this many tiles march from a list of them
     bool timing;
     std::vector<EventPair> pending;   // recorded, not yet read
     std::vector<hipEvent_t> spare;    // events ready for reuse
@@ -408,6 +409,7 @@ tsdf_status tsdf_create_volume(const tsdf_volume_desc *desc, void *dev_buf, uint
     w.max_height = desc->max_height;
     v->raycast_stamp = 0;
     v->ray_group = 8;
+    v->list_tiles = kListTiles;
     w.hash = (unsigned long long *)(v->base + L.hash);
     w.occ = (unsigned long long *)(v->base + L.occupancy);
     w.block_index = desc->dense_index ? (int32_t *)(v->base + L.block_index) : nullptr;
@@ -517,7 +519,8 @@ tsdf_status tsdf_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, const doubl
     hipError_t e = timed(vol, STAGE_RANGE, stream, [&] { return launch_range(w, cam, stamp, stream); });
     if (e == hipSuccess)
         e = timed(vol, STAGE_RAYCAST, stream, [&] {
-            return launch_march(w, cam, stamp, vol->ray_group, (float4 *)vertex_dev, (float4 *)normal_dev, stream);
+            return launch_march(w, cam, stamp, vol->ray_group, vol->list_tiles, (float4 *)vertex_dev,
+                                (float4 *)normal_dev, stream);
         });
     return hip_status(e);
 }
@@ -537,7 +540,8 @@ tsdf_status tsdf_raycast_footprint(tsdf_volume *vol, const tsdf_intrinsics *K, c
     if (e == hipSuccess) e = fill_u32((uint32_t *)count, 2, 0u, stream);
     if (e == hipSuccess) e = launch_range(w, cam, stamp, stream);
     if (e == hipSuccess)
-        e = launch_march(w, cam, stamp, vol->ray_group, (float4 *)vertex_dev, (float4 *)normal_dev, stream, true);
+        e = launch_march(w, cam, stamp, vol->ray_group, vol->list_tiles, (float4 *)vertex_dev, (float4 *)normal_dev,
+                         stream, true);
     if (e == hipSuccess) e = launch_count_bits(w.mark_bits, vol->layout.bitmap_words, count, stream);
     unsigned long long host = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&host, count, sizeof(host), hipMemcpyDeviceToHost, stream);
@@ -603,15 +607,21 @@ tsdf_status tsdf_autotune_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, co
         return TSDF_EINVAL;
     if (K->width > vol->desc.max_width || K->height > vol->desc.max_height) return TSDF_EINVAL;
     const int candidates[5] = {1, 2, 4, 8, 16};
+    // every group size with the march over all tiles and, where the frame is large
+    // enough for it, with the march from a tile list
+    const int tiles = ((K->width + 7) / 8) * ((K->height + 7) / 8), was_list = vol->list_tiles;
+    const int forms = tiles >= kTuneListTiles ? 2 : 1;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return TSDF_EHIP;
     const bool was_timing = vol->timing;
     vol->timing = false;
     float best = 3.4e38f;
-    int bestg = vol->ray_group;
+    int bestg = vol->ray_group, bestl = was_list;
     tsdf_status st = TSDF_OK;
-    for (int c = 0; c < 5 && st == TSDF_OK; ++c) {
-        vol->ray_group = candidates[c];
+    for (int c = 0; c < 5 * forms && st == TSDF_OK; ++c) {
+        vol->ray_group = candidates[c % 5];
+        vol->list_tiles = forms == 1 ? was_list : c < 5 ? (was_list > tiles ? was_list : tiles + 1)
+                                                        : (was_list < tiles ? was_list : tiles);
         st = tsdf_raycast(vol, K, pose_c2w, vertex_dev, normal_dev, stream);   // warm-up
         if (st != TSDF_OK) break;
         if (hipEventRecord(e0, stream) != hipSuccess) st = TSDF_EHIP;
@@ -622,13 +632,15 @@ tsdf_status tsdf_autotune_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, co
             st = TSDF_EHIP;
         if (st == TSDF_OK && ms / reps < best) {
             best = ms / reps;
-            bestg = candidates[c];
+            bestg = candidates[c % 5];
+            bestl = vol->list_tiles;
         }
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     vol->timing = was_timing;
     vol->ray_group = bestg;
+    vol->list_tiles = bestl;
     *best_group = bestg;
     *best_ms = best;
     return st;

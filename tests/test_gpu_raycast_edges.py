@@ -1,5 +1,5 @@
 """The raycast where its shortcuts could show: the refinement inside a cell, rays
-with many brackets that are none (needs an MI355X)."""
+with many brackets that are none, marches from a tile list (needs an MI355X)."""
 
 import numpy as np
 import pytest
@@ -141,3 +141,67 @@ def test_candidates_without_a_crossing(tsdf):
     assert np.mean(got[inner]) > 0.999
     assert np.linalg.norm(vert[hit, :3] - want, axis=1)[got].max() < 1e-4   # a bracket of the search
     assert np.mean(np.linalg.norm(vert[hit, :3] - want, axis=1)[got] < 4e-6) > 0.99
+
+
+@pytest.fixture(scope="module")
+def shells():
+    """Blocks of a sphere and a plane inside a 128^3 grid, half-precision values."""
+    n = 128
+    q = np.arange(n) + 0.5
+    x, y, z = np.meshgrid(q, q, q, indexing="ij")
+    T = np.minimum(np.sqrt((x - 64) ** 2 + (y - 64) ** 2 + (z - 64) ** 2) - 40, y - 10) / 4
+    T[np.abs(T) > 1] = 2.0
+    T = T.astype(np.float16)
+    keys, blocks = [], []
+    for k in np.ndindex(n // 8, n // 8, n // 8):
+        t = T[tuple(slice(8 * a, 8 * a + 8) for a in k)]
+        if (t <= 1).any():
+            keys.append(k)
+            blocks.append(t.transpose(2, 1, 0).reshape(-1))
+    return n, torch.tensor(keys, dtype=torch.int32), torch.from_numpy(np.stack(blocks))
+
+
+def shells_volume(tsdf, shells, storage, dense, W, H):
+    n, keys, T = shells
+    gv = tsdf.Volume((n, n, n), 0.01, (0.0, 0.0, 0.0), 4.0, 4096, 8192, storage, 1e-4, W, H, dense_index=dense)
+    gv.import_blocks(keys, T.to(gv.elem_dtype), torch.full(T.shape, 1e-3))
+    return gv
+
+
+@pytest.mark.parametrize("group,dense", [(1, False), (2, True), (8, True), (16, False)])
+def test_half_precision_from_a_tile_list(tsdf, shells, group, dense):
+    """A ragged half-precision frame of 8320 tiles against its two halves, which
+    march every tile: bitwise the same."""
+    W, H, cut = 1037, 509, 520
+    gv = shells_volume(tsdf, shells, 1, dense, W, H)
+    gv.set_raycast_group(group)
+    pose = look_at((-0.9, 1.6, -1.1), (0.6, 0.5, 0.6))
+    out = {}
+    for x0, x1 in ((0, W), (0, cut), (cut, W)):
+        maps = [torch.full((H, x1 - x0, 4), float("nan"), device="cuda") for _ in range(2)]
+        gv.raycast(Intrinsics(700.0, 700.0, 500.25 - x0, 250.5, x1 - x0, H), pose, *maps)
+        torch.cuda.synchronize()
+        out[x0, x1] = maps
+    hits = int((out[0, W][0][..., 3] > 0).sum())
+    assert 20000 < hits < 0.9 * W * H
+    for m in range(2):
+        assert torch.equal(out[0, W][m], torch.cat((out[0, cut][m], out[cut, W][m]), 1))
+
+
+@pytest.mark.parametrize("W,H", [(120, 90), (512, 255), (512, 256), (801, 650), (1040, 512)])
+@pytest.mark.parametrize("storage", [0, 1])
+def test_autotuned_form_gives_the_same_maps(tsdf, shells, W, H, storage):
+    """Frames below and above the sizes from which the list is timed (2048 tiles)
+    and taken untuned (8192): whatever the autotuner keeps, the maps of that frame
+    and of smaller and larger ones are bitwise those before."""
+    gv = shells_volume(tsdf, shells, storage, True, 1100, 700)
+    pose = look_at((-0.9, 1.6, -1.1), (0.6, 0.5, 0.6))
+    Ks = [Intrinsics(0.7 * w, 0.7 * w, 0.48 * w, 0.49 * h, w, h) for w, h in ((W, H), (160, 120), (1100, 700))]
+    before = [gv.raycast(K, pose) for K in Ks]
+    group, ms = gv.autotune_raycast(Ks[0], pose)
+    assert group in (1, 2, 4, 8, 16) and gv.raycast_group == group and ms > 0
+    for K, maps in zip(Ks, before):
+        assert int((maps[0][..., 3] > 0).sum()) > 1000
+        after = [torch.full_like(m, float("nan")) for m in maps]
+        gv.raycast(K, pose, *after)
+        assert all(torch.equal(a, b) for a, b in zip(maps, after))
