@@ -169,14 +169,14 @@ tsdf_status tsdf_integrate_frame(tsdf_volume *vol, const float *depth_dev, const
 tsdf_status tsdf_raycast(tsdf_volume *vol, const tsdf_intrinsics *K, const double pose_c2w[12],
                          float *vertex_dev, float *normal_dev, hipStream_t stream);
 
-/* The raycast above, also counting the blocks that the samples it evaluates
- * are based in (each block once, however many rays read it; samples decided
- * from the blocks' bit records alone are not evaluated, and a group of lanes
- * evaluates a step's together, so the count depends a little on the group
- * size).  This is the data the raycast reads from the pool: the measure of its
- * algorithmic traffic.  The maps are bitwise those of tsdf_raycast.  Runs an
- * instrumented copy of the march (not the one tsdf_raycast times) and
- * synchronises `stream` to return *blocks_out. */
+/* The raycast above, also counting the blocks whose voxels the rays' samples are
+ * based in, from the start of a ray's depth span to its crossing, as many
+ * samples a step as lanes march a ray (each block once, however many rays read
+ * it).  This is the data that a raycast by the definition above must read from
+ * the pool: the measure of its algorithmic traffic (tsdf_raycast decides most
+ * samples from bit records of the blocks and reads fewer voxels).  The maps are
+ * bitwise those of tsdf_raycast.  Runs an instrumented copy of the march (not
+ * the one tsdf_raycast times) and synchronises `stream` to return *blocks_out. */
 tsdf_status tsdf_raycast_footprint(tsdf_volume *vol, const tsdf_intrinsics *K, const double pose_c2w[12],
                                    float *vertex_dev, float *normal_dev, uint64_t *blocks_out,
                                    hipStream_t stream);

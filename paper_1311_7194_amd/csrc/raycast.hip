@@ -76,6 +76,56 @@ __global__ __launch_bounds__(256) void range_kernel(VolumeView v, Camera cam, ui
     }
 }
 
+// Footprint query: widens the spans that range_kernel left to those of the
+// samples whose voxels may all hold a distance, a lane per allocated block: q in
+// the box of the block's non-chi voxels, extended by one voxel upwards.
+__global__ __launch_bounds__(256) void footprint_range_kernel(VolumeView v, Camera cam, uint32_t stamp, int tiles_x,
+                                                              int tiles_y)
+{
+    const uint32_t n = min(v.state->pool_count, v.capacity);
+    const int cw = (cam.width + kCell - 1) / kCell, ch = (cam.height + kCell - 1) / kCell;
+    for (uint32_t slot = blockIdx.x * 256u + threadIdx.x; slot < n; slot += gridDim.x * 256u) {
+        const uint32_t key = v.pool_keys[slot];
+        if (key == kEmptyKey) continue;
+        const unsigned long long *m = (const unsigned long long *)v.masks[slot].value;
+        unsigned long long all = 0;
+        uint32_t xb = 0, yb = 0, zb = 0;
+        for (int y = 0; y < 8; ++y) {
+            all |= m[y];
+            yb |= (m[y] ? 1u : 0u) << y;
+        }
+        if (!all) continue;
+        for (int x = 0; x < 8; ++x) {
+            const uint32_t col = (uint32_t)(all >> (8 * x)) & 0xffu;
+            xb |= (col ? 1u : 0u) << x;
+            zb |= col;
+        }
+        const int lo[3] = {__builtin_ctz(xb), __builtin_ctz(yb), __builtin_ctz(zb)};
+        const int hi[3] = {32 - __builtin_clz(xb), 32 - __builtin_clz(yb), 32 - __builtin_clz(zb)};
+        int bx, by, bz;
+        unpack_key(key, bx, by, bz);
+        const BoxView w = project_box(v, cam, bx, by, bz, lo, hi);
+        if (!w.visible) continue;
+        if (w.behind) {
+            v.state->near_stamp = stamp;
+            continue;
+        }
+        const uint32_t zl = __float_as_uint(fmaxf(w.zlo * (1.0f - 1e-5f) - 1e-6f, 0.0f));
+        const uint32_t zh = __float_as_uint(w.zhi * (1.0f + 1e-5f) + 1e-6f);
+        int c0 = w.i0 / kCell, c1 = w.i1 / kCell, d0 = w.j0 / kCell, d1 = w.j1 / kCell, width = cw;
+        uint32_t *smin = v.pix_range, *smax = smin + (size_t)cw * ch;
+        if ((c1 - c0 + 1) * (d1 - d0 + 1) > kCellFootprint) {   // large: whole tiles
+            c0 = w.i0 / kRT, c1 = w.i1 / kRT, d0 = w.j0 / kRT, d1 = w.j1 / kRT, width = tiles_x;
+            smin = v.tile_range, smax = smin + (size_t)tiles_x * tiles_y;
+        }
+        for (int d = d0; d <= d1; ++d)
+            for (int c = c0; c <= c1; ++c) {
+                atomicMin(&smin[(size_t)d * width + c], zl);
+                atomicMax(&smax[(size_t)d * width + c], zh);
+            }
+    }
+}
+
 // Sorts the frame's 8x8-pixel tiles, kTilesPerGroup to a workgroup: a tile without a depth
 // span is background, and its part of the maps is cleared here; the others go to
 // the tile list, those with a long span at its front (their rays march longest
@@ -240,6 +290,13 @@ hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, 
         hipLaunchKernelGGL(range_kernel<true>, dim3(2048), dim3(256), 0, s, v, cam, stamp, tiles_x, tiles_y);
     else
         hipLaunchKernelGGL(range_kernel<false>, dim3(2048), dim3(256), 0, s, v, cam, stamp, tiles_x, tiles_y);
+    return hipGetLastError();
+}
+
+hipError_t launch_footprint_range(const VolumeView &v, const Camera &cam, uint32_t stamp, hipStream_t s)
+{
+    hipLaunchKernelGGL(footprint_range_kernel, dim3(1024), dim3(256), 0, s, v, cam, stamp, (cam.width + kRT - 1) / kRT,
+                       (cam.height + kRT - 1) / kRT);
     return hipGetLastError();
 }
 

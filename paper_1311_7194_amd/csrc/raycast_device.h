@@ -510,9 +510,65 @@ __device__ __forceinline__ int cell_exit_sample(const Ray &r, const int B[3], in
 template <int G>
 __device__ __forceinline__ int group_lane(int lane, int src) { return (lane & ~(G - 1)) | src; }
 
+// Whether no voxel of the block in `slot` and its upper neighbours is at or below zero.
+__device__ __forceinline__ bool all_positive(const VolumeView &v, int32_t slot)
+{
+    unsigned long long any = 0;
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t s = v.recs[slot].base[k] / (uint32_t)kBlockVoxels;
+        if (s >= v.capacity) continue;   // absent
+        const unsigned long long *m = (const unsigned long long *)v.masks[s].inside;
+        for (int y = 0; y < 8; ++y) any |= m[y];
+    }
+    return any == 0;
+}
+
+// The footprint query's march: sets the bit of every allocated block that a
+// sample is based in, from the ray's depth span's start to the crossing at
+// sample n_hit, where a group takes G samples a step (those of the crossing's
+// step count whole) and jumps over the rest of a block that is absent or, with
+// its upper neighbours, holds no value at or below zero.
+template <int G, bool kDense>
+__device__ void mark_blocks(const VolumeView &v, const Ray &r, int n_lo, int n_end, int n_hit, bool active, double h,
+                            double inv_h)
+{
+    const int lane = threadIdx.x & 63, j = lane & (G - 1);
+    int n_base = n_lo;
+    bool done = !(active && n_lo <= n_end);
+    while (__ballot(!done)) {
+        double q[3];
+        q_at(r, (double)(n_base + j) * h, q);
+        int c[3];
+        float f[3];
+        uint32_t info = kEmptyKey;   // of the last sample, if it decides a jump (bit 30: absent block)
+        if (!done && n_base + j <= n_end && stencil(v, q, c, f)) {
+            const int bx = c[0] >> 3, by = c[1] >> 3, bz = c[2] >> 3;
+            const int32_t slot = block_slot<kDense>(v, bx, by, bz);
+            if (slot >= 0) {
+                const uint64_t b = block_linear(v, bx, by, bz);
+                atomicOr(&v.mark_bits[b >> 5], 1u << (b & 31));
+            }
+            if (j == G - 1 && (slot < 0 || all_positive(v, slot)))
+                info = pack_key(bx, by, bz) | (slot < 0 ? 1u << 30 : 0u);
+        }
+        info = (uint32_t)__shfl((int)info, group_lane<G>(lane, G - 1));
+        if (!done) {
+            const int last = n_base + G - 1;
+            n_base = last + 1;
+            if (info != kEmptyKey) {
+                int B[3];
+                unpack_key(info, B[0], B[1], B[2]);
+                // (the last sample of a positive block can begin a bracket)
+                n_base = max(n_base, cell_exit_sample(r, B, 0, h, inv_h) - (info >> 30 ? 0 : 1));
+            }
+            done = last >= n_hit || n_base > n_end;
+        }
+    }
+}
+
 // Thread `gt` of a launch space of (tiles x 64 rays x G lanes) for one frame.
-// kMark: also set the bit of every block a march sample is based in (the
-// footprint query; the timed raycast is instantiated without it).
+// kMark: also set the bit of every block a sample up to the crossing is based
+// in (the footprint query; the timed raycast is instantiated without it).
 template <typename S, int G, bool kDense, bool kMark = false>
 __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &cam, uint32_t stamp, int tiles_x,
                                              int tiles_y, float4 *__restrict__ vertex, float4 *__restrict__ normal,
@@ -712,14 +768,6 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
                 double q[3];
                 q_at(r, (double)n * h, q);
                 F[t] = sample<S, kDense>(v, cache, q);
-                if constexpr (kMark) {
-                    if (F[t] == F[t]) {
-                        int bx, by, bz;
-                        unpack_key(cache.key, bx, by, bz);
-                        const uint64_t lb = block_linear(v, bx, by, bz);
-                        atomicOr(&v.mark_bits[lb >> 5], 1u << (lb & 31));
-                    }
-                }
             }
         }
         int first = 0;   // the crossing ends at sample n0 + first (0: none)
@@ -753,6 +801,8 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
             }
         }
     }
+
+    if constexpr (kMark) mark_blocks<G, kDense>(v, r, n_lo, n_end, hit ? (int)rint(s_hi * inv_h) : 2147483647, active, h, inv_h);
 
     // ---- refinement: quaternary search inside [s_lo, s_hi] (F_lo > 0 >= F_hi),
     // six steps that shrink the bracket 4096-fold.  Each looks at the 3 inner

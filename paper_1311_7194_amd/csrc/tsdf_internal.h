@@ -73,7 +73,7 @@ struct VolumeView {
     uint32_t *tile_list;        // raycast: the frame's tiles with something to march
     uint32_t *tile_range;       // raycast: per 8x8 pixel tile (min depth bits, max depth bits)
     uint32_t *pix_range;        // raycast: per kCell x kCell pixel cell (min depth bits, max depth bits)
-    uint32_t *mark_bits;        // one bit per virtual block: blocks a footprint query's rays read
+    uint32_t *mark_bits;        // one bit per virtual block: blocks a footprint query's samples are based in
     unsigned long long *occ;    // allocated blocks: a bit each, a word per 4^3 blocks (see occ_*), then the
                                 // same over those words
     uint32_t occ_words;         // words of the first level
@@ -243,6 +243,7 @@ hipError_t launch_prep(const VolumeView &v, const float *depth, const Camera &ca
                        hipStream_t s);
 hipError_t launch_fuse(const VolumeView &v, const Camera &cam, hipStream_t s);
 hipError_t launch_range(const VolumeView &v, const Camera &cam, uint32_t stamp, hipStream_t s);
+hipError_t launch_footprint_range(const VolumeView &v, const Camera &cam, uint32_t stamp, hipStream_t s);
 hipError_t launch_count_bits(const uint32_t *bits, uint64_t words, unsigned long long *out, hipStream_t s);
 // Frames of at least `list_tiles` 8x8-pixel tiles march from a list of them;
 // kListTiles is the default, kTuneListTiles the smallest frame worth timing both.

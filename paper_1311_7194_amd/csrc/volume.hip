@@ -539,6 +539,7 @@ tsdf_status tsdf_raycast_footprint(tsdf_volume *vol, const tsdf_intrinsics *K, c
     hipError_t e = fill_u32(w.mark_bits, vol->layout.bitmap_words, 0u, stream);
     if (e == hipSuccess) e = fill_u32((uint32_t *)count, 2, 0u, stream);
     if (e == hipSuccess) e = launch_range(w, cam, stamp, stream);
+    if (e == hipSuccess) e = launch_footprint_range(w, cam, stamp, stream);
     if (e == hipSuccess)
         e = launch_march(w, cam, stamp, vol->ray_group, vol->list_tiles, (float4 *)vertex_dev, (float4 *)normal_dev,
                          stream, true);

@@ -205,3 +205,45 @@ def test_autotuned_form_gives_the_same_maps(tsdf, shells, W, H, storage):
         after = [torch.full_like(m, float("nan")) for m in maps]
         gv.raycast(K, pose, *after)
         assert all(torch.equal(a, b) for a, b in zip(maps, after))
+
+
+@pytest.mark.parametrize("group,storage,dense", [(1, 0, True), (8, 0, False), (16, 1, True)])
+def test_footprint_counts_the_blocks_of_all_samples(tsdf, shells, group, storage, dense):
+    """The count holds every block that a valid sample up to a ray's crossing is
+    based in, not those of the samples around the crossing alone, and none
+    but allocated blocks with a sample up to the crossing's step."""
+    W, H = 160, 120
+    n, keys, blocks = shells
+    gv = shells_volume(tsdf, shells, storage, dense, W, H)
+    gv.set_raycast_group(group)
+    T = np.full((n, n, n), 2.0, np.float32)
+    allocated = np.zeros((n // 8,) * 3, bool)
+    for k, b in zip(keys.tolist(), blocks.float().numpy()):
+        T[tuple(slice(8 * a, 8 * a + 8) for a in k)] = b.reshape(8, 8, 8).transpose(2, 1, 0)
+        allocated[tuple(k)] = True
+    K = Intrinsics(112.0, 112.0, 76.8, 58.8, W, H)
+    pose = look_at((-0.9, 1.6, -1.1), (0.6, 0.5, 0.6))
+    d = rays(K, pose)
+    q0 = pose[:, 3] / 0.01 - 0.5
+    chi = T > 1
+    need, may = np.zeros_like(allocated), np.zeros_like(allocated)
+    prev, over = np.full(W * H, np.nan), np.zeros(W * H, int)   # over: samples past the crossing
+    for s in range(1, 900):
+        live = over < group
+        q = q0 + 0.5 * s * d
+        live &= ((q >= 0) & (q < n - 1)).all(1)
+        c = np.floor(q[live]).astype(int)
+        B = tuple((c >> 3).T)
+        may[B] |= allocated[B]
+        ok = ~np.any([chi[c[:, 0] + (e & 1), c[:, 1] + (e >> 1 & 1), c[:, 2] + (e >> 2)] for e in range(8)], axis=0)
+        F = np.full(W * H, np.nan)
+        F[live] = np.where(ok, trilinear(T, q[live], np.float32), np.nan)
+        first = ok & (over[live] == 0)
+        need[tuple((c[first] >> 3).T)] = True
+        over += (over > 0) | ((prev > 0) & (F <= 0))
+        prev = F
+    count, vert, _ = gv.raycast_footprint(K, pose)
+    print(f"[raycast] footprint {count} blocks, {need.sum()} with a valid sample, {may.sum()} with any", flush=True)
+    assert int((vert[..., 3] > 0).sum()) > 1000
+    assert need.sum() - 1 <= count <= may.sum() + 1   # (a sample within rounding of a border)
+    assert need.sum() > 300
