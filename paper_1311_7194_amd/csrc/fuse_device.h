@@ -271,16 +271,15 @@ __device__ __forceinline__ void prep_body(const VolumeView &v, const float *__re
 // start from the exact coordinates of the column's first voxel plus z times
 // that step, which differs from the defined double expression by at most
 // `err` metres.  The pixel index is taken from them in single precision; where
-// the image point lies within `eu`, `ev` of a pixel boundary, or the depth
-// below `zmin`, and for |s| within `thr_s` of delta, the defined expression
-// decides.
+// the image point lies within a margin of a pixel boundary, and for |s| within
+// `thr_s` of delta, the defined expression decides.
 struct FuseCam {
     double sz;           // camera-depth step per voxel along grid z
     double thr_s;        // |s| within thr_s of delta: decided by the defined expression
     float dX, dY, dZ;    // steps of fx x_c, fy y_c, z_c
     float cxh, cyh;      // cx + 1/2, cy + 1/2
-    float zmin;          // smallest depth that single precision decides
-    float hu, hv;        // 1/2 - eu, 1/2 - ev
+    float half;          // 1/2 less the margin far away
+    float k;             // the margin's growth with 1 / depth
 };
 
 __host__ __device__ inline FuseCam make_fuse_cam(const VolumeView &v, const Camera &cam)
@@ -305,36 +304,41 @@ __host__ __device__ inline FuseCam make_fuse_cam(const VolumeView &v, const Came
     f.thr_s = 4.0 * err + 64.0 * ulp * M;
     // Pixel margin, e = 2^-24.  X = fx x_c as a float column start plus z dX is
     // off by e (2 |X| + 14 |dX|), Z by e (2 Z + 14 vs), the hardware reciprocal
-    // by 2 e.  With Z >= 64 vs (and a float's rounding of that) the image point
-    // w = X / Z is off by e (2 + 4 + 1) |w| + e fx / 4, and adding cx + 1/2 by
+    // by 2 e, so the image point w = X / Z by e (2 + 2 + 2) |w| and, with
+    // |dX| <= fx vs, e 14 vs (fx + |w|) / Z; adding cx + 1/2 is off by
     // e (|u| + |cx| + 1); |w| <= max(|cx|, |W - cx|) + 2 and |u| <= W + 2
     // wherever the decision can be near a pixel boundary inside the image.  A
-    // quarter more than the sum, and `err` against the defined expression.
+    // quarter more than the sum, and `err` against the defined expression.  (Second
+    // order: Z is off by at most 0.4 / (fx + |w|) of itself where the margin leaves
+    // anything to decide.)  The part with 1 / Z is taken at a column's smallest
+    // depth.  Taken at 64 voxels for all, with everything nearer left to the defined
+    // expression, it cost frames of coarse volumes and close objects 3 % of their
+    // fusion.  One margin for both axes: with two the constants spill (35 -> 38 us
+    // at 640x480 and 2 mm).
     const double e = 5.9604644775390625e-08;
-    const double zmin = fmax(64.0 * v.vs, 1e-30);
-    f.zmin = (float)(zmin * (1.0 + 8.0 * e));
     const double wu = fmax(fabs(cam.cx), fabs(cam.width - cam.cx)) + 2.0;
     const double wv = fmax(fabs(cam.cy), fabs(cam.height - cam.cy)) + 2.0;
-    const double eu = 1.25 * e * (7.0 * wu + 0.25 * cam.fx + cam.width + fabs(cam.cx) + 4.0) +
-                      2.0 * err * (cam.fx + wu) / zmin;
-    const double ev = 1.25 * e * (7.0 * wv + 0.25 * cam.fy + cam.height + fabs(cam.cy) + 4.0) +
-                      2.0 * err * (cam.fy + wv) / zmin;
-    // (negative: everything is decided by the defined expression; rounded down)
-    f.hu = (float)((0.5 - eu) - 1e-7);
-    f.hv = (float)((0.5 - ev) - 1e-7);
+    const double eu = 1.25 * e * (7.0 * wu + cam.width + fabs(cam.cx) + 4.0);
+    const double ev = 1.25 * e * (7.0 * wv + cam.height + fabs(cam.cy) + 4.0);
+    // (negative: everything is decided by the defined expression; rounded towards that)
+    f.half = (float)((0.5 - fmax(eu, ev)) - 1e-7);
+    // (image points that single precision cannot hold: none is decided from it, so
+    // that no NaN reaches the filter's maximum)
+    if (!(fmax(cam.fx, cam.fy) * M < 1e30 && M < 1e30 * v.vs)) f.half = -1.0f;
+    f.k = (float)((1.25 * 14.0 * e * v.vs + 2.0 * err) * (fmax(cam.fx, cam.fy) + fmax(wu, wv)) * (1.0 + 1e-5));
     return f;
 }
 
 // Nearest-pixel index from single-precision X = fx x_c, Y = fy y_c and Z = z_c:
 // the linear pixel index, -1 outside the image; `sure` is cleared where only
-// the defined expression can decide.
-__device__ __forceinline__ int pixel_filter(int width, int height, const FuseCam &fc, float X, float Y, float Z,
-                                            bool &sure)
+// the defined expression can decide (half: 1/2 less the column's margin).
+__device__ __forceinline__ int pixel_filter(int width, int height, const FuseCam &fc, float half, float X, float Y,
+                                            float Z, bool &sure)
 {
     const float r = __builtin_amdgcn_rcpf(Z);
     const float tu = fmaf(X, r, fc.cxh), tv = fmaf(Y, r, fc.cyh);
     const float fu = floorf(tu), fv = floorf(tv);
-    sure = Z >= fc.zmin && fabsf((tu - fu) - 0.5f) < fc.hu && fabsf((tv - fv) - 0.5f) < fc.hv;
+    sure = fmaxf(fabsf((tu - fu) - 0.5f), fabsf((tv - fv) - 0.5f)) < half;
     const int i = (int)fu, j = (int)fv;   // (saturating far outside the image)
     return ((uint32_t)i < (uint32_t)width && (uint32_t)j < (uint32_t)height) ? j * width + i : -1;
 }
@@ -499,10 +503,12 @@ __device__ __forceinline__ void fuse_block(const VolumeView &v, const Camera &ca
     // phase 1: the pixel decisions of the column in single precision
     int pix[8];
     uint32_t unsure = 0;
+    const float Zc = fminf(Z0, fmaf(7.0f, fc.dZ, Z0));   // the column's smallest depth
+    const float half = Zc > 0.0f ? fc.half - fc.k * __builtin_amdgcn_rcpf(Zc) : -1.0f;
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         bool sure;
-        pix[z] = pixel_filter(cam.width, cam.height, fc, fmaf((float)z, fc.dX, X0), fmaf((float)z, fc.dY, Y0),
+        pix[z] = pixel_filter(cam.width, cam.height, fc, half, fmaf((float)z, fc.dX, X0), fmaf((float)z, fc.dY, Y0),
                               fmaf((float)z, fc.dZ, Z0), sure);
         unsure |= (sure ? 0u : 1u) << z;
     }
