@@ -513,14 +513,18 @@ __device__ __forceinline__ int group_lane(int lane, int src) { return (lane & ~(
 // Whether no voxel of the block in `slot` and its upper neighbours is at or below zero.
 __device__ __forceinline__ bool all_positive(const VolumeView &v, int32_t slot)
 {
-    unsigned long long any = 0;
+    const BlockRec *rec = v.recs + slot;
+    if (rec->box) return false;   // one of its cells has such a voxel
     for (int k = 0; k < 8; ++k) {
-        const uint32_t s = v.recs[slot].base[k] / (uint32_t)kBlockVoxels;
+        const uint32_t s = rec->base[k] / (uint32_t)kBlockVoxels;
         if (s >= v.capacity) continue;   // absent
         const unsigned long long *m = (const unsigned long long *)v.masks[s].inside;
+        unsigned long long any = 0;
+#pragma unroll
         for (int y = 0; y < 8; ++y) any |= m[y];
+        if (any) return false;
     }
-    return any == 0;
+    return true;
 }
 
 // The footprint query's march: sets the bit of every allocated block that a
@@ -546,7 +550,7 @@ __device__ void mark_blocks(const VolumeView &v, const Ray &r, int n_lo, int n_e
             const int32_t slot = block_slot<kDense>(v, bx, by, bz);
             if (slot >= 0) {
                 const uint64_t b = block_linear(v, bx, by, bz);
-                atomicOr(&v.mark_bits[b >> 5], 1u << (b & 31));
+                if (!((v.mark_bits[b >> 5] >> (b & 31)) & 1u)) atomicOr(&v.mark_bits[b >> 5], 1u << (b & 31));
             }
             if (j == G - 1 && (slot < 0 || all_positive(v, slot)))
                 info = pack_key(bx, by, bz) | (slot < 0 ? 1u << 30 : 0u);
@@ -815,7 +819,8 @@ __device__ __forceinline__ void raycast_body(const VolumeView &v, const Camera &
     // bracket, along with the normal's samples, and where they do not enclose the
     // crossing (a root within rounding of an end) the ray goes on with sampled
     // steps.  The crossing is that of six sampled steps, whatever the cubic's
-    // rounding (taken from the cubic, it was off by 1.2 times as much).
+    // rounding (taken from the cubic, it was off by 1.2 times as much); the
+    // normal's samples are placed by the cubic's own, 1e-7 voxel beside it.
     constexpr int kPts = 3, kSteps = 6, kRounds = (kPts + G - 1) / G;
     double a = s_lo, b = s_hi;
     float Fa = F_lo, Fb = F_hi;
