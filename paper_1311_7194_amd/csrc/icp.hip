@@ -381,7 +381,8 @@ __device__ __forceinline__ double wave_total10(const double v[10])
 // maxima); from there on one wavefront works with a lane per matrix entry.  A
 // single thread for the system, the back-substitution and the pose, and an
 // eigen-decomposition that exchanged the matrix between lanes: 14.3 us at
-// 160x120 and 15.9 at 640x480, now 10.1 and 10.7.
+// 160x120 and 15.9 at 640x480, now 11.0 and 11.5 (means over chains of ten
+// iterations from a nearby pose; 15 us at 640x480 between frames 7.5 cm apart).
 __global__ __launch_bounds__(kIcpThreads) void icp_solve_kernel(const double *__restrict__ partial, int groups,
                                                                 const double *__restrict__ pose, IcpArgs a,
                                                                 tsdf_icp_result *__restrict__ res,

@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kMcLanes) void mc_emit_kernel(VolumeView v, const u
                 const uint32_t e = L.owner[tri];
                 const int cx = (int)(e & 7u), cy = (int)(e >> 3 & 7u), cz = (int)(e >> 6 & 7u);
                 const int ed = (int)(e >> (9u + 4u * j) & 15u);
-                const int a = ed >> 2, m = ed & 3;   // mc_edge_lo in arithmetic
+                const int a = ed >> 2, m = ed & 3;   // the edge's lower corner
                 const int lx = a == 0 ? 0 : m & 1, ly = a == 0 ? m & 1 : a == 2 ? m >> 1 : 0, lz = a == 2 ? 0 : m >> 1;
                 const int dx = cx + lx, dy = cy + ly, dz = cz + lz;
                 const int at = tidx(dx, dy, dz), step = a == 0 ? 1 : a == 1 ? kTile : kTile * kTile;

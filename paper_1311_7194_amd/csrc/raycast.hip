@@ -34,12 +34,17 @@
 // What bounds it: instruction issue and the chains of dependent loads (the
 // march's two per step), not bytes.  Evaluating F at every sample of the band
 // kept the vector units 80 % busy on the 640x480 orbit (1 mm); with the
-// records, the refinement finishing on the ray's cubic inside a cell, in one
-// pass after the sampled steps, and a ray's setup without divisions and square
-// roots in the library's form: 263 -> 169 us there (8 lanes per ray, a step of
-// 32 samples), 20 -> 15 us at 160x120, 128 -> 108 us on the 1280x960 hand
-// (0.15 mm, 4 lanes; 79 us from a list of its tiles, see kListTiles), 188 ->
-// 88 us with the hash only (4 mm, FP16).
+// records, a ray's cubic inside a cell in place of most of the refinement's
+// dependent steps, and a ray's setup without divisions and square roots in the
+// library's form: 263 -> 168 us there (8 lanes per ray, a step of 32 samples),
+// 20 -> 17 us at 160x120, 128 -> 94 us on the 1280x960 hand (0.15 mm, 4 lanes;
+// 78 us from a list of its tiles, see kListGrid), 188 -> 67 us with the hash only
+// (4 mm, FP16).  The records make the range pass longer (eight neighbour lookups
+// for each block in view: 34 -> 49 us at 640x480, 6.8 -> 11 us at 160x120), which
+// the march repays also where few rays look at many blocks: views of 16x12 to
+// 640x480 pixels of a room scanned from ten sides (253,000 blocks, 1 mm), from
+// far away, from its side and from inside, take 155-328 us without them and
+// 40-271 us with them.
 #include "raycast_device.h"
 
 namespace tsdf {

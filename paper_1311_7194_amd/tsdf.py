@@ -258,7 +258,7 @@ class Volume:
 
     def raycast_footprint(self, K, pose, vertex: Optional[torch.Tensor] = None,
                           normal: Optional[torch.Tensor] = None, stream=None):
-        """(blocks read by the march, vertex, normal); synchronises."""
+        """(blocks that the rays' samples are based in, vertex, normal); synchronises."""
         intr = make_intrinsics(K)
         shape = (intr.height, intr.width, 4)
         if vertex is None:
